@@ -123,29 +123,50 @@ def _spec(case):
     return _lengths_of(*(case[k] for k in ("chunk", "chunk_prefix", "n_chunks", "decodes", "kv", "median", "kv_lo", "kv_hi", "lengths")))
 
 
-def _load_layers(eng, n_layers, gen):
-    m = eng.model
+def _layer_weights(m, n_layers, gen, device):
+    """The weight matrices of one layer after another, drawn into the same buffers (the gains are ones)."""
     H, F, d = m["hidden"], m["ffn"], m["head_dim"]
     shapes = {"w_qkv": (H, (m["n_q"] + 2 * m["n_kv"]) * d), "w_o": (m["n_q"] * d, H), "w_gate": (H, F), "w_up": (H, F), "w_down": (F, H)}
-    one = torch.ones(H, dtype=torch.bfloat16, device=eng.device)
-    w = {k: torch.empty(s, dtype=torch.bfloat16, device=eng.device) for k, s in shapes.items()}
-    for layer in range(n_layers):
+    w = {k: torch.empty(s, dtype=torch.bfloat16, device=device) for k, s in shapes.items()}
+    for _ in range(n_layers):
         for t in w.values():
             t.normal_(0.0, W.WEIGHT_STD, generator=gen)
+        yield w
+
+
+def _layer_prefixes(m, n_layers, prefixes, gen, device):
+    """N(0, 1) keys and values of one layer after another; request i's are the rows from 16 i on."""
+    rows = max(prefixes) + 16 * len(prefixes)
+    k = torch.empty((rows, m["n_kv"], m["head_dim"]), dtype=torch.bfloat16, device=device)
+    v = torch.empty_like(k)
+    for _ in range(n_layers):
+        k.normal_(generator=gen)
+        v.normal_(generator=gen)
+        yield k, v
+
+
+def _head(m, gen, device):
+    emb = torch.empty((VOCAB, m["hidden"]), dtype=torch.bfloat16, device=device).normal_(generator=gen)
+    w_out = torch.empty((m["hidden"], VOCAB), dtype=torch.bfloat16, device=device).normal_(0.0, W.WEIGHT_STD, generator=gen)
+    return emb, w_out
+
+
+def _generator(seed):
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(int(seed) * 1000003 + 17)
+    return gen
+
+
+def _load_layers(eng, n_layers, gen):
+    one = torch.ones(eng.model["hidden"], dtype=torch.bfloat16, device=eng.device)
+    for layer, w in enumerate(_layer_weights(eng.model, n_layers, gen, eng.device)):
         eng.ctx.init_layer(layer, g_attn=one.data_ptr(), g_ffn=one.data_ptr(), **{k: t.data_ptr() for k, t in w.items()})
     eng.ctx.sync()
 
 
 def _load_prefixes(eng, n_layers, batch, gen):
-    """N(0, 1) keys and values behind every request: one block per layer, read by each request from a row of its own."""
-    m = eng.model
-    rows = max(s.prefix for s in batch) + 16 * len(batch)
-    k = torch.empty((rows, m["n_kv"], m["head_dim"]), dtype=torch.bfloat16, device=eng.device)
-    v = torch.empty_like(k)
-    step = k[0].numel() * k.element_size()
-    for layer in range(n_layers):
-        k.normal_(generator=gen)
-        v.normal_(generator=gen)
+    for layer, (k, v) in enumerate(_layer_prefixes(eng.model, n_layers, [s.prefix for s in batch], gen, eng.device)):
+        step = k[0].numel() * k.element_size()
         for i, s in enumerate(batch):
             if s.prefix > 0:
                 eng.ctx.kv_write(layer, s.pages, 0, s.prefix, k.data_ptr() + 16 * i * step, v.data_ptr() + 16 * i * step)
@@ -154,8 +175,7 @@ def _load_prefixes(eng, n_layers, batch, gen):
 
 def prepare(case, seed):
     spec = _spec(case)
-    gen = torch.Generator(device="cuda:0")
-    gen.manual_seed(int(seed) * 1000003 + 17)
+    gen = _generator(seed)
     layers, n_pages = case["layers"], [(kv + W.PAGE - 1) // W.PAGE for _, kv in spec]
     n_pool = sum(n_pages) + max(3, sum(n_pages) // 8)
     longest = max(kv for _, kv in spec) + W.PAGE
@@ -170,8 +190,7 @@ def prepare(case, seed):
     st = {"kind": case["kind"], "eng": eng, "batch": batch, "layers": layers}
     H, T = eng.model["hidden"], sum(n for n, _ in spec)
     if case["kind"] == "model":
-        emb = torch.empty((VOCAB, H), dtype=torch.bfloat16, device=eng.device).normal_(generator=gen)
-        w_out = torch.empty((H, VOCAB), dtype=torch.bfloat16, device=eng.device).normal_(0.0, W.WEIGHT_STD, generator=gen)
+        emb, w_out = _head(eng.model, gen, eng.device)
         g = torch.ones(H, dtype=torch.bfloat16, device=eng.device)
         eng.ctx.init_head(emb.data_ptr(), g.data_ptr(), w_out.data_ptr(), VOCAB)
         eng.ctx.sync()
@@ -181,7 +200,7 @@ def prepare(case, seed):
         st["x"] = torch.empty((T, H), dtype=torch.bfloat16, device=eng.device).normal_(generator=gen).view(torch.int16)
     if case["kind"] == "handoff":
         # the second instance: the same weights, an empty pool with pages of its own
-        gen.manual_seed(int(seed) * 1000003 + 17)
+        gen = _generator(seed)
         other = Engine(case["model"], n_pool, layers, layers, max_position=longest)
         _load_layers(other, layers, gen)
         st["other"] = other
@@ -244,3 +263,59 @@ def tolerance(case):
     if case["model"] == "tiny":
         return {"rel": 0.008, "max": 0.04}
     return {"rel": 0.025, "max": 0.15}
+
+
+def _exact_layer(m, spec, w, k_pre, v_pre, x):
+    """One layer of plain torch in 64 bits: pre-norm attention over each request's own prefix, SwiGLU; x is [T][hidden]."""
+    d, nq, nkv = m["head_dim"], m["n_q"], m["n_kv"]
+    half, dev = d // 2, x.device
+    norm = lambda t: t * torch.rsqrt(t.square().mean(-1, keepdim=True) + W.RMS_EPS)
+    pos = torch.cat([torch.arange(kv - n, kv, device=dev) for n, kv in spec]).double()
+    theta = float(m["rope_base"]) ** (-2.0 * torch.arange(half, device=dev).double() / d)
+    cos, sin = (pos[:, None] * theta).cos()[:, None], (pos[:, None] * theta).sin()[:, None]
+
+    def rotate(t):
+        lo, hi = t[..., :half], t[..., half:]
+        return torch.cat([lo * cos - hi * sin, hi * cos + lo * sin], -1)
+
+    q, k, v = (norm(x) @ w["w_qkv"].double()).view(len(x), -1, d).split([nq, nkv, nkv], 1)
+    q, k, out, at = rotate(q), rotate(k), torch.empty_like(q), 0
+    for i, (n, kv) in enumerate(spec):
+        pre = kv - n
+        keys = torch.cat([k_pre[16 * i:16 * i + pre].double(), k[at:at + n]])
+        values = torch.cat([v_pre[16 * i:16 * i + pre].double(), v[at:at + n]])
+        allowed = torch.arange(kv, device=dev)[None] <= torch.arange(pre, kv, device=dev)[:, None]
+        for h in range(nq):
+            g = h // (nq // nkv)
+            s = (q[at:at + n, h] @ keys[:, g].T / d ** 0.5).masked_fill_(~allowed, -float("inf"))
+            out[at:at + n, h] = torch.softmax(s, -1) @ values[:, g]
+        at += n
+    x = x + out.reshape(len(x), nq * d) @ w["w_o"].double()
+    y = norm(x)
+    return x + (torch.nn.functional.silu(y @ w["w_gate"].double()) * (y @ w["w_up"].double())) @ w["w_down"].double()
+
+
+def exact(case, seed):
+    """The same inputs through plain torch in 64 bits, nothing rounded on the way.  The value of `picked` is left out: which
+    of two logits that lie within rounding of each other it is taken at has no one answer."""
+    m, spec, layers, dev = W.MODELS[case["model"]], _spec(case), case["layers"], torch.device("cuda:0")
+    T = sum(n for n, _ in spec)
+    gen = _generator(seed)
+    for _ in _layer_weights(m, layers, gen, dev):   # only for the draws: the weights come again below
+        pass
+    cached = [(k.clone(), v.clone()) for k, v in _layer_prefixes(m, layers, [kv - n for n, kv in spec], gen, dev)]
+    if case["kind"] == "model":
+        emb, w_out = _head(m, gen, dev)
+        x = emb[torch.from_numpy(np.asarray(W.token_ids(VOCAB, T, seed))).long().to(dev)].double()
+    else:
+        x = torch.empty((T, m["hidden"]), dtype=torch.bfloat16, device=dev).normal_(generator=gen).double()
+    for w, (k, v) in zip(_layer_weights(m, layers, _generator(seed), dev), cached):
+        x = _exact_layer(m, spec, w, k, v, x)
+    if case["kind"] == "model":
+        last = x[np.cumsum([n for n, _ in spec]) - 1]
+        logits = (last * torch.rsqrt(last.square().mean(-1, keepdim=True) + W.RMS_EPS)) @ w_out.double()
+        return {"logits": logits, "hidden": x, "picked": None}
+    if case["kind"] == "handoff":
+        n = spec[0][1] - spec[0][0]
+        return {"k": torch.stack([k[:n] for k, _ in cached]).double(), "v": torch.stack([v[:n] for _, v in cached]).double(), "x": x}
+    return x
