@@ -678,7 +678,7 @@ extern "C" ps_status ps_set_taps(ps_ctx* c, int32_t layer, const ps_taps* taps) 
 static size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 
 // What the tiled GEMM needs beside its output for a step of T tokens: the largest over the layer's four projections.
-static void sk_need(const ps_ctx* c, int T, int head_rows, size_t* frag_bytes, int* n_counters) {
+static void sk_need(const ps_ctx* c, int T, int head_rows, size_t* frag_bytes, int* n_counters, bool no_wreg = false) {
     const ps_model_desc& d = c->desc;
     const int H = d.hidden, F = d.ffn, NQ = d.n_q_heads * d.head_dim, NQKV = qkv_cols(d);
     const int shapes[4][3] = {{NQKV, H, GemmOut::PARTIAL_F32}, {H, NQ, GemmOut::PARTIAL_F32}, {2 * F, H, GemmOut::SWIGLU_BF16}, {H, F, GemmOut::PARTIAL_F32}};
@@ -687,7 +687,7 @@ static void sk_need(const ps_ctx* c, int T, int head_rows, size_t* frag_bytes, i
     for (const auto& sh : shapes) {
         size_t fb = 0;
         int nc = 0;
-        gemm_workspace(T, sh[0], sh[1], sh[2], c->opt_gemm_split_k, c->opt_gemm_tile, c->opt_gemm_whole_tiles, &fb, &nc);
+        gemm_workspace(T, sh[0], sh[1], sh[2], c->opt_gemm_split_k, c->opt_gemm_tile, c->opt_gemm_whole_tiles, &fb, &nc, no_wreg);
         *frag_bytes = std::max(*frag_bytes, fb);
         *n_counters = std::max(*n_counters, nc);
     }
@@ -813,12 +813,14 @@ struct StepBufs {
     size_t skfrag_bytes = 0;
     int* skcnt = nullptr;
     int skcnt_n = 0;
+    bool no_wreg = false;  // static steps only: leave the weights-in-registers GEMM out (see carve_static)
     char* meta = nullptr;  // static steps only: device copy of the metadata
 };
 
 // Lay the buffers of a step of T tokens out in the static scratch array.  Nothing is allocated: a step whose buffers
-// do not fit PS_STATIC_SCRATCH_BYTES is refused.
-static ps_status carve_static(ps_ctx* c, int T, int n_part_slots, size_t meta_bytes, StepBufs* w) {
+// do not fit PS_STATIC_SCRATCH_BYTES is refused.  The weights-in-registers GEMM may want more K splits, i.e. more partial
+// sums, than the other kernels: it is left out where only that makes the step too large.
+static ps_status carve_static(ps_ctx* c, int T, int n_part_slots, size_t meta_bytes, StepBufs* w, bool no_wreg = false) {
     const ps_model_desc& d = c->desc;
     const int H = d.hidden, F = d.ffn, NQ = d.n_q_heads * d.head_dim, NQKV = qkv_cols(d);
     const size_t T16 = (size_t)((T + 15) & ~15);
@@ -827,19 +829,21 @@ static ps_status carve_static(ps_ctx* c, int T, int n_part_slots, size_t meta_by
     const size_t o_xn = take(T16 * H * 2), o_q = take((size_t)T * NQ * 2), o_attn = take(T16 * NQ * 2);
     w->act_bytes = gemm_out_bytes(T, 2 * F, H, GemmOut::SWIGLU_BF16, 0, 0);
     const size_t o_act = take(w->act_bytes), o_x1 = take((size_t)T * H * 4), o_xmid = take(d.n_layers > 1 ? (size_t)T * H * 4 : 0);
-    w->part_bytes = gemm_out_bytes(T, NQKV, H, GemmOut::PARTIAL_F32, c->opt_gemm_split_k, c->opt_gemm_tile);
-    w->part_bytes = std::max(w->part_bytes, gemm_out_bytes(T, H, NQ, GemmOut::PARTIAL_F32, c->opt_gemm_split_k, c->opt_gemm_tile));
-    w->part_bytes = std::max(w->part_bytes, gemm_out_bytes(T, H, F, GemmOut::PARTIAL_F32, c->opt_gemm_split_k, c->opt_gemm_tile));
+    w->part_bytes = gemm_out_bytes(T, NQKV, H, GemmOut::PARTIAL_F32, c->opt_gemm_split_k, c->opt_gemm_tile, no_wreg);
+    w->part_bytes = std::max(w->part_bytes, gemm_out_bytes(T, H, NQ, GemmOut::PARTIAL_F32, c->opt_gemm_split_k, c->opt_gemm_tile, no_wreg));
+    w->part_bytes = std::max(w->part_bytes, gemm_out_bytes(T, H, F, GemmOut::PARTIAL_F32, c->opt_gemm_split_k, c->opt_gemm_tile, no_wreg));
     const size_t o_part = take(w->part_bytes);
     const size_t o_po = take((size_t)n_part_slots * 16 * d.head_dim * 4), o_pml = take((size_t)n_part_slots * 16 * 2 * 4);
     const size_t o_meta = take(meta_bytes);
     int n_cnt = 0;
-    sk_need(c, T, 0, &w->skfrag_bytes, &n_cnt);
+    sk_need(c, T, 0, &w->skfrag_bytes, &n_cnt, no_wreg);
+    w->no_wreg = no_wreg;
     w->skcnt_n = (n_cnt + 3) & ~3;
     const size_t o_skfrag = take(w->skfrag_bytes), o_skcnt = take((size_t)w->skcnt_n * sizeof(int));
     if (meta_bytes > STATIC_META_SLOT)
         return fail(c, PS_ERANGE, "ps_step_static: the step's metadata (" + std::to_string(meta_bytes) + " bytes: positions, page lists, attention work list) exceeds " +
                                       std::to_string(STATIC_META_SLOT) + " bytes; use ps_step for batches of this size");
+    if (at > (size_t)PS_STATIC_SCRATCH_BYTES && !no_wreg) return carve_static(c, T, n_part_slots, meta_bytes, w, true);
     if (at > (size_t)PS_STATIC_SCRATCH_BYTES)
         return fail(c, PS_ERANGE, "ps_step_static: the step needs " + std::to_string(at) + " bytes of scratch, the static array holds " +
                                       std::to_string((size_t)PS_STATIC_SCRATCH_BYTES) + "; use ps_step for batches of this size");
@@ -1020,7 +1024,7 @@ static ps_status step_impl(ps_ctx* c, const ps_seq* seqs, int32_t n_seqs, const 
         g.A = W.xn; g.Wp = L.wqkv_t; g.M = T; g.N = NQKV; g.K = H; g.kind = GemmOut::PARTIAL_F32;
         g.out = W.part; g.out_bytes = W.part_bytes; g.split_k = c->opt_gemm_split_k; g.tile = c->opt_gemm_tile;
         g.sk_frag = W.skfrag; g.sk_frag_bytes = W.skfrag_bytes; g.sk_counters = W.skcnt; g.sk_n_counters = W.skcnt_n;
-        g.sk_mode = c->opt_gemm_whole_tiles;
+        g.sk_mode = c->opt_gemm_whole_tiles; g.no_wreg = W.no_wreg;
         HIP_TRY(c, run_gemm(g, &n_splits, 0));
         if (stats) HIP_TRY(c, hipEventRecord(c->ev[++e], s));
         // 2: sum the partials, rotate, round once to bf16, append k/v to the pages

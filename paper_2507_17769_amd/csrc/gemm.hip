@@ -12,12 +12,13 @@
 // of 4 KiB per k-block between them instead of four separate streams of 1 KiB, which is what keeps
 // DRAM rows open when two thousand wavefronts stream at once.
 //
-// Two kernels:
+// Three kernels (plan_gemm chooses):
+//  * gemm_wreg_kernel (gemm_wreg.hip; from 65 tokens on, most shapes up to some 1000 tokens): weights in registers.
 //  * gemm_wstream_kernel (M <= 96, and up to 160 for all but the QKV-shaped projection): weight streaming.  The four computing wavefronts of a block own 16 of
 //    its 64 output columns each and load their weight operands straight from HBM into registers
 //    (no LDS hop), four stages of two k-blocks ahead; a fifth wavefront copies the activation k-blocks
 //    that all four need into an LDS ring.
-//  * gemm_sk_kernel (above that, or forced by the tile option above 64): 256x256 or 128x128 block tile, bf16 MFMA 16x16x32.  Activations and
+//  * gemm_sk_kernel (where its tiles fill the chip, or forced by the tile option above 64): 256x256 or 128x128 block tile, bf16 MFMA 16x16x32.  Activations and
 //    weights are both stored as KiB blocks that already are MFMA operands, so a k-slice of the
 //    tile is copied HBM/L2 -> LDS verbatim by global_load_lds (no register hop, no transform) into
 //    a ring of four stages, three in flight; the wavefronts read operands back with one
@@ -27,9 +28,12 @@
 // Output is either fp32 partials [split][M][N] (one per K split of the streaming kernel; the consumer kernel sums the splits, adds the
 // residual, normalises, rotates ...) or, for the fused gate/up matrix, silu(gate) * up in bf16.
 #include "ps_device.h"
+#include "gemm_wreg.h"
 #include "sk_decomp.h"
 
 #include <algorithm>
+#include <cmath>
+#include <limits>
 #include <mutex>
 
 namespace ps {
@@ -42,8 +46,6 @@ struct GemmParams {
     void* out;         // fp32 [split][M][N] row-major, or bf16 [M][N/2] in operand order
     int kb_per_split;  // 32-wide k-blocks per block
 };
-
-__device__ __forceinline__ float silu_f(float z) { return z / (1.0f + __expf(-z)); }
 
 // ------------------------------------------------------------------------------------------
 // Weight streaming kernel (M <= 160: up to ten row tiles of 16).  grid (N/64/NG, splits), 64 (4 NG + 1) threads, NG = 1 or 2 column groups per block.
@@ -585,6 +587,8 @@ __global__ __launch_bounds__(256) void gemm_sk_kernel(SkParams sp) {
 // ------------------------------------------------------------------------------------------
 struct GemmPlan {
     bool wstream;
+    bool wreg;          // weights in registers (gemm_wreg.hip), with the plan below
+    WregPlan wreg_plan;
     bool big_tile;      // tiled: 256x256 blocks (else 128x128)
     int splits;         // partial buffers written
     int kb_per_split;   // 32-wide k-blocks per split
@@ -645,8 +649,46 @@ static double tiled_estimate(int M, int N, int K, int edge, int splits, bool cut
     return us;
 }
 
-static GemmPlan plan_gemm(int M, int N, int K, int kind, int split_opt, int tile_opt, int sk_mode = 0) {
+// Estimated time (us) of the weights-in-registers kernel for one plan: blocks run one per compute unit in waves, a stage
+// costs 0.34 + 0.07 per row tile with four column groups (0.22 + 0.096 with two, whose K shares copy twice the activations),
+// a block 8 more for its first loads and its epilogue, a wave that is not full three quarters of its time plus a quarter of
+// its fill (the blocks that do run have the memory to themselves); the weights stream at 6.2 TB/s, and the shorter of the
+// two times hides all but 15 % of itself.  Fitted to 190 runs of the 8B shapes at 80 to 1024 tokens; the plan it picks is within
+// 8 % of the best one measured at every one of them.  Partial sums are read back by the consumer.
+static double wreg_estimate(const WregPlan& g, int M, int N, int K) {
+    const int cus = device_cus(), shares = 8 / g.nc, n = K / 32 / (g.splits * shares);
+    const int blocks = g.row_tiles * g.splits * ((N / 64 + g.nc - 1) / g.nc);
+    const int full = blocks / cus, rem = blocks % cus;
+    const double waves = full + (rem ? 0.77 + 0.23 * rem / cus : 0.0);
+    const double core = 2.0 + waves * (8.0 + n * (g.nc == 4 ? 0.34 + 0.07 * g.tm : 0.22 + 0.096 * g.tm));
+    const double hbm = 2.0 * N * K / 6.2e6;
+    return std::max(core, hbm) + 0.15 * std::min(core, hbm) + (g.splits - 1) * (double)M * N * 4 / 5e6;
+}
+
+// The best plan of the weights-in-registers kernel, or an estimate of infinity where it does not serve the shape.
+static double wreg_best(int M, int N, int K, int kind, int split_opt, WregPlan* best) {
+    double best_us = std::numeric_limits<double>::infinity();
+    const int tiles = (M + 15) / 16;
+    const int s_lo = kind == GemmOut::SWIGLU_BF16 ? 1 : (split_opt > 0 ? std::min(split_opt, 8) : 1);
+    const int s_hi = kind == GemmOut::SWIGLU_BF16 ? 1 : (split_opt > 0 ? s_lo : 8);
+    for (int rt = (tiles + WREG_MAX_TM - 1) / WREG_MAX_TM; rt <= (tiles + WREG_MIN_TM - 1) / WREG_MIN_TM; rt++) {
+        const int tm = std::max(WREG_MIN_TM, (tiles + rt - 1) / rt);
+        if (rt > 1 && tm * (rt - 1) >= tiles) continue;   // the last row block would be empty
+        for (int nc : {4, 2})
+            for (int sp = s_lo; sp <= s_hi; sp++) {
+                const WregPlan g{tm, nc, sp, rt};
+                if (!wreg_valid(g, M, N, K, kind)) continue;
+                const double us = wreg_estimate(g, M, N, K);
+                if (us < best_us) { best_us = us; *best = g; }
+            }
+    }
+    return best_us;
+}
+
+static GemmPlan plan_gemm(int M, int N, int K, int kind, int split_opt, int tile_opt, int sk_mode = 0, bool allow_wreg = true) {
     GemmPlan g;
+    g.wreg = false;
+    allow_wreg = allow_wreg && M > 64 && tile_opt == 0 && sk_mode == 0;   // the options that name the tiled kernel get it
     // measured: streaming wins up to 96 tokens for every projection, and up to 160 (ten row tiles) for all but the QKV-shaped
     // one (more columns than rows of weights: 48 blocks per split and six splits of partial sums; 129 tokens: 29 vs 24 us),
     // above all for the gate/up matrix (129 tokens: 61 vs 75 us) and the down projection (42 vs 46)
@@ -657,6 +699,20 @@ static GemmPlan plan_gemm(int M, int N, int K, int kind, int split_opt, int tile
     g.cut_tail = false;
     g.slots_per_xcd = 0;
     if (g.wstream) {
+        // Measured against streaming up to 160 tokens (us, streaming / weights in registers): gate/up of the 8B shape 41.9 /
+        // 42.6 at 80 tokens, 46.9 / 45.9 at 97, 53.4 / 49.1 at 144, 58.9 / 49.8 at 160; of the 70B shape, where streaming
+        // puts two blocks on a compute unit, 157 / 136 at 80 and 217 / 155 at 128; QKV 17.7 / 15.0 at 80; the O and down
+        // projections are no faster (11.5 / 12.4, 24.4 / 25.2 at 80, 14.4 / 14.4, 29.6 / 30.9 at 144).
+        const bool gate_up = kind == GemmOut::SWIGLU_BF16;
+        if (allow_wreg && ((gate_up && (M > 96 || N / 128 > device_cus())) || (!gate_up && N > K))) {
+            const double us = wreg_best(M, N, K, kind, split_opt, &g.wreg_plan);
+            g.wreg = std::isfinite(us) && g.wreg_plan.row_tiles * g.wreg_plan.splits * (N / 64 / g.wreg_plan.nc) >= device_cus() / 2;
+        }
+        if (g.wreg) {
+            g.wstream = false;
+            g.splits = g.wreg_plan.splits;
+            return g;
+        }
         const int groups = N / 64, KB = K / 32;
         int s = 1;
         if (kind != GemmOut::SWIGLU_BF16) {
@@ -690,26 +746,42 @@ static GemmPlan plan_gemm(int M, int N, int K, int kind, int split_opt, int tile
                     }
                 }
         }
+        // The tiled estimate runs below what is measured: by a sixth with 128x128 tiles (5 to 30 % over 40 shapes), by an eighth
+        // with 256x256 ones.  Where the weights-in-registers kernel wins
+        // (8B shape, us, tiled / it): gate/up 80.2 / 67.0 at 256 tokens, 115 / 69.2 at 271, 187 / 158 at 640, 434 / 379 at
+        // 1600; down 45.3 / 38.1, 52.3 / 39.3, 94.1 / 66.4; 70B shape at 264 tokens: gate/up 443 / 307, down 212 / 146.
+        // The tiled kernel keeps what fills its 256x256 tiles: gate/up at 512 tokens 112 / 121, at 2048 444 / 460.
+        WregPlan w;
+        if (allow_wreg && wreg_best(M, N, K, kind, split_opt, &w) < (g.big_tile ? 1.12 : 1.17) * best) {
+            g.wreg = true;
+            g.wreg_plan = w;
+            g.splits = w.splits;
+            g.cut_tail = false;
+            g.slots_per_xcd = 0;
+        }
     }
     return g;
 }
 
-size_t gemm_out_bytes(int M, int N, int K, int kind, int split_opt, int tile_opt) {
+size_t gemm_out_bytes(int M, int N, int K, int kind, int split_opt, int tile_opt, bool no_wreg) {
     if (kind == GemmOut::SWIGLU_BF16) {
         // dense [rows][N/2] in operand order.  The tiled kernel stores whole row tiles without a row check
         // (rows past M are never read back), so the buffer holds M rounded up to its largest tile.
         const size_t rows = M <= 64 ? (size_t)((M + 15) / 16 * 16) : (size_t)((M + 255) / 256 * 256);
         return rows * (N / 2) * sizeof(bf16_t);
     }
-    return (size_t)plan_gemm(M, N, K, kind, split_opt, tile_opt).splits * M * N * sizeof(float);
+    // room for whichever kernel the options of a later call pick
+    int splits = plan_gemm(M, N, K, kind, split_opt, tile_opt, 0, false).splits;
+    if (!no_wreg) splits = std::max(splits, plan_gemm(M, N, K, kind, split_opt, tile_opt).splits);
+    return (size_t)splits * M * N * sizeof(float);
 }
 
-void gemm_workspace(int M, int N, int K, int kind, int split_opt, int tile_opt, int sk_mode, size_t* frag_bytes, int* n_counters) {
+void gemm_workspace(int M, int N, int K, int kind, int split_opt, int tile_opt, int sk_mode, size_t* frag_bytes, int* n_counters, bool no_wreg) {
     *frag_bytes = 0;
     *n_counters = 0;
     if (M <= 0) return;
-    const GemmPlan g = plan_gemm(M, N, K, kind, split_opt, tile_opt, sk_mode);
-    if (g.wstream) return;
+    const GemmPlan g = plan_gemm(M, N, K, kind, split_opt, tile_opt, sk_mode, !no_wreg);
+    if (g.wstream || g.wreg) return;
     const int b = g.big_tile ? 256 : 128;
     *frag_bytes = (size_t)8 * g.slots_per_xcd * b * b * sizeof(float);
     *n_counters = ((M + b - 1) / b) * ((N + b - 1) / b);
@@ -752,14 +824,15 @@ hipError_t launch_gemm(const GemmArgs& a, int* n_splits, hipStream_t st) {
     // the tiled kernel addresses A and Wp with 32-bit byte offsets
     if (a.M > 64 && ((size_t)a.N * a.K * 2 >= (1ull << 32) || (size_t)((a.M + 15) / 16 * 16) * a.K * 2 >= (1ull << 32)))
         return hipErrorInvalidValue;
-    const GemmPlan g = plan_gemm(a.M, a.N, a.K, a.kind, a.split_k, a.tile, a.sk_mode);
+    const GemmPlan g = plan_gemm(a.M, a.N, a.K, a.kind, a.split_k, a.tile, a.sk_mode, !a.no_wreg);
     if ((size_t)g.splits * (a.kind == GemmOut::SWIGLU_BF16 ? 0 : (size_t)a.M * a.N * sizeof(float)) > a.out_bytes ||
-        gemm_out_bytes(a.M, a.N, a.K, a.kind, a.split_k, a.tile) > a.out_bytes)
+        (a.kind == GemmOut::SWIGLU_BF16 && gemm_out_bytes(a.M, a.N, a.K, a.kind, a.split_k, a.tile) > a.out_bytes))
         return hipErrorInvalidValue;
     GemmParams p;
     p.A = a.A; p.Wp = a.Wp; p.M = a.M; p.N = a.N; p.K = a.K; p.kind = a.kind; p.out = a.out;
     p.kb_per_split = g.kb_per_split;
     if (n_splits) *n_splits = g.splits;
+    if (g.wreg) return launch_gemm_wreg(a, g.wreg_plan, st);
     if (g.wstream) {
         const int mt = (a.M + 15) / 16;
         // Two column groups per block halve the activation copies (as many bytes as the weights at 64 tokens) at the

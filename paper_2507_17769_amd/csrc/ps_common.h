@@ -137,12 +137,13 @@ struct GemmArgs {
     size_t sk_frag_bytes;
     int* sk_counters;
     int sk_n_counters;
+    bool no_wreg;      // leave the weights-in-registers kernel out (a static step whose scratch its K splits would overflow)
 };
 // *n_splits receives the number of partial buffers written (1 for SWIGLU_BF16)
 hipError_t launch_gemm(const GemmArgs& a, int* n_splits, hipStream_t st);
-size_t gemm_out_bytes(int M, int N, int K, int kind, int split_k_opt, int tile_opt);
-// what launch_gemm needs in sk_frag / sk_counters for this shape (both 0 where the streaming kernel serves it)
-void gemm_workspace(int M, int N, int K, int kind, int split_k_opt, int tile_opt, int sk_mode, size_t* frag_bytes, int* n_counters);
+size_t gemm_out_bytes(int M, int N, int K, int kind, int split_k_opt, int tile_opt, bool no_wreg = false);
+// what launch_gemm needs in sk_frag / sk_counters for this shape (both 0 unless the tiled kernel serves it)
+void gemm_workspace(int M, int N, int K, int kind, int split_k_opt, int tile_opt, int sk_mode, size_t* frag_bytes, int* n_counters, bool no_wreg = false);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st);   // bytes: rounded down to a multiple of 16
 hipError_t launch_fill_words(void* p, size_t bytes, uint32_t word, hipStream_t st);
 

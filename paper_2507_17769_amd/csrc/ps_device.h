@@ -32,6 +32,8 @@ __device__ __forceinline__ uint4 ldg16_stream(const void* p) {
     return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4_nt_t*>(p)));
 }
 
+__device__ __forceinline__ float silu_f(float z) { return z / (1.0f + __expf(-z)); }
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -68,6 +70,18 @@ __device__ __forceinline__ void lgkm_tie(u32x4_t& a, u32x4_t& b, u32x4_t& c) {
 template <int CNT>
 __device__ __forceinline__ void lgkm_tie(u32x4_t& a, u32x4_t& b, u32x4_t& c, u32x4_t& d, u32x4_t& e) {
     asm volatile("s_waitcnt lgkmcnt(%5)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d), "+v"(e) : "n"(CNT));
+}
+// the same with a count that is a constant once the caller's loop is unrolled
+__device__ __forceinline__ void lgkm_tie_dyn(u32x4_t& a, int cnt) {
+    switch (cnt) {
+        case 0: lgkm_tie<0>(a); break;
+        case 1: lgkm_tie<1>(a); break;
+        case 2: lgkm_tie<2>(a); break;
+        case 3: lgkm_tie<3>(a); break;
+        case 4: lgkm_tie<4>(a); break;
+        case 5: lgkm_tie<5>(a); break;
+        default: lgkm_tie<6>(a); break;
+    }
 }
 template <int CNT>
 __device__ __forceinline__ void vm_wait() {

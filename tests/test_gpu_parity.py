@@ -324,6 +324,22 @@ def test_tiled_gemm_tile_sizes_and_k_splits(tile, split, tails):
         c.close()
 
 
+@pytest.mark.parametrize("tokens", [65, 97, 113, 129, 161, 209, 257, 289, 321])
+def test_weights_in_registers_gemm_row_blocks(tokens):
+    # a shape whose projections reach the weights-in-registers GEMM from 65 tokens on; the token counts leave one row in the
+    # last 16-row tile (or end in a row block's last tile) for every number of row tiles per block from five to ten, with one, two
+    # and more row blocks, two and four column groups
+    W.MODELS["_r"] = dict(hidden=2048, n_q=16, n_kv=8, head_dim=128, ffn=12288, rope_base=500000.0, n_layers=1)
+    try:
+        c = Case(W.custom_batch("_r", 29, tokens - 5, 40, [1, 16, 17, 90, 200], name="row blocks"))
+        errs = c.run()
+        _assert_errs(errs, f"row blocks T={tokens}")
+        c.check_pool()
+        c.close()
+    finally:
+        del W.MODELS["_r"]
+
+
 def test_only_layer_runs_that_layer_as_the_whole_model():
     # a 3-layer context restricted to layer 1 gives bit for bit what a 1-layer context with layer 1's weights gives
     b = W.custom_batch("tiny", 23, 40, 20, [3, 60, 129], name="only")

@@ -99,6 +99,49 @@ def test_accumulators_are_not_read_right_behind_the_last_matrix_instruction(gemm
 
 
 @pytest.fixture(scope="module")
+def wreg_asm():
+    with tempfile.TemporaryDirectory() as tmp:
+        out = os.path.join(tmp, "gemm_wreg.s")
+        flags = [f for f in B.FLAGS if f != "-fPIC"]
+        cmd = [B.HIPCC] + flags + ["--cuda-device-only", "-S", os.path.join(B.CSRC, "gemm_wreg.hip"), "-o", out]
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr
+        return open(out).read()
+
+
+def test_weights_in_registers_gemm_main_loop_is_clean(wreg_asm):
+    """The kernel counts its outstanding loads itself: every stage must issue exactly the loads its wait counts assume (a load
+    the compiler dropped or moved would let a stage read activations that have not landed), and nothing may be spilled or
+    moved between registers while reads are in flight."""
+    n = 0
+    for m in re.finditer(r"^(_ZN2ps16gemm_wreg_kernelILi(\d+)ELi(\d)E\w+):\s*;.*?\n(.*?)s_endpgm", wreg_asm, re.S | re.M):
+        name, tm, nc = m.group(1), int(m.group(2)), int(m.group(3))
+        lines = [l.strip() for l in m.group(4).splitlines()]
+        loop = _main_loop(lines)
+        assert loop, name
+        ops = [l.split()[0] for l in loop]
+        copies = -(-tm // nc)
+        ring = 5 if 8 // nc * tm * 5 <= 160 else 4
+        assert sum(o == "v_mfma_f32_16x16x32_bf16" for o in ops) == 4 * 4 * tm, name
+        assert sum(o == "ds_read_b128" for o in ops) == 4 * tm, name
+        assert sum(o == "buffer_load_dwordx4" for o in ops) == 4 * (4 + copies), name
+        assert sum(l.endswith("offen lds") for l in loop) == 4 * copies, name
+        assert ops.count("s_barrier") == 4, name
+        # the wait ahead of each barrier covers the copies of the next stage and nothing younger than this stage's weights
+        before = [loop[max(j for j in range(i) if "vmcnt" in loop[j])] for i, o in enumerate(ops) if o == "s_barrier"]
+        assert all(f"vmcnt({(ring - 3) * (4 + copies) + 4})" in l for l in before), (name, before)
+        assert not [l for l in loop if re.match(r"(v_mov|v_accvgpr|scratch_|v_swap)", l) or "vmcnt(0)" in l], name
+        before_loop = lines[:max(i for i, l in enumerate(lines) if l == loop[0])]
+        assert sum(l.startswith("buffer_load") for l in before_loop) == (ring - 1) * copies + 12, name
+        assert not any(l.startswith("scratch_") for l in lines), name
+        last = max(i for i, l in enumerate(lines) if l.startswith("v_mfma"))
+        nops = [i for i, l in enumerate(lines) if l == "s_nop 15"]
+        assert len(nops) == 2 and nops[1] == nops[0] + 1 and nops[0] > last, (name, nops, last)
+        n += 1
+    assert n == 6 * 2 * 2 * 2      # row tiles x column groups x epilogues x streamed or shared weights
+
+
+@pytest.fixture(scope="module")
 def attn_asm():
     with tempfile.TemporaryDirectory() as tmp:
         out = os.path.join(tmp, "attention.s")
@@ -194,15 +237,15 @@ def test_the_scan_for_early_uses_finds_a_planted_one():
     assert _touched_before_their_wait(partial) == [(4, partial[4])]
 
 
-def test_no_register_is_used_while_an_lds_read_is_still_writing_it(gemm_asm, attn_asm):
+def test_no_register_is_used_while_an_lds_read_is_still_writing_it(gemm_asm, wreg_asm, attn_asm):
     """The tiled GEMM and the attention teams read LDS through assembly whose results the compiler believes valid at
     once; the kernels wait for them with statements that name the registers.  Anywhere in these kernels, loop or not, a
     register copy or an operand use that the compiler slipped in between a read and its wait would read stale data."""
     n = 0
-    for asm, pat in ((gemm_asm, "gemm_sk_kernel"), (gemm_asm, "gemm_wstream_kernel"), (attn_asm, "attn_kernel")):
+    for asm, pat in ((gemm_asm, "gemm_sk_kernel"), (gemm_asm, "gemm_wstream_kernel"), (wreg_asm, "gemm_wreg_kernel"), (attn_asm, "attn_kernel")):
         for m in re.finditer(r"^(\S*" + pat + r"\S*):\s*;.*?\n(.*?)s_endpgm", asm, re.S | re.M):
             lines = [x.strip() for x in m.group(2).splitlines()]
             bad = _touched_before_their_wait(lines)
             assert not bad, (m.group(1), bad[:3])
             n += 1
-    assert n >= 4 + 10
+    assert n >= 4 + 48 + 10
