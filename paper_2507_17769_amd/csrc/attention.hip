@@ -540,51 +540,60 @@ __global__ __launch_bounds__(64 * TEAM_WAVES) __attribute__((amdgpu_waves_per_eu
 // Combine split partials of one query tile: out = sum_j 2^(m_j - M) O_j / sum_j 2^(m_j - M) l_j.
 // One block per merge group.  A tile is n_rows x D/4 float4 pieces, 64 pieces per pass and wavefront.  The block's
 // wavefronts form a (pass, split) grid: wavefront (wp, ws) takes the passes wp, wp + NWP, ... and of each the splits
-// ws, ws + NWS, ...  Passes are independent, so a 16-row prefill tile (eight passes) costs the latency of one;
-// the NWS wavefronts of a pass (a sequence cut over hundreds of workers would otherwise be merged split after split)
-// each reduce their share to (max, sum, O) against their own maximum, and the first of them combines the NWS results
-// through LDS in a fixed order.
+// ws, ws + NWS, ...  What bounds the kernel is the latency of its loads, one trip after another, so every group gets the
+// NWS that lets a wavefront load its splits in one batch of eight and leaves the other wavefronts to the passes: a
+// 16-row prefill tile (eight passes) in few splits takes one trip also where a decode of the same step, cut over
+// hundreds of workers, needs all the wavefronts for its splits.  The NWS wavefronts of a pass each reduce their share to
+// (max, sum, O) against their own maximum, and the first of them combines the NWS results through LDS in a fixed order.
+// (8B shape, four layers, whole step, us, one NWS for the launch and two trips over the maxima and the rows / now: 128 tokens
+// behind 1500 next to 16 decodes 743 / 726; 250 in three requests next to 21 decodes 976 / 958; decodes alone 834 / 834.)
 constexpr int MERGE_MAX_WAVES = 16;
+constexpr int MERGE_BATCH = 8;   // splits whose loads a wavefront has in flight
+
+// Wavefronts that share a pass's splits: a batch each, a power of two, as many as the block has at most.
+__host__ __device__ inline int merge_split_waves(int n_splits, int n_waves) {
+    int nws = 1;
+    while (nws < n_waves && nws * MERGE_BATCH < n_splits) nws *= 2;
+    return nws;
+}
 
 template <int D, int G>
-__global__ __launch_bounds__(64 * MERGE_MAX_WAVES) void attn_merge_kernel(AttnArgs a, int NWS) {
+__global__ __launch_bounds__(64 * MERGE_MAX_WAVES) void attn_merge_kernel(AttnArgs a) {
     __shared__ float4 s_acc[MERGE_MAX_WAVES][64];
     __shared__ float2 s_ml[MERGE_MAX_WAVES][64];
     const MergeGroup mg = a.groups[blockIdx.x];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, NW = blockDim.x >> 6;
-    const int NWP = NW / NWS, ws = wave % NWS, wp = wave / NWS;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), NW = blockDim.x >> 6;   // NW: a power of two
+    const int NWS = merge_split_waves(mg.n_splits, NW), NWP = NW / NWS, ws = wave % NWS, wp = wave / NWS;
     const int n_rows = mg.n_tok * G;  // valid rows are the first n_tok * G of the tile
     const int n_items = n_rows * (D / 4);
     for (int c0 = 0; c0 < n_items; c0 += 64 * NWP) {   // the same trip count for every wavefront: the barriers below
         const int c = c0 + wp * 64 + lane;
         const bool live = c < n_items;
         const int r = live ? c / (D / 4) : 0, col = live ? (c % (D / 4)) * 4 : 0;
-        // this wavefront's splits, eight at a time with all loads of a batch issued together
-        float M = NEG_BIG;
-        for (int j0 = ws; j0 < mg.n_splits; j0 += 8 * NWS) {
-            float mv[8];
-#pragma unroll
-            for (int j = 0; j < 8; j++)
-                if (j0 + j * NWS < mg.n_splits) mv[j] = a.part_ml[((size_t)(mg.first_slot + (j0 + j * NWS) * mg.stride) * 16 + r) * 2];
-#pragma unroll
-            for (int j = 0; j < 8; j++)
-                if (j0 + j * NWS < mg.n_splits) M = fmaxf(M, mv[j]);
-        }
+        // this wavefront's splits, a batch at a time with all its loads issued together
+        float M = NEG_BIG, L = 0.f;
         float4 acc = {0.f, 0.f, 0.f, 0.f};
-        float L = 0.f;
-        for (int j0 = ws; j0 < mg.n_splits; j0 += 8 * NWS) {
-            float2 ml[8];
-            float4 v[8];
+        const int n_splits = c0 + wp * 64 < n_items ? mg.n_splits : 0;   // a wavefront past the last pass only meets the barriers
+        for (int j0 = ws; j0 < n_splits; j0 += MERGE_BATCH * NWS) {
+            float2 ml[MERGE_BATCH];
+            float4 v[MERGE_BATCH];
 #pragma unroll
-            for (int j = 0; j < 8; j++)
-                if (j0 + j * NWS < mg.n_splits) {
+            for (int j = 0; j < MERGE_BATCH; j++)
+                if (j0 + j * NWS < n_splits) {
                     const size_t row = (size_t)(mg.first_slot + (j0 + j * NWS) * mg.stride) * 16 + r;
                     ml[j] = *reinterpret_cast<const float2*>(a.part_ml + row * 2);
                     v[j] = *reinterpret_cast<const float4*>(a.part_o + row * D + col);
                 }
+            float m_new = M;
 #pragma unroll
-            for (int j = 0; j < 8; j++)
-                if (j0 + j * NWS < mg.n_splits) {
+            for (int j = 0; j < MERGE_BATCH; j++)
+                if (j0 + j * NWS < n_splits) m_new = fmaxf(m_new, ml[j].x);
+            const float f = __builtin_amdgcn_exp2f(M - m_new);   // first batch: 0 (or 1 over masked rows only) times nothing
+            M = m_new;
+            L *= f; acc.x *= f; acc.y *= f; acc.z *= f; acc.w *= f;
+#pragma unroll
+            for (int j = 0; j < MERGE_BATCH; j++)
+                if (j0 + j * NWS < n_splits) {
                     const float w = __builtin_amdgcn_exp2f(ml[j].x - M);
                     L += w * ml[j].y;
                     acc.x += w * v[j].x; acc.y += w * v[j].y; acc.z += w * v[j].z; acc.w += w * v[j].w;
@@ -631,14 +640,11 @@ static hipError_t launch_dg(const AttnArgs& a_in, hipStream_t st) {
     hipError_t e = hipGetLastError();
     if (a.ev_end) (void)hipEventRecord(a.ev_end, st);
     if (e != hipSuccess || a.n_groups == 0) return e;
-    // wavefronts that share a pass's splits: about eight splits each (one batch of loads), a power of two up to 16;
-    // the rest of the block's 16 wavefronts take different passes, as many as the largest tile has
-    int nws = 1;
-    while (nws < MERGE_MAX_WAVES && nws * 8 < a.max_splits) nws *= 2;
+    // wavefronts of a block: for the most splits times the most passes (a power of two each) of any group
     const int passes = (std::max(1, a.max_merge_rows) * (D / 4) + 63) / 64;
-    int nwp = 1;
-    while (nwp * 2 * nws <= MERGE_MAX_WAVES && nwp < passes) nwp *= 2;
-    hipLaunchKernelGGL((attn_merge_kernel<D, G>), dim3(a.n_groups), dim3(64 * nws * nwp), 0, st, a, nws);
+    int nw = merge_split_waves(a.max_splits, MERGE_MAX_WAVES);
+    for (int p = 1; p < passes && nw < MERGE_MAX_WAVES; p *= 2) nw *= 2;
+    hipLaunchKernelGGL((attn_merge_kernel<D, G>), dim3(a.n_groups), dim3(64 * nw), 0, st, a);
     return hipGetLastError();
 }
 

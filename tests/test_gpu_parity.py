@@ -340,6 +340,18 @@ def test_weights_in_registers_gemm_row_blocks(tokens):
         del W.MODELS["_r"]
 
 
+@pytest.mark.parametrize("chunk,splits", [(0, [1, 2, 8]), (0, [9, 16, 17]), (40, [2, 64, 65]), (40, [128, 129, 257])])
+def test_merge_groups_with_different_numbers_of_splits(chunk, splits):
+    # decodes of 128 tokens per split (workers take at least four pairs of pages each) next to each other and to a chunk in few
+    # splits: a wavefront's batch of eight full and one over, one wavefront per pass to all sixteen, and more than their batches hold
+    b = W.custom_batch("tiny", 37, chunk, 300 if chunk else 0, [128 * n for n in splits], name="merge")
+    c = Case(b, options={"attn_workers": 100000})
+    errs = c.run()
+    _assert_errs(errs, f"chunk={chunk} splits={splits}")
+    c.check_pool()
+    c.close()
+
+
 def test_only_layer_runs_that_layer_as_the_whole_model():
     # a 3-layer context restricted to layer 1 gives bit for bit what a 1-layer context with layer 1's weights gives
     b = W.custom_batch("tiny", 23, 40, 20, [3, 60, 129], name="only")
