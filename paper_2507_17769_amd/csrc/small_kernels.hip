@@ -20,21 +20,23 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
     return tot;
 }
 
-// The step's first kernel also brings the step's integer metadata over: blocks past the n_rows normalising ones copy
-// it from the pinned host buffer the planner filled (mapped into the device's address space) to its device slot, 16
+// The step's first kernel also brings the step's integer metadata over: its first meta_blocks blocks (the reads cross the
+// host link and take longest) copy it from the pinned host buffer the planner filled (mapped into the device's address space) to its device slot, 16
 // bytes per thread and trip.  The kernels that read it come later in the stream; a copy engine transfer in its place
 // sat between two steps for some 16 us (it only started once the previous step's last kernel had ended).
 template <bool X_F32>
 __global__ __launch_bounds__(1024) void rmsnorm_kernel(const void* __restrict__ xin, const bf16_t* __restrict__ gain,
                                                        bf16_t* __restrict__ out, int H, float eps,
                                                        const int32_t* __restrict__ src_rows, int n_rows,
-                                                       const uint4* __restrict__ meta_src, uint4* __restrict__ meta_dst, uint32_t meta_n16) {
-    if ((int)blockIdx.x >= n_rows) {
-        const uint32_t stride = (gridDim.x - n_rows) * blockDim.x;
-        for (uint32_t i = (blockIdx.x - n_rows) * blockDim.x + threadIdx.x; i < meta_n16; i += stride) meta_dst[i] = meta_src[i];
+                                                       const uint4* __restrict__ meta_src, uint4* __restrict__ meta_dst, uint32_t meta_n16,
+                                                       int meta_blocks) {
+    if ((int)blockIdx.x < meta_blocks) {
+        const uint32_t stride = meta_blocks * blockDim.x;
+        for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < meta_n16; i += stride) meta_dst[i] = meta_src[i];
         return;
     }
-    const int orow = blockIdx.x;                            // output row
+    const int orow = row_of_block(blockIdx.x - meta_blocks, n_rows);   // output row
+    if (orow >= n_rows) return;
     const int row = src_rows ? src_rows[orow] : orow;       // input row (the head normalises selected rows only)
     const int c = threadIdx.x * 8;
     __shared__ float red[16];
@@ -79,9 +81,9 @@ hipError_t launch_rmsnorm(const void* x, bool x_is_f32, const bf16_t* gain, bf16
     const uint4* ms = static_cast<const uint4*>(meta_src);
     uint4* md = static_cast<uint4*>(meta_dst);
     if (x_is_f32)
-        hipLaunchKernelGGL(rmsnorm_kernel<true>, dim3(T + nc), dim3(nt), 0, st, x, gain, out, H, eps, src_rows, T, ms, md, n16);
+        hipLaunchKernelGGL(rmsnorm_kernel<true>, dim3(row_blocks(T) + nc), dim3(nt), 0, st, x, gain, out, H, eps, src_rows, T, ms, md, n16, nc);
     else
-        hipLaunchKernelGGL(rmsnorm_kernel<false>, dim3(T + nc), dim3(nt), 0, st, x, gain, out, H, eps, src_rows, T, ms, md, n16);
+        hipLaunchKernelGGL(rmsnorm_kernel<false>, dim3(row_blocks(T) + nc), dim3(nt), 0, st, x, gain, out, H, eps, src_rows, T, ms, md, n16, nc);
     return hipGetLastError();
 }
 
@@ -141,7 +143,7 @@ hipError_t launch_argmax_rows(const float* x, int M, int N, int32_t* out, hipStr
 }
 
 // --------------------------------------------------------------- rotary + KV append
-// grid (T, ceil((n_q + 2 n_kv) / heads per block)), 256 threads.  A head takes d/8 threads; a thread owns the four
+// grid (row_blocks(T), ceil((n_q + 2 n_kv) / heads per block)), 256 threads.  A head takes d/8 threads; a thread owns the four
 // rotation pairs (j, j + d/2), j = 4 * (its index in the head) .. + 3, and moves them as 16-byte pieces.
 // Input is the fp32 QKV projection as n_splits partial sums [n_splits][T][(n_q + 2 n_kv) d],
 // added up here; every value is rounded to bf16 exactly once, after the rotation: query heads
@@ -151,8 +153,9 @@ __global__ __launch_bounds__(256) void rope_append_kernel(const float* __restric
                                                           bf16_t* __restrict__ q_out, int n_q, int n_kv, int d,
                                                           const int32_t* __restrict__ positions,
                                                           const int32_t* __restrict__ slots,
-                                                          const float2* __restrict__ cs, bf16_t* __restrict__ pool) {
-    const int t = blockIdx.x;
+                                                          const float2* __restrict__ cs, bf16_t* __restrict__ pool, int T) {
+    const int t = row_of_block(blockIdx.x, T);
+    if (t >= T) return;
     const int tph = d >> 3;                       // threads per head
     const int hh = blockIdx.y * (256 / tph) + threadIdx.x / tph;
     if (hh >= n_q + 2 * n_kv) return;
@@ -224,9 +227,9 @@ hipError_t launch_rope_append(const float* qkv, int n_splits, bf16_t* q_out, int
     if (n_splits > 8 || d % 8 || d > 2048) return hipErrorInvalidValue;
     const size_t split_stride = (size_t)T * (n_q + 2 * n_kv) * d;
     const int heads_per_block = 256 / (d / 8);
-    hipLaunchKernelGGL(rope_append_kernel, dim3(T, (n_q + 2 * n_kv + heads_per_block - 1) / heads_per_block), dim3(256), 0, st, qkv,
+    hipLaunchKernelGGL(rope_append_kernel, dim3(row_blocks(T), (n_q + 2 * n_kv + heads_per_block - 1) / heads_per_block), dim3(256), 0, st, qkv,
                        n_splits, split_stride, q_out, n_q, n_kv, d,
-                       positions, slots, reinterpret_cast<const float2*>(rope_cs), pool_slot);
+                       positions, slots, reinterpret_cast<const float2*>(rope_cs), pool_slot, T);
     return hipGetLastError();
 }
 
@@ -319,7 +322,8 @@ hipError_t launch_kv_copy(bool to_pool, bf16_t* pool_slot, const int32_t* slots_
 // as bf16.  The row stays in registers between the two phases.
 template <bool RESID_F32>
 __global__ __launch_bounds__(1024) void reduce_add_norm_kernel(ReduceAddNormArgs a) {
-    const int row = blockIdx.x;
+    const int row = row_of_block(blockIdx.x, a.T);
+    if (row >= a.T) return;
     const int H = a.H, c = threadIdx.x * 8;
     const size_t split_stride = (size_t)a.T * H;
     __shared__ float red[16];
@@ -384,9 +388,9 @@ hipError_t launch_reduce_add_norm(const ReduceAddNormArgs& a, hipStream_t st) {
     if (a.H > 8192 || a.H % 8 || a.n_splits > 8) return hipErrorInvalidValue;
     const int nt = ((a.H / 8 + 63) / 64) * 64;
     if (a.resid_f32)
-        hipLaunchKernelGGL(reduce_add_norm_kernel<true>, dim3(a.T), dim3(nt), 0, st, a);
+        hipLaunchKernelGGL(reduce_add_norm_kernel<true>, dim3(row_blocks(a.T)), dim3(nt), 0, st, a);
     else
-        hipLaunchKernelGGL(reduce_add_norm_kernel<false>, dim3(a.T), dim3(nt), 0, st, a);
+        hipLaunchKernelGGL(reduce_add_norm_kernel<false>, dim3(row_blocks(a.T)), dim3(nt), 0, st, a);
     return hipGetLastError();
 }
 

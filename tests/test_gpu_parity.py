@@ -352,6 +352,17 @@ def test_merge_groups_with_different_numbers_of_splits(chunk, splits):
     c.close()
 
 
+@pytest.mark.parametrize("tokens", [63, 64, 65, 127, 128, 129, 200])
+def test_row_kernels_visit_every_row(tokens):
+    # from 64 rows on a block's row is a permutation of its index over whole rounds of 64; the buffers start as NaN, so a row
+    # that no block takes shows in the output
+    c = Case(W.custom_batch("tiny", 43, tokens - 3, 21, [1, 16, 50], name="rows"), options={"poison_workspaces": 1})
+    errs = c.run()
+    _assert_errs(errs, f"rows T={tokens}")
+    c.check_pool()
+    c.close()
+
+
 def test_only_layer_runs_that_layer_as_the_whole_model():
     # a 3-layer context restricted to layer 1 gives bit for bit what a 1-layer context with layer 1's weights gives
     b = W.custom_batch("tiny", 23, 40, 20, [3, 60, 129], name="only")
