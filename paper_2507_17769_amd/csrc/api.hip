@@ -605,23 +605,10 @@ static ps_status kv_copy(ps_ctx* c, bool to_pool, int32_t layer, const ps_seq* s
     for (int p = pos0 / PS_PAGE_SIZE; p <= (pos0 + n - 1) / PS_PAGE_SIZE; p++)
         if (seq->page_table[p] < 0 || seq->page_table[p] >= c->n_pool_pages)
             return fail(c, PS_ERANGE, std::string(name) + ": page id outside the pool");
-    Staging* s;
-    int s_idx = 0;
-    ps_status st = staging_acquire(c, (size_t)n * 4, &s, &s_idx);
-    if (st != PS_OK) return st;
-    StagingGuard guard(c);
-    int32_t* slots = static_cast<int32_t*>(s->host);
-    for (int i = 0; i < n; i++) {
-        const int p = pos0 + i;
-        slots[i] = seq->page_table[p / PS_PAGE_SIZE] * PS_PAGE_SIZE + p % PS_PAGE_SIZE;
-    }
-    const char* dslots = nullptr;
-    if ((st = upload_meta(c, s, s_idx, (size_t)n * 4, &dslots)) != PS_OK) return st;
     bf16_t* slot_base = c->pool + (size_t)(layer % c->n_kv_slots) * c->slot_elems;
-    HIP_TRY(c, launch_kv_copy(to_pool, slot_base, reinterpret_cast<const int32_t*>(dslots), n, pos0 & 3, c->desc.n_kv_heads,
-                              c->desc.head_dim, static_cast<bf16_t*>(k), static_cast<bf16_t*>(v), c->stream));
-    if ((st = staging_commit(c, s_idx)) == PS_OK) guard.committed = true;
-    return st;
+    HIP_TRY(c, launch_kv_copy(to_pool, slot_base, seq->page_table, pos0, n, c->desc.n_kv_heads, c->desc.head_dim, static_cast<bf16_t*>(k),
+                              static_cast<bf16_t*>(v), c->stream));
+    return PS_OK;
 }
 
 extern "C" ps_status ps_kv_write(ps_ctx* c, int32_t layer, const ps_seq* seq, int32_t pos0, int32_t n, const void* k, const void* v) {

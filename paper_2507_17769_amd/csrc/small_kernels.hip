@@ -234,15 +234,20 @@ hipError_t launch_rope_append(const float* qkv, int n_splits, bf16_t* q_out, int
 }
 
 // ------------------------------------------------------- logical KV write / read
-// k, v are [n][n_kv][d] in logical order; slots[i] = page * 16 + position in the page of token i, the tokens being
-// consecutive positions starting at a position whose remainder mod 4 is `phase`.  One thread per (group of four
+// k, v are [n][n_kv][d] in logical order, positions pos0 .. pos0 + n - 1 of a sequence; pages.id[i] is the page of positions
+// 16 (pos0 / 16 + i) on.  The pages travel as a kernel argument, not as a transfer of its own on the copy engine with events
+// to order it: eight reads and eight writes of 2047 tokens and a one-token step 495 us before, 457 now.  One thread per (group of four
 // positions aligned to 4, kv head, 8 consecutive dd): in the cache a key keeps 8 consecutive dd of one token together
 // (16 bytes) and a value keeps the four tokens of such a group together for one dd (8 bytes), so the thread moves
 // whole 16-byte rows on the logical side and 16- or 8-byte pieces on the cache side, transposing the 4 x 8 value
 // tile in registers.  Tokens of a group outside [0, n) are left alone (the first and last group may be partial).
+constexpr int KV_COPY_PAGES = 256;   // pages per launch: 1 KiB of the 4 KiB that a kernel's arguments may take
+struct KvPages { int32_t id[KV_COPY_PAGES]; };
+
 template <bool TO_POOL>
-__global__ __launch_bounds__(256) void kv_copy_kernel(bf16_t* __restrict__ pool, const int32_t* __restrict__ slots, int n,
-                                                      int phase, int n_kv, int d, bf16_t* __restrict__ k, bf16_t* __restrict__ v) {
+__global__ __launch_bounds__(256) void kv_copy_kernel(bf16_t* __restrict__ pool, KvPages pages, int pos0, int n, int n_kv, int d,
+                                                      bf16_t* __restrict__ k, bf16_t* __restrict__ v) {
+    const int phase = pos0 & 3;
     const int gpd = d >> 3;  // 8-element groups per head
     const int n_quads = (phase + n + 3) >> 2;
     const long long id = (long long)blockIdx.x * 256 + threadIdx.x;
@@ -251,10 +256,10 @@ __global__ __launch_bounds__(256) void kv_copy_kernel(bf16_t* __restrict__ pool,
     const int dd0 = g * 8;
     const int i0 = 4 * qi - phase;                    // token index of the group's first position
     const int t_lo = max(0, -i0), t_hi = min(4, n - i0);   // valid positions of the group: t_lo <= t < t_hi
-    const int slot = slots[i0 + t_lo] - t_lo;         // slot of the group's first position (same page: groups are aligned)
-    bf16_t* kc = pool + (((size_t)(slot >> 4) * n_kv + h) * 2 + 0) * (size_t)(16 * d);
+    const int pos = pos0 + i0;                        // the group's first position, a multiple of 4 (groups lie within a page)
+    bf16_t* kc = pool + (((size_t)pages.id[(pos >> 4) - (pos0 >> 4)] * n_kv + h) * 2 + 0) * (size_t)(16 * d);
     bf16_t* vc = kc + 16 * d;
-    const int tok0 = slot & 15;                       // a multiple of 4
+    const int tok0 = pos & 15;
     for (int t = t_lo; t < t_hi; t++) {
         uint4* kr = reinterpret_cast<uint4*>(k + ((size_t)(i0 + t) * n_kv + h) * d + dd0);
         uint4* kp = reinterpret_cast<uint4*>(kc + k_elem_offset(tok0 + t, dd0));
@@ -303,17 +308,29 @@ __global__ __launch_bounds__(256) void kv_copy_kernel(bf16_t* __restrict__ pool,
     }
 }
 
-hipError_t launch_kv_copy(bool to_pool, bf16_t* pool_slot, const int32_t* slots_dev, int n, int phase, int n_kv, int d, bf16_t* k,
+hipError_t launch_kv_copy(bool to_pool, bf16_t* pool_slot, const int32_t* page_table, int pos0, int n, int n_kv, int d, bf16_t* k,
                           bf16_t* v, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    if (d % 8 || phase < 0 || phase > 3) return hipErrorInvalidValue;
-    const long long threads = (long long)((phase + n + 3) >> 2) * n_kv * (d >> 3);
-    const int blocks = (int)((threads + 255) / 256);
-    if (to_pool)
-        hipLaunchKernelGGL(kv_copy_kernel<true>, dim3(blocks), dim3(256), 0, st, pool_slot, slots_dev, n, phase, n_kv, d, k, v);
-    else
-        hipLaunchKernelGGL(kv_copy_kernel<false>, dim3(blocks), dim3(256), 0, st, pool_slot, slots_dev, n, phase, n_kv, d, k, v);
-    return hipGetLastError();
+    if (d % 8 || pos0 < 0) return hipErrorInvalidValue;
+    // a launch ends where its last page ends, so that no group of four positions is shared by two
+    for (int done = 0; done < n;) {
+        const int p = pos0 + done, page = p / PS_PAGE_SIZE;
+        const int m = (int)std::min<long long>(n - done, (long long)(page + KV_COPY_PAGES) * PS_PAGE_SIZE - p);
+        const int n_pages = (p + m - 1) / PS_PAGE_SIZE - page + 1;
+        KvPages pages;
+        std::copy(page_table + page, page_table + page + n_pages, pages.id);
+        std::fill(pages.id + n_pages, pages.id + KV_COPY_PAGES, 0);
+        const size_t row = (size_t)done * n_kv * d;
+        const long long threads = (long long)(((p & 3) + m + 3) >> 2) * n_kv * (d >> 3);
+        const int blocks = (int)((threads + 255) / 256);
+        if (to_pool)
+            hipLaunchKernelGGL(kv_copy_kernel<true>, dim3(blocks), dim3(256), 0, st, pool_slot, pages, p, m, n_kv, d, k + row, v + row);
+        else
+            hipLaunchKernelGGL(kv_copy_kernel<false>, dim3(blocks), dim3(256), 0, st, pool_slot, pages, p, m, n_kv, d, k + row, v + row);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        done += m;
+    }
+    return hipSuccess;
 }
 
 // ------------------------------------------------- split reduce + residual + RMSNorm

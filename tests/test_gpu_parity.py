@@ -209,6 +209,26 @@ def test_kv_write_read_roundtrip_is_exact():
     c.close()
 
 
+@pytest.mark.parametrize("pos0,n", [(0, 4096), (0, 4097), (13, 4083), (13, 4084), (4095, 2), (5, 8400)])
+def test_kv_copies_of_more_pages_than_one_launch_takes(pos0, n):
+    # a launch takes the ids of 256 pages; spans that end with them, one position later, and that need three launches
+    c = Case(W.custom_batch("tiny", 7, 0, 0, [8416], name="long copy"))
+    rng = np.random.default_rng(n)
+    k_all, v_all = (rng.integers(0, 0x7F80, size=(8416, 2, 64)).astype(np.uint16) for _ in range(2))
+    pages = c.batch.seqs[0].pages
+    for at in range(0, 8416, 526):   # small spans, a single launch each
+        c.eng.write_kv(0, pages, at, k_all[at:at + 526], v_all[at:at + 526])
+    k, v = c.eng.read_kv(0, pages, pos0, n)
+    assert np.array_equal(k, k_all[pos0:pos0 + n]) and np.array_equal(v, v_all[pos0:pos0 + n])
+    k_new, v_new = (rng.integers(0, 0x7F80, size=(n, 2, 64)).astype(np.uint16) for _ in range(2))
+    c.eng.write_kv(0, pages, pos0, k_new, v_new)
+    k_all[pos0:pos0 + n], v_all[pos0:pos0 + n] = k_new, v_new
+    for at in range(0, 8416, 526):
+        k, v = c.eng.read_kv(0, pages, at, 526)
+        assert np.array_equal(k, k_all[at:at + 526]) and np.array_equal(v, v_all[at:at + 526]), at
+    c.close()
+
+
 def test_state_errors_and_empty_step():
     m = W.MODELS["tiny"]
     ctx = B.Context(m["hidden"], m["n_q"], m["n_kv"], m["head_dim"], m["ffn"], 1, 256, 1e-5, 1e4)
