@@ -664,8 +664,20 @@ extern "C" ps_status ps_set_taps(ps_ctx* c, int32_t layer, const ps_taps* taps) 
 // ------------------------------------------------------------------------------ the step
 static size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 
+static GemmOptions gemm_options(const ps_ctx* c) {
+    GemmOptions o;
+    o.split_k = c->opt_gemm_split_k; o.tile = c->opt_gemm_tile; o.sk_mode = c->opt_gemm_whole_tiles;
+    return o;
+}
+// The output projection of the model writes one partial buffer: it is the logits.
+static GemmOptions head_options(const ps_ctx* c) {
+    GemmOptions o = gemm_options(c);
+    o.split_k = 1;
+    return o;
+}
+
 // What the tiled GEMM needs beside its output for a step of T tokens: the largest over the layer's four projections.
-static void sk_need(const ps_ctx* c, int T, int head_rows, size_t* frag_bytes, int* n_counters, bool no_wreg = false) {
+static void sk_need(const ps_ctx* c, int T, int head_rows, const GemmOptions& o, size_t* frag_bytes, int* n_counters) {
     const ps_model_desc& d = c->desc;
     const int H = d.hidden, F = d.ffn, NQ = d.n_q_heads * d.head_dim, NQKV = qkv_cols(d);
     const int shapes[4][3] = {{NQKV, H, GemmOut::PARTIAL_F32}, {H, NQ, GemmOut::PARTIAL_F32}, {2 * F, H, GemmOut::SWIGLU_BF16}, {H, F, GemmOut::PARTIAL_F32}};
@@ -674,14 +686,14 @@ static void sk_need(const ps_ctx* c, int T, int head_rows, size_t* frag_bytes, i
     for (const auto& sh : shapes) {
         size_t fb = 0;
         int nc = 0;
-        gemm_workspace(T, sh[0], sh[1], sh[2], c->opt_gemm_split_k, c->opt_gemm_tile, c->opt_gemm_whole_tiles, &fb, &nc, no_wreg);
+        gemm_workspace(T, sh[0], sh[1], sh[2], o, &fb, &nc);
         *frag_bytes = std::max(*frag_bytes, fb);
         *n_counters = std::max(*n_counters, nc);
     }
     if (head_rows > 0) {   // the output projection: one row per sequence
         size_t fb = 0;
         int nc = 0;
-        gemm_workspace(head_rows, c->vocab, H, GemmOut::PARTIAL_F32, 1, c->opt_gemm_tile, c->opt_gemm_whole_tiles, &fb, &nc);
+        gemm_workspace(head_rows, c->vocab, H, GemmOut::PARTIAL_F32, head_options(c), &fb, &nc);
         *frag_bytes = std::max(*frag_bytes, fb);
         *n_counters = std::max(*n_counters, nc);
     }
@@ -689,6 +701,7 @@ static void sk_need(const ps_ctx* c, int T, int head_rows, size_t* frag_bytes, i
 
 static ps_status ensure_workspaces(ps_ctx* c, int T, int n_part_slots, int head_rows) {
     const ps_model_desc& d = c->desc;
+    const GemmOptions o = gemm_options(c);
     if (T > c->cap_tokens) {
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         free_workspaces(c);
@@ -700,7 +713,7 @@ static ps_status ensure_workspaces(ps_ctx* c, int T, int n_part_slots, int head_
         if ((st = dev_alloc(c, &c->ws_xn, (size_t)cap16 * H * 2, "xn")) != PS_OK) return st;
         if ((st = dev_alloc(c, &c->ws_q, (size_t)cap * NQ * 2, "q")) != PS_OK) return st;
         if ((st = dev_alloc(c, &c->ws_attn, (size_t)cap16 * NQ * 2, "attn")) != PS_OK) return st;
-        c->act_bytes = gemm_out_bytes(cap, 2 * F, H, GemmOut::SWIGLU_BF16, 0, 0);  // whole row tiles of the GEMM
+        c->act_bytes = gemm_out_bytes(cap, 2 * F, H, GemmOut::SWIGLU_BF16, o);  // whole row tiles of the GEMM
         if ((st = dev_alloc(c, &c->ws_act, c->act_bytes, "act")) != PS_OK) return st;
         if ((st = dev_alloc(c, &c->ws_x1, (size_t)cap * H * 4, "x1")) != PS_OK) return st;
         if (d.n_layers > 1 && (st = dev_alloc(c, &c->ws_xmid, (size_t)cap * H * 4, "inter-layer x")) != PS_OK) return st;
@@ -712,9 +725,9 @@ static ps_status ensure_workspaces(ps_ctx* c, int T, int n_part_slots, int head_
     }
     {   // GEMM partial buffer: sized for this step's T (the split count depends on T)
         const int H = d.hidden, F = d.ffn, NQ = d.n_q_heads * d.head_dim, NQKV = qkv_cols(d);
-        size_t need = gemm_out_bytes(T, NQKV, H, GemmOut::PARTIAL_F32, c->opt_gemm_split_k, c->opt_gemm_tile);
-        need = std::max(need, gemm_out_bytes(T, H, NQ, GemmOut::PARTIAL_F32, c->opt_gemm_split_k, c->opt_gemm_tile));
-        need = std::max(need, gemm_out_bytes(T, H, F, GemmOut::PARTIAL_F32, c->opt_gemm_split_k, c->opt_gemm_tile));
+        size_t need = gemm_out_bytes(T, NQKV, H, GemmOut::PARTIAL_F32, o);
+        need = std::max(need, gemm_out_bytes(T, H, NQ, GemmOut::PARTIAL_F32, o));
+        need = std::max(need, gemm_out_bytes(T, H, F, GemmOut::PARTIAL_F32, o));
         if (need > c->part_bytes) {
             HIP_TRY(c, hipStreamSynchronize(c->stream));
             dev_free(c->ws_part);
@@ -728,7 +741,7 @@ static ps_status ensure_workspaces(ps_ctx* c, int T, int n_part_slots, int head_
     {   // tiled GEMM workspace
         size_t fb = 0;
         int nc = 0;
-        sk_need(c, T, head_rows, &fb, &nc);
+        sk_need(c, T, head_rows, o, &fb, &nc);
         if (fb > c->skfrag_bytes) {
             HIP_TRY(c, hipStreamSynchronize(c->stream));
             dev_free(c->ws_skfrag);
@@ -809,21 +822,23 @@ struct StepBufs {
 // sums, than the other kernels: it is left out where only that makes the step too large.
 static ps_status carve_static(ps_ctx* c, int T, int n_part_slots, size_t meta_bytes, StepBufs* w, bool no_wreg = false) {
     const ps_model_desc& d = c->desc;
+    GemmOptions o = gemm_options(c);
+    o.no_wreg = no_wreg;
     const int H = d.hidden, F = d.ffn, NQ = d.n_q_heads * d.head_dim, NQKV = qkv_cols(d);
     const size_t T16 = (size_t)((T + 15) & ~15);
     size_t at = 0;
     auto take = [&](size_t bytes) { const size_t o = at; at = (at + bytes + 255) & ~(size_t)255; return o; };
     const size_t o_xn = take(T16 * H * 2), o_q = take((size_t)T * NQ * 2), o_attn = take(T16 * NQ * 2);
-    w->act_bytes = gemm_out_bytes(T, 2 * F, H, GemmOut::SWIGLU_BF16, 0, 0);
+    w->act_bytes = gemm_out_bytes(T, 2 * F, H, GemmOut::SWIGLU_BF16, o);
     const size_t o_act = take(w->act_bytes), o_x1 = take((size_t)T * H * 4), o_xmid = take(d.n_layers > 1 ? (size_t)T * H * 4 : 0);
-    w->part_bytes = gemm_out_bytes(T, NQKV, H, GemmOut::PARTIAL_F32, c->opt_gemm_split_k, c->opt_gemm_tile, no_wreg);
-    w->part_bytes = std::max(w->part_bytes, gemm_out_bytes(T, H, NQ, GemmOut::PARTIAL_F32, c->opt_gemm_split_k, c->opt_gemm_tile, no_wreg));
-    w->part_bytes = std::max(w->part_bytes, gemm_out_bytes(T, H, F, GemmOut::PARTIAL_F32, c->opt_gemm_split_k, c->opt_gemm_tile, no_wreg));
+    w->part_bytes = gemm_out_bytes(T, NQKV, H, GemmOut::PARTIAL_F32, o);
+    w->part_bytes = std::max(w->part_bytes, gemm_out_bytes(T, H, NQ, GemmOut::PARTIAL_F32, o));
+    w->part_bytes = std::max(w->part_bytes, gemm_out_bytes(T, H, F, GemmOut::PARTIAL_F32, o));
     const size_t o_part = take(w->part_bytes);
     const size_t o_po = take((size_t)n_part_slots * 16 * d.head_dim * 4), o_pml = take((size_t)n_part_slots * 16 * 2 * 4);
     const size_t o_meta = take(meta_bytes);
     int n_cnt = 0;
-    sk_need(c, T, 0, &w->skfrag_bytes, &n_cnt, no_wreg);
+    sk_need(c, T, 0, o, &w->skfrag_bytes, &n_cnt);
     w->no_wreg = no_wreg;
     w->skcnt_n = (n_cnt + 3) & ~3;
     const size_t o_skfrag = take(w->skfrag_bytes), o_skcnt = take((size_t)w->skcnt_n * sizeof(int));
@@ -1009,9 +1024,8 @@ static ps_status step_impl(ps_ctx* c, const ps_seq* seqs, int32_t n_seqs, const 
         // 1: QKV projection -> fp32 partials
         GemmArgs g{};
         g.A = W.xn; g.Wp = L.wqkv_t; g.M = T; g.N = NQKV; g.K = H; g.kind = GemmOut::PARTIAL_F32;
-        g.out = W.part; g.out_bytes = W.part_bytes; g.split_k = c->opt_gemm_split_k; g.tile = c->opt_gemm_tile;
+        g.out = W.part; g.out_bytes = W.part_bytes; g.opt = gemm_options(c); g.opt.no_wreg = W.no_wreg;
         g.sk_frag = W.skfrag; g.sk_frag_bytes = W.skfrag_bytes; g.sk_counters = W.skcnt; g.sk_n_counters = W.skcnt_n;
-        g.sk_mode = c->opt_gemm_whole_tiles; g.no_wreg = W.no_wreg;
         HIP_TRY(c, run_gemm(g, &n_splits, 0));
         if (stats) HIP_TRY(c, hipEventRecord(c->ev[++e], s));
         // 2: sum the partials, rotate, round once to bf16, append k/v to the pages
@@ -1133,9 +1147,7 @@ static ps_status step_impl(ps_ctx* c, const ps_seq* seqs, int32_t n_seqs, const 
         GemmArgs g{};
         g.A = W.xn; g.Wp = c->wout_t; g.M = M; g.N = V; g.K = H; g.kind = GemmOut::PARTIAL_F32;
         g.out = logits; g.out_bytes = (size_t)M * V * sizeof(float);
-        g.split_k = 1;  // one partial buffer: it is the logits
-        g.tile = c->opt_gemm_tile;
-        g.sk_mode = c->opt_gemm_whole_tiles;
+        g.opt = head_options(c);
         g.sk_frag = W.skfrag; g.sk_frag_bytes = W.skfrag_bytes; g.sk_counters = W.skcnt; g.sk_n_counters = W.skcnt_n;
         int n_splits = 1;
         HIP_TRY(c, launch_gemm(g, &n_splits, s));

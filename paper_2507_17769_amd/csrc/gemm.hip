@@ -29,11 +29,8 @@
 // residual, normalises, rotates ...) or, for the fused gate/up matrix, silu(gate) * up in bf16.
 #include "ps_device.h"
 #include "gemm_wreg.h"
-#include "sk_decomp.h"
 
 #include <algorithm>
-#include <cmath>
-#include <limits>
 #include <mutex>
 
 namespace ps {
@@ -583,19 +580,8 @@ __global__ __launch_bounds__(256) void gemm_sk_kernel(SkParams sp) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Planning and launch
+// Launch (gemm_plan.h plans)
 // ------------------------------------------------------------------------------------------
-struct GemmPlan {
-    bool wstream;
-    bool wreg;          // weights in registers (gemm_wreg.hip), with the plan below
-    WregPlan wreg_plan;
-    bool big_tile;      // tiled: 256x256 blocks (else 128x128)
-    int splits;         // partial buffers written
-    int kb_per_split;   // 32-wide k-blocks per split
-    bool cut_tail;      // tiled: cut the K loops of the last, partial wave of tiles over the blocks (one split only)
-    int slots_per_xcd;  // tiled: parked pieces an XCD may hold
-};
-
 static int device_cus() {
     static int cus = 0;
     static std::once_flag once;
@@ -607,184 +593,10 @@ static int device_cus() {
     return cus;
 }
 
-// Estimated time (us) of the tiled kernel for one choice of tile edge, K splits and tail cutting, from the rates measured
-// on the layer shapes: a block takes about 1.4 us (0.9 us for a 128x128 tile, two of which share a compute unit) per pair
-// of k-blocks plus a fixed prologue and epilogue per unit; blocks take units in waves; every split beyond the first is
-// written and read back by the consumer; parked pieces of a cut tail cost about 1.4 us per MB all told (store, count,
-// reload by the last block and the clock the extra traffic costs the rest of the step: measured on the gate/up and O
-// matrices), less where whole tiles follow to hide them behind.
-static double tiled_estimate(int M, int N, int K, int edge, int splits, bool cut, int* kp_per_split, int* eff_splits, int* slots_per_xcd) {
-    const int B = device_cus() * (edge == 256 ? 1 : 2) / 8;
-    const int KPt = K / 64;
-    const int kps = (KPt + splits - 1) / splits, s_eff = (KPt + kps - 1) / kps;
-    const int tiles = ((M + edge - 1) / edge) * ((N + edge - 1) / edge), units = tiles * s_eff;
-    const int upx = (units + 7) / 8;
-    const double t_pair = edge == 256 ? 1.4 : 0.9, t_fix = edge == 256 ? 8.0 : 4.0;
-    const double unit_us = kps * t_pair + t_fix;
-    double waves = 0, waves_uncut = 0;
-    int slots = 0, pieces = 0;
-    bool any_full = false;
-    for (int x = 0; x < 8; x++) {
-        const int T = std::min(units, (x + 1) * upx) - x * upx;
-        if (T <= 0) break;
-        const int full = T / B, R = T % B;
-        any_full |= full > 0;
-        waves_uncut = std::max(waves_uncut, (double)full + (R > 0));
-        if (!cut || R == 0) { waves = std::max(waves, (double)full + (R > 0)); continue; }
-        const int Bt = sk_tail_blocks(B, R, kps);
-        waves = std::max(waves, full + (double)R / Bt);
-        slots = std::max(slots, sk_slots(Bt, R));
-        pieces += Bt > R ? sk_slots(Bt, R) : 0;
-    }
-    *kp_per_split = kps;
-    *eff_splits = s_eff;
-    *slots_per_xcd = slots;
-    // With 256x256 tiles on every compute unit the device runs at its power limit, and compute units left idle by an
-    // uncut tail give part of their share back as clock for the busy ones: measured on the 70B-shaped gate/up matrix,
-    // cutting the tail of 4.4 waves bought nothing, where the arithmetic says 11 %.  Half the gain is what is counted.
-    if (cut && edge == 256) waves = waves_uncut - 0.5 * (waves_uncut - waves);
-    double us = waves * unit_us;
-    if (s_eff > 1) us += 2.0 * (s_eff - 1) * (double)M * N * 4 / 3e6;
-    if (cut) us += pieces * (double)edge * edge * 4 / 0.7e6 * (any_full ? 0.6 : 1.0) + 10.0;
-    return us;
-}
+size_t gemm_out_bytes(int M, int N, int K, int kind, const GemmOptions& o) { return gemm_plan_out_bytes(M, N, K, kind, o, device_cus()); }
 
-// Estimated time (us) of the weights-in-registers kernel for one plan: blocks run one per compute unit in waves, a stage
-// costs 0.34 + 0.07 per row tile with four column groups (0.22 + 0.096 with two, whose K shares copy twice the activations),
-// a block 8 more for its first loads and its epilogue, a wave that is not full three quarters of its time plus a quarter of
-// its fill (the blocks that do run have the memory to themselves); the weights stream at 6.2 TB/s, and the shorter of the
-// two times hides all but 15 % of itself.  Fitted to 190 runs of the 8B shapes at 80 to 1024 tokens; the plan it picks is within
-// 8 % of the best one measured at every one of them.  Partial sums are read back by the consumer.
-static double wreg_estimate(const WregPlan& g, int M, int N, int K) {
-    const int cus = device_cus(), shares = 8 / g.nc, n = K / 32 / (g.splits * shares);
-    const int blocks = g.row_tiles * g.splits * ((N / 64 + g.nc - 1) / g.nc);
-    const int full = blocks / cus, rem = blocks % cus;
-    const double waves = full + (rem ? 0.77 + 0.23 * rem / cus : 0.0);
-    const double core = 2.0 + waves * (8.0 + n * (g.nc == 4 ? 0.34 + 0.07 * g.tm : 0.22 + 0.096 * g.tm));
-    const double hbm = 2.0 * N * K / 6.2e6;
-    return std::max(core, hbm) + 0.15 * std::min(core, hbm) + (g.splits - 1) * (double)M * N * 4 / 5e6;
-}
-
-// The best plan of the weights-in-registers kernel, or an estimate of infinity where it does not serve the shape.
-static double wreg_best(int M, int N, int K, int kind, int split_opt, WregPlan* best) {
-    double best_us = std::numeric_limits<double>::infinity();
-    const int tiles = (M + 15) / 16;
-    const int s_lo = kind == GemmOut::SWIGLU_BF16 ? 1 : (split_opt > 0 ? std::min(split_opt, 8) : 1);
-    const int s_hi = kind == GemmOut::SWIGLU_BF16 ? 1 : (split_opt > 0 ? s_lo : 8);
-    for (int rt = (tiles + WREG_MAX_TM - 1) / WREG_MAX_TM; rt <= (tiles + WREG_MIN_TM - 1) / WREG_MIN_TM; rt++) {
-        const int tm = std::max(WREG_MIN_TM, (tiles + rt - 1) / rt);
-        if (rt > 1 && tm * (rt - 1) >= tiles) continue;   // the last row block would be empty
-        for (int nc : {4, 2})
-            for (int sp = s_lo; sp <= s_hi; sp++) {
-                const WregPlan g{tm, nc, sp, rt};
-                if (!wreg_valid(g, M, N, K, kind)) continue;
-                const double us = wreg_estimate(g, M, N, K);
-                if (us < best_us) { best_us = us; *best = g; }
-            }
-    }
-    return best_us;
-}
-
-static GemmPlan plan_gemm(int M, int N, int K, int kind, int split_opt, int tile_opt, int sk_mode = 0, bool allow_wreg = true) {
-    GemmPlan g;
-    g.wreg = false;
-    allow_wreg = allow_wreg && M > 64 && tile_opt == 0 && sk_mode == 0;   // the options that name the tiled kernel get it
-    // measured: streaming wins up to 96 tokens for every projection, and up to 160 (ten row tiles) for all but the QKV-shaped
-    // one (more columns than rows of weights: 48 blocks per split and six splits of partial sums; 129 tokens: 29 vs 24 us),
-    // above all for the gate/up matrix (129 tokens: 61 vs 75 us) and the down projection (42 vs 46)
-    g.wstream = M <= 64 || (tile_opt == 0 && (M <= 96 || (M <= 160 && (kind == GemmOut::SWIGLU_BF16 || N <= K))));
-    g.big_tile = false;
-    g.splits = 1;
-    g.kb_per_split = K / 32;
-    g.cut_tail = false;
-    g.slots_per_xcd = 0;
-    if (g.wstream) {
-        // Measured against streaming up to 160 tokens (us, streaming / weights in registers): gate/up of the 8B shape 41.9 /
-        // 42.6 at 80 tokens, 46.9 / 45.9 at 97, 53.4 / 49.1 at 144, 58.9 / 49.8 at 160; of the 70B shape, where streaming
-        // puts two blocks on a compute unit, 157 / 136 at 80 and 217 / 155 at 128; QKV 17.7 / 15.0 at 80; the O and down
-        // projections are no faster (11.5 / 12.4, 24.4 / 25.2 at 80, 14.4 / 14.4, 29.6 / 30.9 at 144).
-        const bool gate_up = kind == GemmOut::SWIGLU_BF16;
-        if (allow_wreg && ((gate_up && (M > 96 || N / 128 > device_cus())) || (!gate_up && N > K))) {
-            const double us = wreg_best(M, N, K, kind, split_opt, &g.wreg_plan);
-            g.wreg = std::isfinite(us) && g.wreg_plan.row_tiles * g.wreg_plan.splits * (N / 64 / g.wreg_plan.nc) >= device_cus() / 2;
-        }
-        if (g.wreg) {
-            g.wstream = false;
-            g.splits = g.wreg_plan.splits;
-            return g;
-        }
-        const int groups = N / 64, KB = K / 32;
-        int s = 1;
-        if (kind != GemmOut::SWIGLU_BF16) {
-            s = split_opt > 0 ? split_opt : (512 + groups - 1) / groups;  // aim at two blocks per CU
-            s = std::min(s, 8);
-            s = std::min(s, std::max(1, KB / 8));  // keep at least two k-blocks per wavefront slice
-            s = std::max(s, 1);
-        }
-        int kps = (KB + s - 1) / s;
-        kps += kps & 1;  // whole stages of two k-blocks
-        g.kb_per_split = kps;
-        g.splits = (KB + kps - 1) / kps;
-    } else {
-        // every combination of tile edge, K splits (none for the gate/up matrix, whose epilogue is not linear) and, for
-        // one split, tail cutting; the smallest estimate wins
-        const int s_lo = kind == GemmOut::SWIGLU_BF16 ? 1 : (split_opt > 0 ? std::min(split_opt, 8) : 1);
-        const int s_hi = kind == GemmOut::SWIGLU_BF16 ? 1 : (split_opt > 0 ? s_lo : 8);
-        double best = 0;
-        bool first = true;
-        for (int edge : {128, 256}) {
-            if ((tile_opt == 128 || tile_opt == 256) && edge != tile_opt) continue;
-            for (int sp = s_lo; sp <= s_hi; sp++)
-                for (int cut = 0; cut < (sp == 1 && sk_mode != 1 ? 2 : 1); cut++) {
-                    int kps, eff, slots;
-                    double us = tiled_estimate(M, N, K, edge, sp, cut != 0, &kps, &eff, &slots);
-                    if (cut && slots == 0) continue;
-                    if (cut && sk_mode == 2) us -= 1e9;   // test knob: a tail that can be cut is cut
-                    if (first || us < best) {
-                        first = false; best = us;
-                        g.big_tile = edge == 256; g.splits = eff; g.kb_per_split = 2 * kps; g.cut_tail = cut != 0; g.slots_per_xcd = slots;
-                    }
-                }
-        }
-        // The tiled estimate runs below what is measured: by a sixth with 128x128 tiles (5 to 30 % over 40 shapes), by an eighth
-        // with 256x256 ones.  Where the weights-in-registers kernel wins
-        // (8B shape, us, tiled / it): gate/up 80.2 / 67.0 at 256 tokens, 115 / 69.2 at 271, 187 / 158 at 640, 434 / 379 at
-        // 1600; down 45.3 / 38.1, 52.3 / 39.3, 94.1 / 66.4; 70B shape at 264 tokens: gate/up 443 / 307, down 212 / 146.
-        // The tiled kernel keeps what fills its 256x256 tiles: gate/up at 512 tokens 112 / 121, at 2048 444 / 460.
-        WregPlan w;
-        if (allow_wreg && wreg_best(M, N, K, kind, split_opt, &w) < (g.big_tile ? 1.12 : 1.17) * best) {
-            g.wreg = true;
-            g.wreg_plan = w;
-            g.splits = w.splits;
-            g.cut_tail = false;
-            g.slots_per_xcd = 0;
-        }
-    }
-    return g;
-}
-
-size_t gemm_out_bytes(int M, int N, int K, int kind, int split_opt, int tile_opt, bool no_wreg) {
-    if (kind == GemmOut::SWIGLU_BF16) {
-        // dense [rows][N/2] in operand order.  The tiled kernel stores whole row tiles without a row check
-        // (rows past M are never read back), so the buffer holds M rounded up to its largest tile.
-        const size_t rows = M <= 64 ? (size_t)((M + 15) / 16 * 16) : (size_t)((M + 255) / 256 * 256);
-        return rows * (N / 2) * sizeof(bf16_t);
-    }
-    // room for whichever kernel the options of a later call pick
-    int splits = plan_gemm(M, N, K, kind, split_opt, tile_opt, 0, false).splits;
-    if (!no_wreg) splits = std::max(splits, plan_gemm(M, N, K, kind, split_opt, tile_opt).splits);
-    return (size_t)splits * M * N * sizeof(float);
-}
-
-void gemm_workspace(int M, int N, int K, int kind, int split_opt, int tile_opt, int sk_mode, size_t* frag_bytes, int* n_counters, bool no_wreg) {
-    *frag_bytes = 0;
-    *n_counters = 0;
-    if (M <= 0) return;
-    const GemmPlan g = plan_gemm(M, N, K, kind, split_opt, tile_opt, sk_mode, !no_wreg);
-    if (g.wstream || g.wreg) return;
-    const int b = g.big_tile ? 256 : 128;
-    *frag_bytes = (size_t)8 * g.slots_per_xcd * b * b * sizeof(float);
-    *n_counters = ((M + b - 1) / b) * ((N + b - 1) / b);
+void gemm_workspace(int M, int N, int K, int kind, const GemmOptions& o, size_t* frag_bytes, int* n_counters) {
+    gemm_plan_workspace(M, N, K, kind, o, device_cus(), frag_bytes, n_counters);
 }
 
 template <int BM, int BN, int NS, int KIND>
@@ -824,9 +636,9 @@ hipError_t launch_gemm(const GemmArgs& a, int* n_splits, hipStream_t st) {
     // the tiled kernel addresses A and Wp with 32-bit byte offsets
     if (a.M > 64 && ((size_t)a.N * a.K * 2 >= (1ull << 32) || (size_t)((a.M + 15) / 16 * 16) * a.K * 2 >= (1ull << 32)))
         return hipErrorInvalidValue;
-    const GemmPlan g = plan_gemm(a.M, a.N, a.K, a.kind, a.split_k, a.tile, a.sk_mode, !a.no_wreg);
+    const GemmPlan g = plan_gemm(a.M, a.N, a.K, a.kind, a.opt, device_cus());
     if ((size_t)g.splits * (a.kind == GemmOut::SWIGLU_BF16 ? 0 : (size_t)a.M * a.N * sizeof(float)) > a.out_bytes ||
-        (a.kind == GemmOut::SWIGLU_BF16 && gemm_out_bytes(a.M, a.N, a.K, a.kind, a.split_k, a.tile) > a.out_bytes))
+        (a.kind == GemmOut::SWIGLU_BF16 && gemm_out_bytes(a.M, a.N, a.K, a.kind, a.opt) > a.out_bytes))
         return hipErrorInvalidValue;
     GemmParams p;
     p.A = a.A; p.Wp = a.Wp; p.M = a.M; p.N = a.N; p.K = a.K; p.kind = a.kind; p.out = a.out;

@@ -240,16 +240,6 @@ static hipError_t launch_tm(const WregParams& p, int nc, int kind, hipStream_t s
     return nc == 4 ? launch_kind<TM, 4, GemmOut::PARTIAL_F32>(p, st) : launch_kind<TM, 2, GemmOut::PARTIAL_F32>(p, st);
 }
 
-bool wreg_valid(const WregPlan& g, int M, int N, int K, int kind) {
-    if (g.tm < WREG_MIN_TM || g.tm > WREG_MAX_TM || (g.nc != 2 && g.nc != 4) || g.splits < 1 || g.row_tiles < 1) return false;
-    if (M <= 0 || N % 64 || K % 32 || (kind == GemmOut::SWIGLU_BF16 && g.splits != 1)) return false;
-    if ((long long)16 * g.tm * g.row_tiles < M) return false;
-    // 32-bit buffer offsets, the upper half of which marks a request as one past the end
-    if ((long long)N * K * 2 >= (1ll << 31) || (long long)(M + 15) / 16 * 16 * K * 2 >= (1ll << 31)) return false;
-    const int shares = g.splits * (8 / g.nc);
-    return (K / 32) % (shares * WREG_STAGES) == 0;
-}
-
 hipError_t launch_gemm_wreg(const GemmArgs& a, const WregPlan& g, hipStream_t st) {
     if (!wreg_valid(g, a.M, a.N, a.K, a.kind)) return hipErrorInvalidValue;
     WregParams p;

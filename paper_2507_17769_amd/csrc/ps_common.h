@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "../../include/polystep.h"
+#include "gemm_plan.h"
 
 namespace ps {
 
@@ -88,10 +89,6 @@ struct SeqInfo {
     int32_t page_off;  // offset of its page list in the flat page array
 };
 
-struct GemmOut {
-    enum Kind : int { PARTIAL_F32 = 0, SWIGLU_BF16 = 1 };
-};
-
 // ------------------------------------------------------------------ launchers (device side)
 // All take the stream explicitly and return hipGetLastError() of the launch.
 // out is written in operand order (act_offset)
@@ -140,22 +137,19 @@ struct GemmArgs {
     int kind;          // GemmOut::Kind
     void* out;         // PARTIAL_F32: fp32 [splits][M][N] row-major; SWIGLU_BF16: bf16 [M][N/2] in operand order
     size_t out_bytes;  // capacity of out; at least gemm_out_bytes(...)
-    int split_k;       // 0 = choose
-    int tile;          // M > 64: 0 = choose (streaming up to 96 tokens, then a tile), 128 or 256 = block tile edge
+    GemmOptions opt;
     // tiled kernel only (see gemm_workspace): parked accumulators of K runs that cover part of a tile, and one counter
     // per tile that must be zero on entry (the kernel leaves it zero)
-    int sk_mode;       // 0 = the cost model decides whether the tail's K loops are cut, 1 = never (whole tiles only), 2 = wherever possible
     float* sk_frag;
     size_t sk_frag_bytes;
     int* sk_counters;
     int sk_n_counters;
-    bool no_wreg;      // leave the weights-in-registers kernel out (a static step whose scratch its K splits would overflow)
 };
 // *n_splits receives the number of partial buffers written (1 for SWIGLU_BF16)
 hipError_t launch_gemm(const GemmArgs& a, int* n_splits, hipStream_t st);
-size_t gemm_out_bytes(int M, int N, int K, int kind, int split_k_opt, int tile_opt, bool no_wreg = false);
+size_t gemm_out_bytes(int M, int N, int K, int kind, const GemmOptions& o);
 // what launch_gemm needs in sk_frag / sk_counters for this shape (both 0 unless the tiled kernel serves it)
-void gemm_workspace(int M, int N, int K, int kind, int split_k_opt, int tile_opt, int sk_mode, size_t* frag_bytes, int* n_counters, bool no_wreg = false);
+void gemm_workspace(int M, int N, int K, int kind, const GemmOptions& o, size_t* frag_bytes, int* n_counters);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st);   // bytes: rounded down to a multiple of 16
 hipError_t launch_fill_words(void* p, size_t bytes, uint32_t word, hipStream_t st);
 
