@@ -699,9 +699,8 @@ static void sk_need(const ps_ctx* c, int T, int head_rows, const GemmOptions& o,
     }
 }
 
-static ps_status ensure_workspaces(ps_ctx* c, int T, int n_part_slots, int head_rows) {
+static ps_status ensure_workspaces(ps_ctx* c, int T, int n_part_slots, int head_rows, const GemmOptions& o) {
     const ps_model_desc& d = c->desc;
-    const GemmOptions o = gemm_options(c);
     if (T > c->cap_tokens) {
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         free_workspaces(c);
@@ -813,49 +812,67 @@ struct StepBufs {
     size_t skfrag_bytes = 0;
     int* skcnt = nullptr;
     int skcnt_n = 0;
-    bool no_wreg = false;  // static steps only: leave the weights-in-registers GEMM out (see carve_static)
+    GemmOptions gemm;      // of the layer projections
     char* meta = nullptr;  // static steps only: device copy of the metadata
 };
 
-// Lay the buffers of a step of T tokens out in the static scratch array.  Nothing is allocated: a step whose buffers
-// do not fit PS_STATIC_SCRATCH_BYTES is refused.  The weights-in-registers GEMM may want more K splits, i.e. more partial
-// sums, than the other kernels: it is left out where only that makes the step too large.
-static ps_status carve_static(ps_ctx* c, int T, int n_part_slots, size_t meta_bytes, StepBufs* w, bool no_wreg = false) {
+// Where the buffers of a step of T tokens lie in the static scratch array; `total` may exceed the array.
+struct StaticLayout {
+    size_t xn, q, attn, act, x1, xmid, part, part_o, part_ml, meta, skfrag, skcnt, total;
+    size_t act_bytes, part_bytes, skfrag_bytes;
+    int skcnt_n;
+};
+static StaticLayout static_layout(const ps_ctx* c, int T, int n_part_slots, size_t meta_bytes, const GemmOptions& o) {
     const ps_model_desc& d = c->desc;
-    GemmOptions o = gemm_options(c);
-    o.no_wreg = no_wreg;
     const int H = d.hidden, F = d.ffn, NQ = d.n_q_heads * d.head_dim, NQKV = qkv_cols(d);
     const size_t T16 = (size_t)((T + 15) & ~15);
+    StaticLayout m;
     size_t at = 0;
-    auto take = [&](size_t bytes) { const size_t o = at; at = (at + bytes + 255) & ~(size_t)255; return o; };
-    const size_t o_xn = take(T16 * H * 2), o_q = take((size_t)T * NQ * 2), o_attn = take(T16 * NQ * 2);
-    w->act_bytes = gemm_out_bytes(T, 2 * F, H, GemmOut::SWIGLU_BF16, o);
-    const size_t o_act = take(w->act_bytes), o_x1 = take((size_t)T * H * 4), o_xmid = take(d.n_layers > 1 ? (size_t)T * H * 4 : 0);
-    w->part_bytes = gemm_out_bytes(T, NQKV, H, GemmOut::PARTIAL_F32, o);
-    w->part_bytes = std::max(w->part_bytes, gemm_out_bytes(T, H, NQ, GemmOut::PARTIAL_F32, o));
-    w->part_bytes = std::max(w->part_bytes, gemm_out_bytes(T, H, F, GemmOut::PARTIAL_F32, o));
-    const size_t o_part = take(w->part_bytes);
-    const size_t o_po = take((size_t)n_part_slots * 16 * d.head_dim * 4), o_pml = take((size_t)n_part_slots * 16 * 2 * 4);
-    const size_t o_meta = take(meta_bytes);
+    auto take = [&](size_t bytes) { const size_t r = at; at = (at + bytes + 255) & ~(size_t)255; return r; };
+    m.xn = take(T16 * H * 2); m.q = take((size_t)T * NQ * 2); m.attn = take(T16 * NQ * 2);
+    m.act_bytes = gemm_out_bytes(T, 2 * F, H, GemmOut::SWIGLU_BF16, o);
+    m.act = take(m.act_bytes); m.x1 = take((size_t)T * H * 4); m.xmid = take(d.n_layers > 1 ? (size_t)T * H * 4 : 0);
+    m.part_bytes = gemm_out_bytes(T, NQKV, H, GemmOut::PARTIAL_F32, o);
+    m.part_bytes = std::max(m.part_bytes, gemm_out_bytes(T, H, NQ, GemmOut::PARTIAL_F32, o));
+    m.part_bytes = std::max(m.part_bytes, gemm_out_bytes(T, H, F, GemmOut::PARTIAL_F32, o));
+    m.part = take(m.part_bytes);
+    m.part_o = take((size_t)n_part_slots * 16 * d.head_dim * 4); m.part_ml = take((size_t)n_part_slots * 16 * 2 * 4);
+    m.meta = take(meta_bytes);
     int n_cnt = 0;
-    sk_need(c, T, 0, o, &w->skfrag_bytes, &n_cnt);
-    w->no_wreg = no_wreg;
-    w->skcnt_n = (n_cnt + 3) & ~3;
-    const size_t o_skfrag = take(w->skfrag_bytes), o_skcnt = take((size_t)w->skcnt_n * sizeof(int));
+    sk_need(c, T, 0, o, &m.skfrag_bytes, &n_cnt);
+    m.skcnt_n = (n_cnt + 3) & ~3;
+    m.skfrag = take(m.skfrag_bytes); m.skcnt = take((size_t)m.skcnt_n * sizeof(int));
+    m.total = at;
+    return m;
+}
+
+// GEMM options of a step's layers.  A function of the batch and the options of the context alone, not of the call: a batch
+// that the static scratch can hold is planned within it by every call, so that ps_step_static gives the bits of ps_step.
+static GemmOptions layer_gemm_options(const ps_ctx* c, const StepPlan& p) {
+    GemmOptions o = gemm_options(c);
+    o.cap_splits = true;
+    o.cap_splits = static_layout(c, p.n_tokens, p.n_partial_slots, meta_layout(p, false).total, o).total <= (size_t)PS_STATIC_SCRATCH_BYTES;
+    return o;
+}
+
+// The buffers of a static step.  Nothing is allocated: a step whose buffers do not fit PS_STATIC_SCRATCH_BYTES is refused.
+static ps_status carve_static(ps_ctx* c, int T, int n_part_slots, size_t meta_bytes, StepBufs* w) {
     if (meta_bytes > STATIC_META_SLOT)
         return fail(c, PS_ERANGE, "ps_step_static: the step's metadata (" + std::to_string(meta_bytes) + " bytes: positions, page lists, attention work list) exceeds " +
                                       std::to_string(STATIC_META_SLOT) + " bytes; use ps_step for batches of this size");
-    if (at > (size_t)PS_STATIC_SCRATCH_BYTES && !no_wreg) return carve_static(c, T, n_part_slots, meta_bytes, w, true);
-    if (at > (size_t)PS_STATIC_SCRATCH_BYTES)
-        return fail(c, PS_ERANGE, "ps_step_static: the step needs " + std::to_string(at) + " bytes of scratch, the static array holds " +
+    const StaticLayout m = static_layout(c, T, n_part_slots, meta_bytes, w->gemm);
+    if (m.total > (size_t)PS_STATIC_SCRATCH_BYTES)
+        return fail(c, PS_ERANGE, "ps_step_static: the step needs " + std::to_string(m.total) + " bytes of scratch, the static array holds " +
                                       std::to_string((size_t)PS_STATIC_SCRATCH_BYTES) + "; use ps_step for batches of this size");
     unsigned char* b = c->static_scratch;
-    w->xn = reinterpret_cast<bf16_t*>(b + o_xn); w->q = reinterpret_cast<bf16_t*>(b + o_q); w->attn = reinterpret_cast<bf16_t*>(b + o_attn);
-    w->act = reinterpret_cast<bf16_t*>(b + o_act); w->x1 = reinterpret_cast<float*>(b + o_x1); w->xmid = reinterpret_cast<float*>(b + o_xmid);
-    w->part = reinterpret_cast<float*>(b + o_part); w->part_o = reinterpret_cast<float*>(b + o_po); w->part_ml = reinterpret_cast<float*>(b + o_pml);
-    w->meta = reinterpret_cast<char*>(b + o_meta);
-    w->skfrag = reinterpret_cast<float*>(b + o_skfrag);
-    w->skcnt = reinterpret_cast<int*>(b + o_skcnt);
+    w->xn = reinterpret_cast<bf16_t*>(b + m.xn); w->q = reinterpret_cast<bf16_t*>(b + m.q); w->attn = reinterpret_cast<bf16_t*>(b + m.attn);
+    w->act = reinterpret_cast<bf16_t*>(b + m.act); w->act_bytes = m.act_bytes;
+    w->x1 = reinterpret_cast<float*>(b + m.x1); w->xmid = reinterpret_cast<float*>(b + m.xmid);
+    w->part = reinterpret_cast<float*>(b + m.part); w->part_bytes = m.part_bytes;
+    w->part_o = reinterpret_cast<float*>(b + m.part_o); w->part_ml = reinterpret_cast<float*>(b + m.part_ml);
+    w->meta = reinterpret_cast<char*>(b + m.meta);
+    w->skfrag = reinterpret_cast<float*>(b + m.skfrag); w->skfrag_bytes = m.skfrag_bytes;
+    w->skcnt = reinterpret_cast<int*>(b + m.skcnt); w->skcnt_n = m.skcnt_n;
     return PS_OK;
 }
 
@@ -897,10 +914,11 @@ static ps_status step_impl(ps_ctx* c, const ps_seq* seqs, int32_t n_seqs, const 
     const int T = p.n_tokens, H = d.hidden, F = d.ffn, NQ = d.n_q_heads * d.head_dim, NQKV = qkv_cols(d);
     const MetaLayout ml = meta_layout(p, tio != nullptr);
     StepBufs W;
+    W.gemm = layer_gemm_options(c, p);
     if (use_static) {
         if ((st = carve_static(c, T, p.n_partial_slots, ml.total, &W)) != PS_OK) return st;
     } else {
-        if ((st = ensure_workspaces(c, T, p.n_partial_slots, tio ? p.n_seqs : 0)) != PS_OK) return st;
+        if ((st = ensure_workspaces(c, T, p.n_partial_slots, tio ? p.n_seqs : 0, W.gemm)) != PS_OK) return st;
         W.xn = c->ws_xn; W.q = c->ws_q; W.attn = c->ws_attn; W.act = c->ws_act; W.x1 = c->ws_x1; W.xmid = c->ws_xmid;
         W.part = c->ws_part; W.part_o = c->part_o; W.part_ml = c->part_ml; W.part_bytes = c->part_bytes; W.act_bytes = c->act_bytes;
         W.skfrag = c->ws_skfrag; W.skfrag_bytes = c->skfrag_bytes; W.skcnt = c->ws_skcnt; W.skcnt_n = c->skcnt_n;
@@ -1024,7 +1042,7 @@ static ps_status step_impl(ps_ctx* c, const ps_seq* seqs, int32_t n_seqs, const 
         // 1: QKV projection -> fp32 partials
         GemmArgs g{};
         g.A = W.xn; g.Wp = L.wqkv_t; g.M = T; g.N = NQKV; g.K = H; g.kind = GemmOut::PARTIAL_F32;
-        g.out = W.part; g.out_bytes = W.part_bytes; g.opt = gemm_options(c); g.opt.no_wreg = W.no_wreg;
+        g.out = W.part; g.out_bytes = W.part_bytes; g.opt = W.gemm;
         g.sk_frag = W.skfrag; g.sk_frag_bytes = W.skfrag_bytes; g.sk_counters = W.skcnt; g.sk_n_counters = W.skcnt_n;
         HIP_TRY(c, run_gemm(g, &n_splits, 0));
         if (stats) HIP_TRY(c, hipEventRecord(c->ev[++e], s));

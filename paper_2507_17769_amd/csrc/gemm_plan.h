@@ -21,7 +21,10 @@ struct GemmOptions {
     int split_k = 0;   // K splits (partial buffers)
     int tile = 0;      // M > 64: 0 = choose, 128 or 256 = block tile edge of the tiled kernel, which then serves the product
     int sk_mode = 0;   // tiled kernel: 0 = the cost model decides whether the tail's K loops are cut, 1 = never (whole tiles only), 2 = wherever possible
-    bool no_wreg = false;   // leave the weights-in-registers kernel out (a static step whose scratch its K splits would overflow)
+    bool no_wreg = false;   // leave the weights-in-registers kernel out
+    // The weights-in-registers kernel takes no more K splits than the kernel that it replaces would: the partial sums then need
+    // no more memory than without it.  Set for every step that a static step's scratch can hold, whichever call runs it.
+    bool cap_splits = false;
 };
 
 // ------------------------------------------------------------------------- weights in registers (gemm_wreg.hip)
@@ -120,11 +123,12 @@ inline double wreg_estimate(const WregPlan& g, int M, int N, int K, int cus) {
 }
 
 // The best plan of the weights-in-registers kernel, or an estimate of infinity where it does not serve the shape.
-inline double wreg_best(int M, int N, int K, int kind, int split_opt, int cus, WregPlan* best) {
+// At most max_splits K splits.
+inline double wreg_best(int M, int N, int K, int kind, int split_opt, int max_splits, int cus, WregPlan* best) {
     double best_us = std::numeric_limits<double>::infinity();
     const int tiles = (M + 15) / 16;
     const int s_lo = kind == GemmOut::SWIGLU_BF16 ? 1 : (split_opt > 0 ? std::min(split_opt, 8) : 1);
-    const int s_hi = kind == GemmOut::SWIGLU_BF16 ? 1 : (split_opt > 0 ? s_lo : 8);
+    const int s_hi = std::min(max_splits, kind == GemmOut::SWIGLU_BF16 ? 1 : (split_opt > 0 ? s_lo : 8));
     for (int rt = (tiles + WREG_MAX_TM - 1) / WREG_MAX_TM; rt <= (tiles + WREG_MIN_TM - 1) / WREG_MIN_TM; rt++) {
         const int tm = std::max(WREG_MIN_TM, (tiles + rt - 1) / rt);
         if (rt > 1 && tm * (rt - 1) >= tiles) continue;   // the last row block would be empty
@@ -154,20 +158,6 @@ inline GemmPlan plan_gemm(int M, int N, int K, int kind, const GemmOptions& o, i
     g.cut_tail = false;
     g.slots_per_xcd = 0;
     if (g.wstream) {
-        // Measured against streaming up to 160 tokens (us, streaming / weights in registers): gate/up of the 8B shape 41.9 /
-        // 42.6 at 80 tokens, 46.9 / 45.9 at 97, 53.4 / 49.1 at 144, 58.9 / 49.8 at 160; of the 70B shape, where streaming
-        // puts two blocks on a compute unit, 157 / 136 at 80 and 217 / 155 at 128; QKV 17.7 / 15.0 at 80; the O and down
-        // projections are no faster (11.5 / 12.4, 24.4 / 25.2 at 80, 14.4 / 14.4, 29.6 / 30.9 at 144).
-        const bool gate_up = kind == GemmOut::SWIGLU_BF16;
-        if (allow_wreg && ((gate_up && (M > 96 || N / 128 > cus)) || (!gate_up && N > K))) {
-            const double us = wreg_best(M, N, K, kind, split_opt, cus, &g.wreg_plan);
-            g.wreg = std::isfinite(us) && g.wreg_plan.row_tiles * g.wreg_plan.splits * (N / 64 / g.wreg_plan.nc) >= cus / 2;
-        }
-        if (g.wreg) {
-            g.wstream = false;
-            g.splits = g.wreg_plan.splits;
-            return g;
-        }
         const int groups = N / 64, KB = K / 32;
         int s = 1;
         if (kind != GemmOut::SWIGLU_BF16) {
@@ -180,6 +170,19 @@ inline GemmPlan plan_gemm(int M, int N, int K, int kind, const GemmOptions& o, i
         kps += kps & 1;  // whole stages of two k-blocks
         g.kb_per_split = kps;
         g.splits = (KB + kps - 1) / kps;
+        // Measured against streaming up to 160 tokens (us, streaming / weights in registers): gate/up of the 8B shape 41.9 /
+        // 42.6 at 80 tokens, 46.9 / 45.9 at 97, 53.4 / 49.1 at 144, 58.9 / 49.8 at 160; of the 70B shape, where streaming
+        // puts two blocks on a compute unit, 157 / 136 at 80 and 217 / 155 at 128; QKV 17.7 / 15.0 at 80; the O and down
+        // projections are no faster (11.5 / 12.4, 24.4 / 25.2 at 80, 14.4 / 14.4, 29.6 / 30.9 at 144).
+        const bool gate_up = kind == GemmOut::SWIGLU_BF16;
+        if (allow_wreg && ((gate_up && (M > 96 || N / 128 > cus)) || (!gate_up && N > K))) {
+            const double us = wreg_best(M, N, K, kind, split_opt, o.cap_splits ? g.splits : 8, cus, &g.wreg_plan);
+            g.wreg = std::isfinite(us) && g.wreg_plan.row_tiles * g.wreg_plan.splits * (N / 64 / g.wreg_plan.nc) >= cus / 2;
+        }
+        if (g.wreg) {
+            g.wstream = false;
+            g.splits = g.wreg_plan.splits;
+        }
     } else {
         // every combination of tile edge, K splits (none for the gate/up matrix, whose epilogue is not linear) and, for
         // one split, tail cutting; the smallest estimate wins
@@ -207,7 +210,7 @@ inline GemmPlan plan_gemm(int M, int N, int K, int kind, const GemmOptions& o, i
         // 1600; down 45.3 / 38.1, 52.3 / 39.3, 94.1 / 66.4; 70B shape at 264 tokens: gate/up 443 / 307, down 212 / 146.
         // The tiled kernel keeps what fills its 256x256 tiles: gate/up at 512 tokens 112 / 121, at 2048 444 / 460.
         WregPlan w;
-        if (allow_wreg && wreg_best(M, N, K, kind, split_opt, cus, &w) < (g.big_tile ? 1.12 : 1.17) * best) {
+        if (allow_wreg && wreg_best(M, N, K, kind, split_opt, o.cap_splits ? g.splits : 8, cus, &w) < (g.big_tile ? 1.12 : 1.17) * best) {
             g.wreg = true;
             g.wreg_plan = w;
             g.splits = w.splits;
@@ -226,14 +229,7 @@ inline size_t gemm_plan_out_bytes(int M, int N, int K, int kind, const GemmOptio
         const size_t rows = M <= 64 ? (size_t)((M + 15) / 16 * 16) : (size_t)((M + 255) / 256 * 256);
         return rows * (N / 2) * sizeof(uint16_t);
     }
-    // room for whichever kernel the options of a later call pick
-    GemmOptions other = o;
-    other.sk_mode = 0;
-    int splits = 0;
-    if (!o.no_wreg) splits = plan_gemm(M, N, K, kind, other, cus).splits;
-    other.no_wreg = true;
-    splits = std::max(splits, plan_gemm(M, N, K, kind, other, cus).splits);
-    return (size_t)splits * M * N * sizeof(float);
+    return (size_t)plan_gemm(M, N, K, kind, o, cus).splits * M * N * sizeof(float);
 }
 
 // What launch_gemm needs beside its output (both 0 unless the tiled kernel serves the product).
