@@ -135,11 +135,16 @@ const char* ps_last_error(const ps_ctx* ctx);
  * decodes, the other resident blocks streaming the decodes' KV; 0 = one per CU, more if the teams would
  * outlast the streams), "attn_prefill_weight" (what the planner charges a team for a pair of pages, in
  * units of 100 ns, when it decides whether more than one team per CU is needed; it only moves the cuts),
- * "gemm_split_k" (0 = automatic; the weight-streaming kernel's K splits), "gemm_whole_tiles" (1: the tiled GEMM kernel gives
+ * "gemm_split_k" (0 = automatic; N = the K splits, i.e. fp32 partial buffers, of every projection but gate/up where the
+ * kernel that serves it can be split that way: the weight-streaming one takes at most 8, the others 8 as well),
+ * "gemm_tile" (0 = automatic; 128 or 256 = block tile edge: steps of more than 64 tokens then use the tiled GEMM kernel for
+ * every projection, neither of the two others), "gemm_whole_tiles" (1: the tiled GEMM kernel gives
  * every tile to one block instead of cutting the K loops of a last, partial wave of tiles over all blocks; 2: it cuts
- * every such tail that can be cut, also where the cost model would not; same results up to fp32 summation order), "gemm_tile" (block tile edge of the tiled GEMM kernel, which
- * serves more than 64 tokens: 0 = automatic (the weight-streaming kernel stays in charge up to 96
- * tokens, up to 160 for all projections but the QKV one), 128 or 256), "out_f32" (1: ps_step writes x_out as fp32 [T][hidden],
+ * every such tail that can be cut, also where the cost model would not; a non-zero value also leaves the weights-in-registers
+ * GEMM kernel out; same results up to fp32 summation order), "gemm_wreg" (the weights-in-registers GEMM kernel, for more than
+ * 64 tokens: 0 = where the cost model prefers it, 1 = never, 10 R + C = always, with R = 5 .. 10 row tiles of 16 and C = 2 or 4
+ * column groups of 64 per block, for every projection whose input width is a multiple of 1024 / C times the K splits; goes
+ * before gemm_tile), "out_f32" (1: ps_step writes x_out as fp32 [T][hidden],
  * the precision the residual stream is kept in, instead of rounding it to bf16).
  * "only_layer" (l >= 0: ps_step runs layer l alone, x_in -> x_out, as if it were the whole model;
  * -1 = the whole stack.  A benchmark of a single layer loads several copies of it as layers and

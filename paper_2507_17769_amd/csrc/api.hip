@@ -93,6 +93,7 @@ struct ps_ctx {
     int opt_gemm_split_k = 0;
     int opt_gemm_tile = 0;
     int opt_gemm_whole_tiles = 0;
+    int opt_gemm_wreg = 0;
     bool opt_poison = false;
     int opt_only_layer = -1;
     bool opt_out_f32 = false;
@@ -340,6 +341,13 @@ extern "C" ps_status ps_set_option(ps_ctx* c, const char* name, int64_t value) {
     if (!strcmp(name, "gemm_whole_tiles")) {
         if (value < 0 || value > 2) return fail(c, PS_EINVAL, "gemm_whole_tiles must be 0, 1 or 2");
         c->opt_gemm_whole_tiles = (int)value;
+        return PS_OK;
+    }
+    if (!strcmp(name, "gemm_wreg")) {
+        const int64_t tm = value / 10, nc = value % 10;
+        if (value != 0 && value != 1 && (tm < WREG_MIN_TM || tm > WREG_MAX_TM || (nc != 2 && nc != 4)))
+            return fail(c, PS_EINVAL, "gemm_wreg must be 0, 1 or 10 * row tiles (5 .. 10) + column groups (2 or 4)");
+        c->opt_gemm_wreg = (int)value;
         return PS_OK;
     }
     if (!strcmp(name, "gemm_split_k")) {
@@ -667,6 +675,7 @@ static size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 static GemmOptions gemm_options(const ps_ctx* c) {
     GemmOptions o;
     o.split_k = c->opt_gemm_split_k; o.tile = c->opt_gemm_tile; o.sk_mode = c->opt_gemm_whole_tiles;
+    o.wreg = c->opt_gemm_wreg;
     return o;
 }
 // The output projection of the model writes one partial buffer: it is the logits.

@@ -21,7 +21,9 @@ struct GemmOptions {
     int split_k = 0;   // K splits (partial buffers)
     int tile = 0;      // M > 64: 0 = choose, 128 or 256 = block tile edge of the tiled kernel, which then serves the product
     int sk_mode = 0;   // tiled kernel: 0 = the cost model decides whether the tail's K loops are cut, 1 = never (whole tiles only), 2 = wherever possible
-    bool no_wreg = false;   // leave the weights-in-registers kernel out
+    // weights-in-registers kernel: 0 = the cost model decides, 1 = never, 10 tm + nc = with this block (and split_k K splits, or
+    // one) for more than 64 tokens, wherever K is a whole number of rounds of its shares
+    int wreg = 0;
     // The weights-in-registers kernel takes no more K splits than the kernel that it replaces would: the partial sums then need
     // no more memory than without it.  Set for every step that a static step's scratch can hold, whichever call runs it.
     bool cap_splits = false;
@@ -147,7 +149,7 @@ inline GemmPlan plan_gemm(int M, int N, int K, int kind, const GemmOptions& o, i
     const int split_opt = o.split_k, tile_opt = o.tile, sk_mode = o.sk_mode;
     GemmPlan g;
     g.wreg = false;
-    const bool allow_wreg = !o.no_wreg && M > 64 && tile_opt == 0 && sk_mode == 0;   // the options that name the tiled kernel get it
+    const bool allow_wreg = o.wreg == 0 && M > 64 && tile_opt == 0 && sk_mode == 0;   // the options that name the tiled kernel get it
     // measured: streaming wins up to 96 tokens for every projection, and up to 160 (ten row tiles) for all but the QKV-shaped
     // one (more columns than rows of weights: 48 blocks per split and six splits of partial sums; 129 tokens: 29 vs 24 us),
     // above all for the gate/up matrix (129 tokens: 61 vs 75 us) and the down projection (42 vs 46)
@@ -157,6 +159,17 @@ inline GemmPlan plan_gemm(int M, int N, int K, int kind, const GemmOptions& o, i
     g.kb_per_split = K / 32;
     g.cut_tail = false;
     g.slots_per_xcd = 0;
+    if (o.wreg > 1 && M > 64) {
+        const int tm = o.wreg / 10, splits = kind == GemmOut::SWIGLU_BF16 ? 1 : std::min(std::max(split_opt, 1), 8);
+        const WregPlan w{tm, o.wreg % 10, splits, ((M + 15) / 16 + tm - 1) / tm};
+        if (wreg_valid(w, M, N, K, kind)) {
+            g.wreg = true;
+            g.wreg_plan = w;
+            g.wstream = false;
+            g.splits = splits;
+            return g;
+        }
+    }
     if (g.wstream) {
         const int groups = N / 64, KB = K / 32;
         int s = 1;

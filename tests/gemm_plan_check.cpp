@@ -1,5 +1,6 @@
 // Checks of the GEMM planner (gemm_plan.h), compiled for the host by test_host_gemm_plan.py.  Walks the projections of
 // several model shapes over token counts and options and checks every plan against what the kernels and their buffers need.
+// With arguments (M N K kind wreg cap ...) it prints the plan of each: kernel, row tiles, column groups, K splits, row blocks.
 #include <cstdio>
 #include <cstdlib>
 
@@ -35,9 +36,13 @@ static void check(int M, const Shape& s, const GemmOptions& o, int cus) {
     }
     // what the buffers hold is what the plan writes
     if (s.kind == P) REQUIRE(gemm_plan_out_bytes(M, s.N, s.K, s.kind, o, cus) == (size_t)g.splits * M * s.N * 4);
-    if (o.cap_splits) {   // and no more than without the weights-in-registers kernel
+    const WregPlan forced{o.wreg / 10, o.wreg % 10, g.splits, g.wreg_plan.row_tiles};
+    REQUIRE(o.wreg != 1 || !g.wreg);
+    if (o.wreg > 1 && M > 64 && (s.K / 32) % (8 / forced.nc * WREG_STAGES * std::max(1, s.kind == G ? 1 : std::min(o.split_k, 8))) == 0)
+        REQUIRE(g.wreg && g.wreg_plan.tm == forced.tm && g.wreg_plan.nc == forced.nc);
+    if (o.cap_splits && o.wreg == 0) {   // and no more than without the weights-in-registers kernel
         GemmOptions without = o;
-        without.no_wreg = true;
+        without.wreg = 1;
         size_t frag, frag_w;
         int cnt, cnt_w;
         gemm_plan_workspace(M, s.N, s.K, s.kind, o, cus, &frag, &cnt);
@@ -48,7 +53,16 @@ static void check(int M, const Shape& s, const GemmOptions& o, int cus) {
     n_checked++;
 }
 
-int main() {
+int main(int argc, char** argv) {
+    for (int i = 1; i + 5 < argc; i += 6) {
+        GemmOptions o;
+        o.wreg = atoi(argv[i + 4]);
+        o.cap_splits = atoi(argv[i + 5]) != 0;
+        const GemmPlan g = plan_gemm(atoi(argv[i]), atoi(argv[i + 1]), atoi(argv[i + 2]), atoi(argv[i + 3]), o, 256);
+        if (g.wreg) printf("wreg %d %d %d %d\n", g.wreg_plan.tm, g.wreg_plan.nc, g.splits, g.wreg_plan.row_tiles);
+        else printf("%s 0 0 %d 0\n", g.wstream ? "wstream" : "tiled", g.splits);
+    }
+    if (argc > 1) return 0;
     for (int cus : {256, 304, 64})
         for (const Shape& s : shapes)
             for (int M = 1; M < 9000; M += M < 720 ? 1 : 41)
@@ -58,6 +72,11 @@ int main() {
                         o.split_k = split;
                         o.cap_splits = cap;
                         check(M, s, o, cus);
+                        if (M > 700) continue;
+                        for (int wreg : {1, 52, 54, 72, 104}) {
+                            o.wreg = wreg;
+                            check(M, s, o, cus);
+                        }
                     }
     printf("OK %d\n", n_checked);
     return 0;

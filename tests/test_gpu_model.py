@@ -170,3 +170,27 @@ def test_model_step_state_and_range_errors():
     out = eng.step_tokens(b.seqs, [5], want_parts=True)
     assert len(out["parts_ms"]) == 3 and all(x >= 0 for x in out["parts_ms"])
     eng.close()
+
+
+@pytest.mark.parametrize("wreg", [52, 54, 102])
+def test_model_step_with_the_head_by_the_weights_in_registers_gemm(wreg):
+    # 81 decode sequences: two row blocks of five row tiles or one of ten; the vocabulary has five groups of 64 columns
+    m = dict(hidden=1024, n_q=16, n_kv=2, head_dim=64, ffn=512, rope_base=10000.0, n_layers=1)
+    b = W.custom_batch("tiny", 33, 0, 0, [5, 33, 64] * 27, name="head")
+    W.MODELS["_h"] = m
+    b.model = "_h"
+    try:
+        m, layers, head, eng, pool = _setup(m, b, 1, 320)
+        eng.ctx.set_option("gemm_wreg", wreg)
+        ids = W.token_ids(320, b.n_tokens, 7)
+        out = eng.step_tokens(b.seqs, ids, want_hidden=True)
+        eng.ctx.sync()
+        got_logits = out["logits"].cpu().numpy()
+        _, want_logits, want_hidden = orun.run_model(m, head, layers, b.seqs, ids, copy.deepcopy(pool), np.float32)
+        _, want_logits_b, _ = orun.run_model(m, head, layers, b.seqs, ids, copy.deepcopy(pool), np.float32, bf16_activations=True)
+        assert rel_err(out["hidden"].cpu().numpy(), want_hidden) <= TOL
+        assert rel_err(got_logits, want_logits) <= TOL and row_score(got_logits, want_logits_b, TOL, 0.0) <= 1.0
+        _check_tokens(out["next"].cpu().numpy(), got_logits, want_logits, f"wreg={wreg}")
+        eng.close()
+    finally:
+        del W.MODELS["_h"]

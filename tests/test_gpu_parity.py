@@ -346,9 +346,9 @@ def test_tiled_gemm_tile_sizes_and_k_splits(tile, split, tails):
 
 @pytest.mark.parametrize("tokens", [65, 97, 113, 129, 161, 209, 257, 289, 321])
 def test_weights_in_registers_gemm_row_blocks(tokens):
-    # a shape whose projections reach the weights-in-registers GEMM from 65 tokens on; the token counts leave one row in the
-    # last 16-row tile (or end in a row block's last tile) for every number of row tiles per block from five to ten, with one, two
-    # and more row blocks, two and four column groups
+    # a shape whose QKV or gate/up projection reaches the weights-in-registers GEMM by the automatic choice; the token counts
+    # leave one row in the last 16-row tile.  test_host_gemm_plan.py asserts that the kernel is chosen; every block shape is
+    # tested below
     W.MODELS["_r"] = dict(hidden=2048, n_q=16, n_kv=8, head_dim=128, ffn=12288, rope_base=500000.0, n_layers=1)
     try:
         c = Case(W.custom_batch("_r", 29, tokens - 5, 40, [1, 16, 17, 90, 200], name="row blocks"))
@@ -358,6 +358,33 @@ def test_weights_in_registers_gemm_row_blocks(tokens):
         c.close()
     finally:
         del W.MODELS["_r"]
+
+
+def _wreg_case(model, tokens, options):
+    W.MODELS["_b"] = model
+    try:
+        c = Case(W.custom_batch("_b", 31, tokens - 4, 24, [1, 16, 17, 90], name="block"), options=dict(options, poison_workspaces=1))
+        errs = c.run()
+        _assert_errs(errs, f"T={tokens} {options}")
+        c.check_pool()
+        c.close()
+    finally:
+        del W.MODELS["_b"]
+
+
+@pytest.mark.parametrize("nc", [2, 4])
+@pytest.mark.parametrize("tm", [5, 6, 7, 8, 9, 10])
+def test_weights_in_registers_gemm_every_block(tm, nc):
+    # every block shape for all four projections: one row block (weights streamed past the caches), whose last tile has one
+    # row, and three row blocks that share the weights, with one and two K splits.  QKV's 18 column groups leave two of a
+    # block's four without work.  The small shape adds a last block with one group of two or four (three groups of QKV) and
+    # two of four (42 of gate/up); its O and down projections are not divisible and stay with the other kernels.
+    model = dict(hidden=1024, n_q=16, n_kv=1, head_dim=64, ffn=2048, rope_base=10000.0, n_layers=1)
+    _wreg_case(model, 16 * tm - 15, {"gemm_wreg": 10 * tm + nc})
+    for split in (1, 2):
+        _wreg_case(model, 32 * tm + 1, {"gemm_wreg": 10 * tm + nc, "gemm_split_k": split})
+    small = dict(hidden=1024, n_q=1, n_kv=1, head_dim=64, ffn=1344, rope_base=10000.0, n_layers=1)
+    _wreg_case(small, 16 * tm + 1, {"gemm_wreg": 10 * tm + nc})
 
 
 @pytest.mark.parametrize("chunk,splits", [(0, [1, 2, 8]), (0, [9, 16, 17]), (40, [2, 64, 65]), (40, [128, 129, 257])])

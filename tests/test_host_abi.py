@@ -216,3 +216,15 @@ def test_attention_plan_covers_everything_once():
         assert (len(team) > 0) == (cfg == 2)
         for w in (team, wave):
             assert len(w) == 0 or w.max() - w.min() <= 2, (len(w), w.min(), w.max())
+
+
+def test_gemm_wreg_option_takes_its_documented_values_only():
+    m = W.MODELS["tiny"]
+    c = B.Context(m["hidden"], m["n_q"], m["n_kv"], m["head_dim"], m["ffn"], host_only=True)
+    for v in (0, 1, 52, 54, 102, 104):
+        c.set_option("gemm_wreg", v)
+    for v in (-1, 2, 42, 53, 55, 112, 1024, 1 << 40):
+        with pytest.raises(B.PolystepError) as e:
+            c.set_option("gemm_wreg", v)
+        assert e.value.status == B.PS_EINVAL
+    c.destroy()

@@ -1,19 +1,53 @@
 """The GEMM planner (paper_2507_17769_amd/csrc/gemm_plan.h) checked on the host: every plan over a grid of shapes, token counts
-and options is one its kernel accepts, and a capped plan needs no more memory than the kernels without weights in registers."""
+and options is one its kernel accepts, a capped plan needs no more memory than the kernels without weights in registers, and the
+GPU tests that mean to run the weights-in-registers kernel do so."""
 import os
 import subprocess
-import tempfile
+
+import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PARTIAL, SWIGLU = 0, 1
 
 
-def test_every_plan_is_valid_and_capped_plans_stay_within_the_other_kernels_memory():
-    with tempfile.TemporaryDirectory() as tmp:
-        exe = os.path.join(tmp, "gemm_plan_check")
-        cmd = ["g++", "-O2", "-std=c++17", "-D__host__=", "-D__device__=", "-I", os.path.join(ROOT, "paper_2507_17769_amd", "csrc"),
-               os.path.join(ROOT, "tests", "gemm_plan_check.cpp"), "-o", exe]
-        r = subprocess.run(cmd, capture_output=True, text=True)
-        assert r.returncode == 0, r.stderr
-        r = subprocess.run([exe], capture_output=True, text=True)
-        assert r.returncode == 0 and r.stdout.startswith("OK "), r.stdout + r.stderr
-        assert int(r.stdout.split()[1]) > 100000
+@pytest.fixture(scope="module")
+def planner(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("plan") / "gemm_plan_check")
+    cmd = ["g++", "-O2", "-std=c++17", "-D__host__=", "-D__device__=", "-I", os.path.join(ROOT, "paper_2507_17769_amd", "csrc"),
+           os.path.join(ROOT, "tests", "gemm_plan_check.cpp"), "-o", exe]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return exe
+
+
+def _plans(planner, queries):
+    """[(M, N, K, kind, wreg option, capped)] -> [(kernel, row tiles, column groups, K splits, row blocks)] on 256 compute units."""
+    r = subprocess.run([planner] + [str(int(x)) for q in queries for x in q], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return [(l.split()[0], *map(int, l.split()[1:])) for l in r.stdout.splitlines()]
+
+
+def test_every_plan_is_valid_and_capped_plans_stay_within_the_other_kernels_memory(planner):
+    r = subprocess.run([planner], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.startswith("OK "), r.stdout + r.stderr
+    assert int(r.stdout.split()[1]) > 100000
+
+
+def test_gpu_tests_of_the_weights_in_registers_gemm_reach_it(planner):
+    # test_weights_in_registers_gemm_row_blocks: by the automatic choice, QKV at all of its token counts, gate/up at most
+    tokens = [65, 97, 113, 129, 161, 209, 257, 289, 321]
+    assert all(p[0] == "wreg" for p in _plans(planner, [(T, 4096, 2048, PARTIAL, 0, 1) for T in tokens]))
+    assert all(p[0] == "wreg" for p in _plans(planner, [(T, 24576, 2048, SWIGLU, 0, 1) for T in tokens[1:-1]]))
+    # test_weights_in_registers_gemm_every_block: all four projections, any block, one row block and three
+    for tm in range(5, 11):
+        for nc in (2, 4):
+            for N, K, kind in ((1152, 1024, PARTIAL), (1024, 1024, PARTIAL), (4096, 1024, SWIGLU), (1024, 2048, PARTIAL)):
+                assert _plans(planner, [(T, N, K, kind, 10 * tm + nc, 1) for T in (16 * tm - 15, 32 * tm + 1)]) == \
+                    [("wreg", tm, nc, 1, 1), ("wreg", tm, nc, 1, 3)]
+            # ... and its partly filled blocks: three column groups of QKV, 42 of gate/up
+            for N, kind in ((192, PARTIAL), (2688, SWIGLU)):
+                assert _plans(planner, [(16 * tm + 1, N, 1024, kind, 10 * tm + nc, 1)]) == [("wreg", tm, nc, 1, 2)]
+    # test_static_step_8b_layer_runs_the_kernels_of_ps_step_also_where_scratch_is_short
+    free, capped = _plans(planner, [(294, 4096, 14336, PARTIAL, 0, cap) for cap in (0, 1)])
+    assert free[0] == capped[0] == "wreg" and capped[3] < free[3]
+    assert _plans(planner, [(97, 28672, 4096, SWIGLU, 0, 1)])[0][0] == "wreg"
