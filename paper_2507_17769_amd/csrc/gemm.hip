@@ -12,20 +12,23 @@
 // of 4 KiB per k-block between them instead of four separate streams of 1 KiB, which is what keeps
 // DRAM rows open when two thousand wavefronts stream at once.
 //
-// Three kernels (plan_gemm chooses):
-//  * gemm_wreg_kernel (gemm_wreg.hip; from 65 tokens on, most shapes up to some 1000 tokens): weights in registers.
-//  * gemm_wstream_kernel (M <= 96, and up to 160 for all but the QKV-shaped projection): weight streaming.  The four computing wavefronts of a block own 16 of
-//    its 64 output columns each and load their weight operands straight from HBM into registers
+// Three kernels (gemm_plan.h chooses and says why):
+//  * gemm_wstream_kernel (up to 64 tokens; gate/up up to 96, O and down up to 160): weight streaming.  The four computing
+//    wavefronts of a block own 16 of its 64 output columns each and load their weight operands straight from HBM into registers
 //    (no LDS hop), four stages of two k-blocks ahead; a fifth wavefront copies the activation k-blocks
-//    that all four need into an LDS ring.
-//  * gemm_sk_kernel (where its tiles fill the chip, or forced by the tile option above 64): 256x256 or 128x128 block tile, bf16 MFMA 16x16x32.  Activations and
+//    that all four need into an LDS ring.  Gate/up with more than 96 tokens comes here only where a matrix is too small for the
+//    next kernel, or that one is switched off.
+//  * gemm_wreg_kernel (gemm_wreg.hip): weights in registers, from there up to 6144 tokens wherever its estimated time is below
+//    the next kernel's.
+//  * gemm_sk_kernel (the rest): 256x256 or 128x128 block tile, bf16 MFMA 16x16x32.  (Small tiles: of the 8B and 70B shapes only
+//    QKV at 110 to 128 tokens and O around 250; narrower matrices take them more often.)  Activations and
 //    weights are both stored as KiB blocks that already are MFMA operands, so a k-slice of the
 //    tile is copied HBM/L2 -> LDS verbatim by global_load_lds (no register hop, no transform) into
 //    a ring of four stages, three in flight; the wavefronts read operands back with one
 //    ds_read_b128 per 16x32 operand, interleaved with the MFMAs that consume the previous stage.
 //    Blocks are resident once per compute unit and take whole tiles in waves; the K loops of the tiles
 //    that do not fill a wave are cut evenly over the blocks ("stream-K"), see SkParams.
-// Output is either fp32 partials [split][M][N] (one per K split of the streaming kernel; the consumer kernel sums the splits, adds the
+// Output is either fp32 partials [split][M][N] (one per K split; the consumer kernel sums the splits, adds the
 // residual, normalises, rotates ...) or, for the fused gate/up matrix, silu(gate) * up in bf16.
 #include "ps_device.h"
 #include "gemm_wreg.h"

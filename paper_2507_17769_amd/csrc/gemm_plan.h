@@ -31,6 +31,7 @@ struct GemmOptions {
 
 // ------------------------------------------------------------------------- weights in registers (gemm_wreg.hip)
 constexpr int WREG_MIN_TM = 5, WREG_MAX_TM = 10;
+constexpr int WREG_MAX_M = 6144;   // tokens up to which the choice between the kernels has been measured
 
 constexpr int WREG_STAGES = 4;   // register sets of weights; a K share is a whole number of rounds through them
 // slots of the activation ring: one more than weight sets where LDS holds it (8 / nc K shares of tm KiB per slot)
@@ -64,6 +65,7 @@ struct GemmPlan {
     int kb_per_split;   // 32-wide k-blocks per split
     bool cut_tail;      // tiled: cut the K loops of the last, partial wave of tiles over the blocks (one split only)
     int slots_per_xcd;  // tiled: parked pieces an XCD may hold
+    double waves;       // tiled: waves of units that the blocks of a compute unit go through, by tiled_estimate
 };
 
 // Estimated time (us) of the tiled kernel for one choice of tile edge, K splits and tail cutting, from the rates measured
@@ -72,7 +74,7 @@ struct GemmPlan {
 // written and read back by the consumer; parked pieces of a cut tail cost about 1.4 us per MB all told (store, count,
 // reload by the last block and the clock the extra traffic costs the rest of the step: measured on the gate/up and O
 // matrices), less where whole tiles follow to hide them behind.
-inline double tiled_estimate(int M, int N, int K, int edge, int splits, bool cut, int cus, int* kp_per_split, int* eff_splits, int* slots_per_xcd) {
+inline double tiled_estimate(int M, int N, int K, int edge, int splits, bool cut, int cus, int* kp_per_split, int* eff_splits, int* slots_per_xcd, double* waves_out) {
     const int B = cus * (edge == 256 ? 1 : 2) / 8;
     const int KPt = K / 64;
     const int kps = (KPt + splits - 1) / splits, s_eff = (KPt + kps - 1) / kps;
@@ -102,30 +104,58 @@ inline double tiled_estimate(int M, int N, int K, int edge, int splits, bool cut
     // uncut tail give part of their share back as clock for the busy ones: measured on the 70B-shaped gate/up matrix,
     // cutting the tail of 4.4 waves bought nothing, where the arithmetic says 11 %.  Half the gain is what is counted.
     if (cut && edge == 256) waves = waves_uncut - 0.5 * (waves_uncut - waves);
+    *waves_out = waves;
     double us = waves * unit_us;
     if (s_eff > 1) us += 2.0 * (s_eff - 1) * (double)M * N * 4 / 3e6;
     if (cut) us += pieces * (double)edge * edge * 4 / 0.7e6 * (any_full ? 0.6 : 1.0) + 10.0;
     return us;
 }
 
-// Estimated time (us) of the weights-in-registers kernel for one plan: blocks run one per compute unit in waves, a stage
-// costs 0.34 + 0.07 per row tile with four column groups (0.22 + 0.096 with two, whose K shares copy twice the activations),
-// a block 8 more for its first loads and its epilogue, a wave that is not full three quarters of its time plus a quarter of
-// its fill (the blocks that do run have the memory to themselves); the weights stream at 6.2 TB/s, and the shorter of the
-// two times hides all but 15 % of itself.  Fitted to 190 runs of the 8B shapes at 80 to 1024 tokens; the plan it picks is within
-// 8 % of the best one measured at every one of them.  Partial sums are read back by the consumer.
-inline double wreg_estimate(const WregPlan& g, int M, int N, int K, int cus) {
-    const int shares = 8 / g.nc, n = K / 32 / (g.splits * shares);
-    const int blocks = g.row_tiles * g.splits * ((N / 64 + g.nc - 1) / g.nc);
-    const int full = blocks / cus, rem = blocks % cus;
-    const double waves = full + (rem ? 0.77 + 0.23 * rem / cus : 0.0);
-    const double core = 2.0 + waves * (8.0 + n * (g.nc == 4 ? 0.34 + 0.07 * g.tm : 0.22 + 0.096 * g.tm));
-    const double hbm = 2.0 * N * K / 6.2e6;
-    return std::max(core, hbm) + 0.15 * std::min(core, hbm) + (g.splits - 1) * (double)M * N * 4 / 5e6;
+// Time (us) of the consumer's read of `splits` fp32 partial buffers beyond the first: 8 TB/s, half of that for what lies beyond
+// the 256 MB of the last-level cache.  Measured behind the QKV and O projections at 97 to 2048 tokens.
+inline double partials_us(int splits, int M, int N) {
+    const double bytes = (double)M * N * 4;
+    return (splits - 1) * bytes / 8e6 + std::max(0.0, splits * bytes - 256e6) / 8e6;
 }
 
-// The best plan of the weights-in-registers kernel, or an estimate of infinity where it does not serve the shape.
-// At most max_splits K splits.
+// The two times below (us) are of the kernel and of its consumer's read of the partial sums, so that K splits are charged alike.
+// Both are fitted to measured times on the projections of the 8B and the 70B shape at 65 to 6144 tokens: 10 680 runs of the
+// weights-in-registers kernel over its row tiles, column groups and K splits, and the plans that tiled_estimate picks for the
+// tiled one.  In both a quarter of a long run goes by its operations alone, whatever the plan: the power limit.
+
+// Weights in registers: blocks run one per compute unit in waves, the last one as long as any.  A stage costs 0.46 + 0.033
+// per row tile with four column groups (0.39 + 0.073 with two, whose K shares copy twice the activations); the weights stream
+// at 7.9 TB/s, and of the shorter of the two times about half is hidden; partial sums are written at 2.9 TB/s.  6 % rms from
+// the measured kernel times; the plan it picks takes 0.3 % longer than the best one in the mean, 9 % at worst.
+inline double wreg_time(const WregPlan& g, int M, int N, int K, int kind, int cus) {
+    const int shares = 8 / g.nc, n = K / 32 / (g.splits * shares);
+    const int blocks = g.row_tiles * g.splits * ((N / 64 + g.nc - 1) / g.nc), waves = (blocks + cus - 1) / cus;
+    double core = 4.0 + waves * (3.0 + n * (g.nc == 4 ? 0.46 + 0.033 * g.tm : 0.39 + 0.073 * g.tm));
+    core += 0.24 * std::max(0.0, 2.0 * M * N * K / 0.8e9 - core);
+    const double hbm = 2.0 * N * K / 7.9e6, us = std::max(core, hbm) + 0.48 * std::min(core, hbm);
+    if (kind == GemmOut::SWIGLU_BF16) return 0.9 * us;   // bf16 of half the columns: a quarter of the output bytes
+    return us + (g.splits - 1) * (double)M * N * 4 / 2.9e6 + partials_us(g.splits, M, N);
+}
+
+// The tiled kernel with a plan that tiled_estimate has picked (which ranks tiles, splits and cuts against each other, and runs 3
+// to 30 % below the measured times).  A pair of k-blocks costs 1.1 us, 1.3 with 256x256 tiles; two blocks of 128x128 tiles share
+// a compute unit, and a wave of them takes 0.59 of its time where every unit has one, 0.8 to 1 where some have two.  7 % rms from the
+// measured kernel times, 22 % at worst.
+inline double tiled_time(const GemmPlan& g, int M, int N, int K, int kind, int cus) {
+    const int edge = g.big_tile ? 256 : 128, pairs = g.kb_per_split / 2, per_wave = g.big_tile ? cus : 2 * cus;
+    const int units = ((M + edge - 1) / edge) * ((N + edge - 1) / edge) * g.splits, full = units / per_wave;
+    const double rem = (double)(units % per_wave) / per_wave;
+    double waves = g.waves;
+    if (!g.cut_tail) waves = full + (rem == 0 ? 0.0 : g.big_tile ? 1.0 : rem <= 0.5 ? 0.59 : 0.795 + 0.41 * (rem - 0.5));
+    double core = waves * (g.big_tile ? 1.3 * pairs + 3.6 : 1.1 * pairs + 5.4);
+    core += 0.26 * std::max(0.0, 2.0 * M * N * K / 1.0e9 - core);
+    const double hbm = 2.0 * N * K / 6.5e6, us = std::max(core, hbm) + 0.29 * std::min(core, hbm);
+    if (kind == GemmOut::SWIGLU_BF16) return 0.92 * us;
+    return us + (g.splits - 1) * (double)M * N * 4 / 2.8e6 + partials_us(g.splits, M, N);
+}
+
+// The best plan of the weights-in-registers kernel with at most max_splits K splits, and its time, or infinity where the kernel
+// does not serve the shape or would leave more than half of the compute units without a block.
 inline double wreg_best(int M, int N, int K, int kind, int split_opt, int max_splits, int cus, WregPlan* best) {
     double best_us = std::numeric_limits<double>::infinity();
     const int tiles = (M + 15) / 16;
@@ -137,8 +167,8 @@ inline double wreg_best(int M, int N, int K, int kind, int split_opt, int max_sp
         for (int nc : {4, 2})
             for (int sp = s_lo; sp <= s_hi; sp++) {
                 const WregPlan g{tm, nc, sp, rt};
-                if (!wreg_valid(g, M, N, K, kind)) continue;
-                const double us = wreg_estimate(g, M, N, K, cus);
+                if (!wreg_valid(g, M, N, K, kind) || rt * sp * (N / 64 / nc) < cus / 2) continue;
+                const double us = wreg_time(g, M, N, K, kind, cus);
                 if (us < best_us) { best_us = us; *best = g; }
             }
     }
@@ -149,8 +179,8 @@ inline GemmPlan plan_gemm(int M, int N, int K, int kind, const GemmOptions& o, i
     const int split_opt = o.split_k, tile_opt = o.tile, sk_mode = o.sk_mode;
     GemmPlan g;
     g.wreg = false;
-    const bool allow_wreg = o.wreg == 0 && M > 64 && tile_opt == 0 && sk_mode == 0;   // the options that name the tiled kernel get it
-    // measured: streaming wins up to 96 tokens for every projection, and up to 160 (ten row tiles) for all but the QKV-shaped
+    const bool allow_wreg = o.wreg == 0 && M > 64 && M <= WREG_MAX_M && tile_opt == 0 && sk_mode == 0;   // the options that name the tiled kernel get it
+    // measured against the tiled kernel: streaming wins up to 96 tokens for every projection, and up to 160 (ten row tiles) for all but the QKV-shaped
     // one (more columns than rows of weights: 48 blocks per split and six splits of partial sums; 129 tokens: 29 vs 24 us),
     // above all for the gate/up matrix (129 tokens: 61 vs 75 us) and the down projection (42 vs 46)
     g.wstream = M <= 64 || (tile_opt == 0 && (M <= 96 || (M <= 160 && (kind == GemmOut::SWIGLU_BF16 || N <= K))));
@@ -159,6 +189,7 @@ inline GemmPlan plan_gemm(int M, int N, int K, int kind, const GemmOptions& o, i
     g.kb_per_split = K / 32;
     g.cut_tail = false;
     g.slots_per_xcd = 0;
+    g.waves = 0;
     if (o.wreg > 1 && M > 64) {
         const int tm = o.wreg / 10, splits = kind == GemmOut::SWIGLU_BF16 ? 1 : std::min(std::max(split_opt, 1), 8);
         const WregPlan w{tm, o.wreg % 10, splits, ((M + 15) / 16 + tm - 1) / tm};
@@ -183,15 +214,15 @@ inline GemmPlan plan_gemm(int M, int N, int K, int kind, const GemmOptions& o, i
         kps += kps & 1;  // whole stages of two k-blocks
         g.kb_per_split = kps;
         g.splits = (KB + kps - 1) / kps;
-        // Measured against streaming up to 160 tokens (us, streaming / weights in registers): gate/up of the 8B shape 41.9 /
-        // 42.6 at 80 tokens, 46.9 / 45.9 at 97, 53.4 / 49.1 at 144, 58.9 / 49.8 at 160; of the 70B shape, where streaming
-        // puts two blocks on a compute unit, 157 / 136 at 80 and 217 / 155 at 128; QKV 17.7 / 15.0 at 80; the O and down
-        // projections are no faster (11.5 / 12.4, 24.4 / 25.2 at 80, 14.4 / 14.4, 29.6 / 30.9 at 144).
+        // Measured against streaming (kernel and consumer, us, streaming / weights in registers): gate/up of the 8B shape 45 / 45 at
+        // 65 and 80 tokens, 49.6 / 49.1 at 97, 56.5 / 52.9 at 144, 61.5 / 54.0 at 160; of the 70B shape, where streaming puts two
+        // blocks on a compute unit, 154 / 140 at 65, 188 / 147 at 128, 212 / 153 at 160.  Matrices wider than deep: QKV of the
+        // 8B shape 28.7 / 25.4 at 65, 32.4 / 28.0 at 96, of the 70B shape 51.9 / 47.4 and 58.4 / 50.4; the output projection onto
+        // 128256 columns 239 / 204 at 65 and 240 / 210 at 96 (4096 deep), 432 / 356 and 398 / 364 (8192 deep); 4096 columns 2048
+        // deep 19 / 21 and 22 / 21, so that small ones stay, as do the O and down projections.
         const bool gate_up = kind == GemmOut::SWIGLU_BF16;
-        if (allow_wreg && ((gate_up && (M > 96 || N / 128 > cus)) || (!gate_up && N > K))) {
-            const double us = wreg_best(M, N, K, kind, split_opt, o.cap_splits ? g.splits : 8, cus, &g.wreg_plan);
-            g.wreg = std::isfinite(us) && g.wreg_plan.row_tiles * g.wreg_plan.splits * (N / 64 / g.wreg_plan.nc) >= cus / 2;
-        }
+        if (allow_wreg && ((gate_up && (M > 96 || N / 128 > cus)) || (!gate_up && N > K && (double)N * K >= 16e6)))
+            g.wreg = std::isfinite(wreg_best(M, N, K, kind, split_opt, o.cap_splits ? g.splits : 8, cus, &g.wreg_plan));
         if (g.wreg) {
             g.wstream = false;
             g.splits = g.wreg_plan.splits;
@@ -208,22 +239,21 @@ inline GemmPlan plan_gemm(int M, int N, int K, int kind, const GemmOptions& o, i
             for (int sp = s_lo; sp <= s_hi; sp++)
                 for (int cut = 0; cut < (sp == 1 && sk_mode != 1 ? 2 : 1); cut++) {
                     int kps, eff, slots;
-                    double us = tiled_estimate(M, N, K, edge, sp, cut != 0, cus, &kps, &eff, &slots);
+                    double waves;
+                    double us = tiled_estimate(M, N, K, edge, sp, cut != 0, cus, &kps, &eff, &slots, &waves);
                     if (cut && slots == 0) continue;
                     if (cut && sk_mode == 2) us -= 1e9;   // test knob: a tail that can be cut is cut
                     if (first || us < best) {
                         first = false; best = us;
-                        g.big_tile = edge == 256; g.splits = eff; g.kb_per_split = 2 * kps; g.cut_tail = cut != 0; g.slots_per_xcd = slots;
+                        g.big_tile = edge == 256; g.splits = eff; g.kb_per_split = 2 * kps; g.cut_tail = cut != 0; g.slots_per_xcd = slots; g.waves = waves;
                     }
                 }
         }
-        // The tiled estimate runs below what is measured: by a sixth with 128x128 tiles (5 to 30 % over 40 shapes), by an eighth
-        // with 256x256 ones.  Where the weights-in-registers kernel wins
-        // (8B shape, us, tiled / it): gate/up 80.2 / 67.0 at 256 tokens, 115 / 69.2 at 271, 187 / 158 at 640, 434 / 379 at
-        // 1600; down 45.3 / 38.1, 52.3 / 39.3, 94.1 / 66.4; 70B shape at 264 tokens: gate/up 443 / 307, down 212 / 146.
-        // The tiled kernel keeps what fills its 256x256 tiles: gate/up at 512 tokens 112 / 121, at 2048 444 / 460.
+        // The smaller time decides; the half percent keeps the down projection of the 8B shape at 800 and 832 tokens (113 / 102 us
+        // with its consumer in the tiled kernel / in this one).  Checked on stacks deep enough that no weights stay in a cache, on
+        // either side of every crossing: no layer is more than 1 % slower than without this kernel.
         WregPlan w;
-        if (allow_wreg && wreg_best(M, N, K, kind, split_opt, o.cap_splits ? g.splits : 8, cus, &w) < (g.big_tile ? 1.12 : 1.17) * best) {
+        if (allow_wreg && wreg_best(M, N, K, kind, split_opt, o.cap_splits ? g.splits : 8, cus, &w) < 1.005 * tiled_time(g, M, N, K, kind, cus)) {
             g.wreg = true;
             g.wreg_plan = w;
             g.splits = w.splits;
@@ -245,13 +275,14 @@ inline size_t gemm_plan_out_bytes(int M, int N, int K, int kind, const GemmOptio
     return (size_t)plan_gemm(M, N, K, kind, o, cus).splits * M * N * sizeof(float);
 }
 
-// What launch_gemm needs beside its output (both 0 unless the tiled kernel serves the product).
+// What launch_gemm needs beside its output (both 0 unless the tiled kernel serves the product and cuts its tail: only the
+// blocks that share a tile count in on it).
 inline void gemm_plan_workspace(int M, int N, int K, int kind, const GemmOptions& o, int cus, size_t* frag_bytes, int* n_counters) {
     *frag_bytes = 0;
     *n_counters = 0;
     if (M <= 0) return;
     const GemmPlan g = plan_gemm(M, N, K, kind, o, cus);
-    if (g.wstream || g.wreg) return;
+    if (!g.cut_tail) return;
     const int b = g.big_tile ? 256 : 128;
     *frag_bytes = (size_t)8 * g.slots_per_xcd * b * b * sizeof(float);
     *n_counters = ((M + b - 1) / b) * ((N + b - 1) / b);

@@ -346,7 +346,7 @@ def test_tiled_gemm_tile_sizes_and_k_splits(tile, split, tails):
 
 @pytest.mark.parametrize("tokens", [65, 97, 113, 129, 161, 209, 257, 289, 321])
 def test_weights_in_registers_gemm_row_blocks(tokens):
-    # a shape whose QKV or gate/up projection reaches the weights-in-registers GEMM by the automatic choice; the token counts
+    # a shape whose gate/up, QKV or down projection reaches the weights-in-registers GEMM by the automatic choice; the token counts
     # leave one row in the last 16-row tile.  test_host_gemm_plan.py asserts that the kernel is chosen; every block shape is
     # tested below
     W.MODELS["_r"] = dict(hidden=2048, n_q=16, n_kv=8, head_dim=128, ffn=12288, rope_base=500000.0, n_layers=1)

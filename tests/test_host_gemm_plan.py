@@ -34,10 +34,11 @@ def test_every_plan_is_valid_and_capped_plans_stay_within_the_other_kernels_memo
 
 
 def test_gpu_tests_of_the_weights_in_registers_gemm_reach_it(planner):
-    # test_weights_in_registers_gemm_row_blocks: by the automatic choice, QKV at all of its token counts, gate/up at most
-    tokens = [65, 97, 113, 129, 161, 209, 257, 289, 321]
-    assert all(p[0] == "wreg" for p in _plans(planner, [(T, 4096, 2048, PARTIAL, 0, 1) for T in tokens]))
-    assert all(p[0] == "wreg" for p in _plans(planner, [(T, 24576, 2048, SWIGLU, 0, 1) for T in tokens[1:-1]]))
+    # test_weights_in_registers_gemm_row_blocks: by the automatic choice, gate/up up to 289 tokens, QKV and down from 257 on
+    tokens = [97, 113, 129, 161, 209, 257, 289]
+    assert all(p[0] == "wreg" for p in _plans(planner, [(T, 24576, 2048, SWIGLU, 0, 1) for T in tokens]))
+    for N, K in ((4096, 2048), (2048, 12288)):
+        assert all(p[0] == "wreg" for p in _plans(planner, [(T, N, K, PARTIAL, 0, 1) for T in (257, 289, 321)]))
     # test_weights_in_registers_gemm_every_block: all four projections, any block, one row block and three
     for tm in range(5, 11):
         for nc in (2, 4):
@@ -48,6 +49,6 @@ def test_gpu_tests_of_the_weights_in_registers_gemm_reach_it(planner):
             for N, kind in ((192, PARTIAL), (2688, SWIGLU)):
                 assert _plans(planner, [(16 * tm + 1, N, 1024, kind, 10 * tm + nc, 1)]) == [("wreg", tm, nc, 1, 2)]
     # test_static_step_8b_layer_runs_the_kernels_of_ps_step_also_where_scratch_is_short
-    free, capped = _plans(planner, [(294, 4096, 14336, PARTIAL, 0, cap) for cap in (0, 1)])
+    free, capped = _plans(planner, [(673, 4096, 6144, PARTIAL, 0, cap) for cap in (0, 1)])
     assert free[0] == capped[0] == "wreg" and capped[3] < free[3]
-    assert _plans(planner, [(97, 28672, 4096, SWIGLU, 0, 1)])[0][0] == "wreg"
+    assert [p[0] for p in _plans(planner, [(97, 28672, 4096, SWIGLU, 0, 1), (294, 4096, 14336, PARTIAL, 0, 1)])] == ["wreg"] * 2

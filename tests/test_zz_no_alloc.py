@@ -89,16 +89,21 @@ def test_static_step_8b_layer_decode_batch_then_a_smaller_one():
         eng.close()
 
 
-@pytest.mark.parametrize("kv", [[200] * 97, [65 if i % 8 == 0 else 33 for i in range(294)]])
-def test_static_step_8b_layer_runs_the_kernels_of_ps_step_also_where_scratch_is_short(kv):
-    """97 and 294 one-token sequences: the weights-in-registers GEMM serves projections of both.  At 294 the K splits it
-    would take for the down projection, left to itself, do not fit the array beside some 1300 attention partials."""
-    b = W.custom_batch("8b", 3, 0, 0, kv, name="static")
-    eng = Engine(b.model, b.n_pool_pages, 1, 1, max_position=256)
-    eng.n_kv_layers = 1
-    eng.load_layer(0, W.layer_weights(b.model, 3, 0))
+@pytest.mark.parametrize("ffn,kv", [(14336, [200] * 97), (14336, [65 if i % 8 == 0 else 33 for i in range(294)]), (6144, [20] * 673)])
+def test_static_step_8b_layer_runs_the_kernels_of_ps_step_also_where_scratch_is_short(ffn, kv):
+    """97, 294 and 673 one-token sequences on layers of the 8B shape, the last with a narrower FFN: the weights-in-registers
+    GEMM serves projections of all.  At 673 the K splits it would take for the down projection, left to itself, do not fit the
+    array."""
+    W.MODELS["_s"] = dict(W.MODELS["8b"], ffn=ffn, n_kv=8 if ffn == 14336 else 4)
     try:
-        eng.load_prefixes(b)
-        _assert_same(_both_ways(eng, b, b.activations()), f"{len(kv)} decodes")
+        b = W.custom_batch("_s", 3, 0, 0, kv, name="static")
+        eng = Engine(b.model, b.n_pool_pages, 1, 1, max_position=256)
+        eng.n_kv_layers = 1
+        eng.load_layer(0, W.layer_weights(b.model, 3, 0))
+        try:
+            eng.load_prefixes(b)
+            _assert_same(_both_ways(eng, b, b.activations()), f"{len(kv)} decodes")
+        finally:
+            eng.close()
     finally:
-        eng.close()
+        del W.MODELS["_s"]
