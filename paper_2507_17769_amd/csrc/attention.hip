@@ -561,8 +561,7 @@ template <int D, int G>
 __global__ __launch_bounds__(64 * MERGE_MAX_WAVES) void attn_merge_kernel(AttnArgs a) {
     __shared__ float4 s_acc[MERGE_MAX_WAVES][64];
     __shared__ float2 s_ml[MERGE_MAX_WAVES][64];
-    // four consecutive groups (for a prefill chunk four tiles of consecutive rows, which share lines of the output) to an XCD
-    const int group = (blockIdx.x & ~31) | ((blockIdx.x & 7) << 2) | ((blockIdx.x >> 3) & 3);
+    const int group = merge_group_of_block(blockIdx.x, a.n_groups);
     if (group >= a.n_groups) return;
     const MergeGroup mg = a.groups[group];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), NW = blockDim.x >> 6;   // NW: a power of two
@@ -647,7 +646,7 @@ static hipError_t launch_dg(const AttnArgs& a_in, hipStream_t st) {
     const int passes = (std::max(1, a.max_merge_rows) * (D / 4) + 63) / 64;
     int nw = merge_split_waves(a.max_splits, MERGE_MAX_WAVES);
     for (int p = 1; p < passes && nw < MERGE_MAX_WAVES; p *= 2) nw *= 2;
-    hipLaunchKernelGGL((attn_merge_kernel<D, G>), dim3((a.n_groups + 31) / 32 * 32), dim3(64 * nw), 0, st, a);
+    hipLaunchKernelGGL((attn_merge_kernel<D, G>), dim3(merge_blocks(a.n_groups)), dim3(64 * nw), 0, st, a);
     return hipGetLastError();
 }
 

@@ -9,6 +9,7 @@
 
 #include "../../include/polystep.h"
 #include "gemm_plan.h"
+#include "xcd_order.h"
 
 namespace ps {
 
@@ -40,17 +41,6 @@ __host__ __device__ inline int v_elem_offset(int tok, int dd) {
 __host__ __device__ inline size_t act_offset(int m, int k, int K) {
     return ((((size_t)(m >> 4) * (K >> 5) + (k >> 5)) * 4 + ((k & 31) >> 3)) * 16 + (m & 15)) * 8 + (k & 7);
 }
-
-// Token rows and the L2s.  A 128-byte line of an operand-order matrix holds 16 bytes of eight consecutive rows, and a line of
-// the KV cache up to 16 tokens, while consecutive blocks run on different XCDs, each with an L2 of its own: with a block per
-// row a line would be written in pieces by eight L2s and put together in memory, byte-masked.  So the row kernels give every
-// XCD octets of rows: block b takes row row_of_block(b), and the grid is rounded up to whole rounds of eight octets.  Below
-// 64 rows, where the octets would not reach all XCDs and launch latency is what counts, blocks are rows.
-// (2048 tokens, 8B shape, us, rows in order / octets: reduce_add_norm 30.1 / 25.5, rmsnorm 17.8 / 13.9, rope_append 20.9 / 19.9,
-// whole step of four layers 3437 / 3349; 271 tokens 958 / 938; 64 tokens 834 / 832.)
-constexpr int ROW_ROUND = 64;
-__host__ __device__ inline int row_blocks(int n_rows) { return n_rows < ROW_ROUND ? n_rows : (n_rows + ROW_ROUND - 1) / ROW_ROUND * ROW_ROUND; }
-__host__ __device__ inline int row_of_block(int b, int n_rows) { return n_rows < ROW_ROUND ? b : (b & ~63) | ((b & 7) << 3) | ((b >> 3) & 7); }
 
 // Attention work item.  The first 8 fields are what ps_plan_attention reports; the rest is
 // what the kernel needs so that it never has to look the sequence up.
