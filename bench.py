@@ -91,6 +91,10 @@ def cpu_baseline(batch, weights, n_runs=2):
             "ms_per_step": t * 1e3}
 
 
+# the kernels that serve the four projections of a layer at the 1280 tokens of the default workload
+CFG4_GEMM_KERNELS = ("gemm_sk_kernel (QKV) and gemm_wreg_kernel (O, gate/up + SwiGLU, down): the four projection launches of one layer")
+
+
 def measured_traffic(workload, seed):
     """HBM bytes per launch of the workload's dominant kernel from the committed rocprofv3 counter runs
     (FETCH_SIZE and WRITE_SIZE, each scaled by what the same counter reads for a plain copy).  None when
@@ -323,7 +327,7 @@ def run_cfg4(a):
            "ms_per_step_events": percentiles(ms), "wall_ms_per_step": wall_ms / a.steps,
            "host_us_per_step": round(float(np.median(host_us)), 1),
            "host_us_per_step_into_an_empty_queue": round(float(np.median(idle_us)), 1),
-           "roofline": {"bound": "mfma", "kernel": "gemm_sk_kernel: the four projection launches of one layer (QKV, O, gate/up + SwiGLU, down)",
+           "roofline": {"bound": "mfma", "kernel": CFG4_GEMM_KERNELS,
                         "achieved": tflops, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": tflops / MFMA_BF16_PEAK_TFLOPS,
                         "traffic": measured_traffic("cfg4", a.seed),
                         "traffic_note": "HBM bytes of the four launches of one layer: stored reading of the rocprofv3 FETCH_SIZE / WRITE_SIZE "

@@ -14,8 +14,8 @@
 //
 // What is left (8B gate/up, 256 tokens, 67 us): the matrix instructions and LDS reads alone take 45 us, which is the rate the
 // matrix pipes hold under the power limit on the 224 compute units that have a block; all loads served by the caches 50 us;
-// the weights from memory make up the rest.  Measured (8B shape, us, before / with this kernel): gate/up 80 / 67 at 256 tokens,
-// 115 / 69 at 271, 187 / 157 at 640; down 45 / 38, 52 / 39, 94 / 66 (1.13 PFLOP/s); QKV 21 / 17 at 97 tokens, 43 / 36 at 640.
+// the weights from memory make up the rest.  Measured (8B shape, us, other kernel / this one): gate/up 80 / 67 at 256 tokens,
+// 115 / 69 at 271, 187 / 157 at 640; down 45 / 38, 52 / 39, 94 / 66 (1.13 PFLOP/s); QKV 24 / 22 at 97 tokens, 46 / 43 at 640.
 #include "ps_device.h"
 #include "gemm_wreg.h"
 

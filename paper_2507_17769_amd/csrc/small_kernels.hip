@@ -238,7 +238,7 @@ hipError_t launch_rope_append(const float* qkv, int n_splits, bf16_t* q_out, int
 // ------------------------------------------------------- logical KV write / read
 // k, v are [n][n_kv][d] in logical order, positions pos0 .. pos0 + n - 1 of a sequence; pages.id[i] is the page of positions
 // 16 (pos0 / 16 + i) on.  The pages travel as a kernel argument, not as a transfer of its own on the copy engine with events
-// to order it: eight reads and eight writes of 2047 tokens and a one-token step 495 us before, 457 now.  One thread per (group of four
+// to order it: four reads and four writes of 2047 tokens and a one-token step 495 us before, 457 now.  One thread per (group of four
 // positions aligned to 4, kv head, 8 consecutive dd): in the cache a key keeps 8 consecutive dd of one token together
 // (16 bytes) and a value keeps the four tokens of such a group together for one dd (8 bytes), so the thread moves
 // whole 16-byte rows on the logical side and 16- or 8-byte pieces on the cache side, transposing the 4 x 8 value

@@ -52,3 +52,14 @@ def test_gpu_tests_of_the_weights_in_registers_gemm_reach_it(planner):
     free, capped = _plans(planner, [(673, 4096, 6144, PARTIAL, 0, cap) for cap in (0, 1)])
     assert free[0] == capped[0] == "wreg" and capped[3] < free[3]
     assert [p[0] for p in _plans(planner, [(97, 28672, 4096, SWIGLU, 0, 1), (294, 4096, 14336, PARTIAL, 0, 1)])] == ["wreg"] * 2
+
+
+def test_bench_names_the_kernels_that_serve_the_default_workload(planner):
+    import bench
+    shapes = {"QKV": (10240, 8192, PARTIAL), "O": (8192, 8192, PARTIAL), "gate/up + SwiGLU": (57344, 8192, SWIGLU), "down": (8192, 28672, PARTIAL)}
+    names = {"tiled": "gemm_sk_kernel", "wreg": "gemm_wreg_kernel", "wstream": "gemm_wstream_kernel"}
+    by_kernel = {}
+    for proj, p in zip(shapes, _plans(planner, [(1280, *s, 0, 0) for s in shapes.values()])):
+        by_kernel.setdefault(names[p[0]], []).append(proj)
+    want = " and ".join(f"{k} ({', '.join(v)})" for k, v in by_kernel.items())
+    assert bench.CFG4_GEMM_KERNELS.startswith(want + ":"), want
