@@ -135,8 +135,8 @@ const char* ps_last_error(const ps_ctx* ctx);
  * decodes, the other resident blocks streaming the decodes' KV; 0 = one per CU, more if the teams would
  * outlast the streams), "attn_prefill_weight" (what the planner charges a team for a pair of pages, in
  * units of 100 ns, when it decides whether more than one team per CU is needed; it only moves the cuts),
- * "gemm_split_k" (0 = automatic; N = the K splits, i.e. fp32 partial buffers, of every projection but gate/up where the
- * kernel that serves it can be split that way: the weight-streaming one takes at most 8, the others 8 as well),
+ * "gemm_split_k" (0 = automatic; N = the K splits, at most 8, i.e. the fp32 partial buffers of every projection but gate/up,
+ * where the kernel that serves it can be split that way),
  * "gemm_tile" (0 = automatic; 128 or 256 = block tile edge: steps of more than 64 tokens then use the tiled GEMM kernel for
  * every projection, neither of the two others), "gemm_whole_tiles" (1: the tiled GEMM kernel gives
  * every tile to one block instead of cutting the K loops of a last, partial wave of tiles over all blocks; 2: it cuts
