@@ -302,20 +302,10 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
 // sb (page b) -> P as a packed B operand, reference maximum updated, alpha = the factor the accumulators take.  The row
 // sums are not taken here: the matrix unit adds up the rounded P it multiplies V with (see team_pair), so that the
 // output is a weighted mean of V rows whose weights sum to one exactly as rounded.
-// mask: keys beyond the row's position are taken out by setting their scores to -inf (the running maximum starts at a
-// large finite negative number, so a row that has seen no key yet keeps it and gets P = 0, alpha = 1).
-__device__ __forceinline__ bf16x8_t team_softmax(bool mask, const f32x4_t& sa, const f32x4_t& sb, float& m, float& alpha,
-                                                 int pq, int kpos_a, float scale2) {
-    float sv[8] = {sa[0], sa[1], sa[2], sa[3], sb[0], sb[1], sb[2], sb[3]};
-    if (mask) {   // uniform: only the pairs that reach past the wavefront's first query position
-        const float ninf = -__builtin_inff();
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            sv[i] = kpos_a + i <= pq ? sv[i] : ninf;
-            sv[4 + i] = kpos_a + 16 + i <= pq ? sv[4 + i] : ninf;
-        }
-    }
-    float mx = max3(max3(sv[0], sv[1], sv[2]), max3(sv[3], sv[4], sv[5]), max3(sv[6], sv[7], sv[7]));
+// The maximum is kept in the scores' own units, so that it joins the last step of the reduction over the row's lanes.
+__device__ __forceinline__ bf16x8_t team_softmax(const f32x4_t& sa, const f32x4_t& sb, float& m, float& alpha, float scale2) {
+    const float sv[8] = {sa[0], sa[1], sa[2], sa[3], sb[0], sb[1], sb[2], sb[3]};
+    float mx = max3(max3(sv[0], sv[1], sv[2]), max3(sv[3], sv[4], sv[5]), max3(sv[6], sv[7], m));
     {   // over the four lanes r, r+16, r+32, r+48 that share the row (see row_quad_max)
         const u32x2_t x = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
         const float y = max3(__uint_as_float(x.x), __uint_as_float(x.y), mx);
@@ -325,13 +315,12 @@ __device__ __forceinline__ bf16x8_t team_softmax(bool mask, const f32x4_t& sa, c
     // The reference is the exact running maximum, so a row's largest P is exactly 1 and carries no rounding error into
     // P.V.  (A reference that follows lazily, moving only after the maximum has grown by some factor, saves most of the
     // accumulator rescaling: measured 6 % faster on long prefixes, with 10 % more rounding error in the layer's output.)
-    const float cand = mx * scale2;
-    const float m_new = cand > m ? cand : m;
-    alpha = __builtin_amdgcn_exp2f(m - m_new);
-    m = m_new;
+    alpha = __builtin_amdgcn_exp2f((m - mx) * scale2);
+    m = mx;
+    const float ms = mx * scale2;
     float pv[8];
 #pragma unroll
-    for (int i = 0; i < 8; i++) pv[i] = __builtin_amdgcn_exp2f(fmaf(sv[i], scale2, -m_new));
+    for (int i = 0; i < 8; i++) pv[i] = __builtin_amdgcn_exp2f(fmaf(sv[i], scale2, -ms));
     uint4 pw;
     pw.x = pack_bf16(pv[0], pv[1]);
     pw.y = pack_bf16(pv[2], pv[3]);
@@ -374,15 +363,35 @@ __device__ __forceinline__ void team_pair(TileState<D, NT>& st, f32x4_t (&lacc)[
             sb[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kk[2 * s + 1]), qf[nt][s], sb[nt], 0, 0, 0);
         }
     }
+    if (mask) {   // uniform: only the pairs that reach past the wavefront's first query position
+        // Keys beyond the row's position are taken out by setting their scores to -inf (the running maximum starts at a large
+        // finite negative number, so a row that has seen no key yet keeps it and gets P = 0, alpha = 1).
+        const float ninf = -__builtin_inff();
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) {
+            const int left = min(pos_row + nt * tok_step, pos_max) - kpos_a;
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                sa[nt][i] = i <= left ? sa[nt][i] : ninf;
+                sb[nt][i] = 16 + i <= left ? sb[nt][i] : ninf;
+            }
+        }
+    }
     bf16x8_t pf[NT];
     float alpha[NT];
 #pragma unroll
-    for (int nt = 0; nt < NT; nt++) pf[nt] = team_softmax(mask, sa[nt], sb[nt], st.m[nt], alpha[nt], min(pos_row + nt * tok_step, pos_max), kpos_a, scale2);
+    for (int nt = 0; nt < NT; nt++) pf[nt] = team_softmax(sa[nt], sb[nt], st.m[nt], alpha[nt], scale2);
     if constexpr (DT == 8)
         asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(va[0]), "+v"(va[1]), "+v"(va[2]), "+v"(va[3]), "+v"(va[4]), "+v"(va[5]), "+v"(va[6]), "+v"(va[7]),
                      "+v"(vb[0]), "+v"(vb[1]), "+v"(vb[2]), "+v"(vb[3]), "+v"(vb[4]), "+v"(vb[5]), "+v"(vb[6]), "+v"(vb[7]));
     else
         asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(va[0]), "+v"(va[1]), "+v"(va[2]), "+v"(va[3]), "+v"(vb[0]), "+v"(vb[1]), "+v"(vb[2]), "+v"(vb[3]));
+    // What bounds the loop: the two wavefronts of a SIMD have to fill each other's waits, one on the matrix unit while the other
+    // is in its softmax.  Left to itself the arbiter serves the older one whatever it is about to issue; with the priority raised
+    // for the accumulation the matrix unit is fed first.  (2048 tokens behind 8192, 8B shape, with the scalar copy addresses and the
+    // maximum in the scores' units: 342 -> 301 us; 1024 behind 4096, 70B shape: 194 -> 173; 512 behind 2048: 44.5 -> 39.7.  Raised
+    // in the score products too, or there and in the softmax instead: 345 and 340 where this was 324 and nothing 371.)
+    __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int nt = 0; nt < NT; nt++) {
         // once the running max has settled alpha is exactly 1 in every lane: skip the D/4 multiplies
@@ -402,6 +411,7 @@ __device__ __forceinline__ void team_pair(TileState<D, NT>& st, f32x4_t (&lacc)[
             st.o[nt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, vw), pf[nt], st.o[nt][dt], 0, 0, 0);
         }
     }
+    __builtin_amdgcn_s_setprio(0);
 }
 
 // One work item on a team.  Wavefront w holds the tiles TEAM_NT w .. TEAM_NT w + TEAM_NT - 1 of the query block.
@@ -451,8 +461,10 @@ __device__ __forceinline__ void team_item(const AttnArgs& a, const AttnItem it, 
 #pragma unroll
     for (int nt = 0; nt < NT; nt++) lacc[nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     const float scale2 = 1.4426950408889634f / sqrtf((float)D);
-    const size_t page_stride = (size_t)a.n_kv * 2 * 16 * D;
-    const bf16_t* pool_lane = a.pool_slot + (size_t)it.kv_head * 2 * 16 * D + (size_t)lane * 8;
+    const uint32_t page_bytes = (uint32_t)a.n_kv * 2 * 16 * D * 2, lane16 = lane * 16;
+    // block c = wave KS + k of a pair: k-step c / 4, K or V by the second bit of c, page a or b by the first
+    const uint8_t* const pool_wave = reinterpret_cast<const uint8_t*>(a.pool_slot) + (size_t)it.kv_head * 2 * 16 * D * 2 + (wave * KS >> 2) * 1024 +
+                                     (KS == 4 ? 0 : (wave & 1) * 32 * D);
     const uint32_t ring0 = (uint32_t)(uintptr_t)ring;
 
     const int n_pg = it.page_end - it.page_begin;
@@ -469,17 +481,17 @@ __device__ __forceinline__ void team_item(const AttnArgs& a, const AttnItem it, 
             vm_wait<0>();   // here, so that the compiler does not wait for everything where the paths join
         }
         const int la = 2 * jj - tb0;
-        const int pa = __builtin_amdgcn_readlane(tbl, la);
-        const int pb = __builtin_amdgcn_readlane(tbl, min(la + 1, n_pg - tb0 - 1));
-        const bf16_t* ca = pool_lane + (size_t)pa * page_stride;
-        const bf16_t* cb = pool_lane + (size_t)pb * page_stride;
-        uint8_t* dst = ring + slot * PAIR_BYTES;
+        const uint32_t pa = __builtin_amdgcn_readlane(tbl, la);
+        const uint32_t pb = __builtin_amdgcn_readlane(tbl, min(la + 1, n_pg - tb0 - 1));
+        // uniform page addresses and a lane offset that never changes: no vector arithmetic per copy
+        const uint8_t* ca = pool_wave + (uint64_t)pa * page_bytes;
+        const uint8_t* cb = pool_wave + (uint64_t)pb * page_bytes;
+        uint8_t* dst = ring + slot * PAIR_BYTES + wave * (KS * 1024);
+        uint32_t off[2] = {lane16, lane16 + (KS == 4 ? 32 * D : 0)};   // K and V of a page (of head dim 64, a wavefront copies only one)
+        asm volatile("" : "+v"(off[0]), "+v"(off[1]));   // 32-bit offsets in registers of their own: scalar base + vector offset addressing
 #pragma unroll
-        for (int k = 0; k < KS; k++) {
-            const int c = wave * KS + k;            // KiB block of the pair: [k-step c / 4][c % 4: Ka, Kb, Va, Vb]
-            const bf16_t* src = ((c & 1) ? cb : ca) + ((c >> 1) & 1) * 16 * D + (c >> 2) * 512;
-            PS_GLOBAL_TO_LDS(src, dst + c * 1024);
-        }
+        for (int k = 0; k < KS; k++)            // KiB block wave KS + k of the pair: [k-step s][Ka, Kb, Va, Vb]
+            PS_GLOBAL_TO_LDS(((k & 1) ? cb : ca) + off[k >> 1], dst + k * 1024);
     };
 
     __builtin_amdgcn_s_barrier();   // every wavefront has finished with the ring (previous item)
@@ -510,6 +522,7 @@ __device__ __forceinline__ void team_item(const AttnArgs& a, const AttnItem it, 
 #pragma unroll
     for (int nt = 0; nt < NT; nt++) {
         st.lsum[nt] = lacc[nt][0];
+        st.m[nt] *= scale2;   // the merge works in the exponent's units
         rvalid[nt] = tok_row + nt * TQ < it.q_ntok;
         qi[nt] = it.tok_g0 + min(tok_row + nt * TQ, it.q_ntok - 1);
     }
