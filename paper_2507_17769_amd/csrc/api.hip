@@ -181,6 +181,7 @@ static PlanConfig plan_config(const ps_ctx* c) {
     pc.n_teams = c->opt_attn_teams;
     pc.team_pair_ns = 100.0 * c->opt_attn_prefill_weight;
     pc.block_slots = c->worker_slots / 4;
+    pc.compute_units = c->host_only ? 0 : pc.block_slots / 2;   // two blocks to a unit
     pc.prefill_tokens = attn_prefill_tokens_per_item(pc.group);
     return pc;
 }
@@ -627,13 +628,24 @@ extern "C" ps_status ps_kv_read(ps_ctx* c, int32_t layer, const ps_seq* seq, int
 }
 
 // ------------------------------------------------------------------------------ planning
+static bool static_fits(const ps_ctx* c, const StepPlan& p, bool with_partials);
+
 static ps_status make_plan(ps_ctx* c, const ps_seq* seqs, int32_t n_seqs, bool with_attention) {
     const PlanConfig pc = plan_config(c);
     std::string err;
     ps_status st = validate_batch(seqs, n_seqs, pc, c->page_seen, err);
     if (st != PS_OK) return fail(c, st, err);
     build_indices(seqs, n_seqs, c->plan);
-    if (with_attention) build_attention_plan(pc, c->plan);
+    if (!with_attention) return PS_OK;
+    build_attention_plan(pc, c->plan);
+    // A step that would fit the static scratch with the partials of fewer teams gets those, whichever call runs it, so that
+    // ps_step_static takes it and gives the bits of ps_step.
+    if (!c->host_only && n_seqs > 0 && c->plan.n_team_workers > pc.block_slots / 2 && static_fits(c, c->plan, false) && !static_fits(c, c->plan, true)) {
+        PlanConfig one = pc;
+        one.one_block_per_cu = true;
+        build_attention_plan(one, c->plan);
+        if (!static_fits(c, c->plan, true)) build_attention_plan(pc, c->plan);
+    }
     return PS_OK;
 }
 
@@ -853,6 +865,14 @@ static StaticLayout static_layout(const ps_ctx* c, int T, int n_part_slots, size
     m.skfrag = take(m.skfrag_bytes); m.skcnt = take((size_t)m.skcnt_n * sizeof(int));
     m.total = at;
     return m;
+}
+
+// Whether the static scratch holds a step's buffers (with_partials: those of the attention splits, and the metadata, too).
+static bool static_fits(const ps_ctx* c, const StepPlan& p, bool with_partials) {
+    GemmOptions o = gemm_options(c);
+    o.cap_splits = true;
+    const size_t meta = with_partials ? meta_layout(p, false).total : 0;
+    return meta <= STATIC_META_SLOT && static_layout(c, p.n_tokens, with_partials ? p.n_partial_slots : 0, meta, o).total <= (size_t)PS_STATIC_SCRATCH_BYTES;
 }
 
 // GEMM options of a step's layers.  A function of the batch and the options of the context alone, not of the call: a batch

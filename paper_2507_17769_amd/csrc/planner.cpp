@@ -101,6 +101,51 @@ void build_indices(const ps_seq* seqs, int n_seqs, StepPlan& plan) {
     }
 }
 
+// Blocks of the attention launch: how many work as teams and how many wavefronts stream.  pairs_*: page pairs of either pool, and of
+// a decode and KV head in the mean.
+//
+// A compute unit holds two blocks, but a second one mostly does not pay: two teams on a unit take 1.8 us per pair of pages where
+// one takes 1.2, a team slows down beside streaming wavefronts, and twice the workers leave twice the partials to merge, while
+// some 800 wavefronts already keep HBM busy.  So a step gets one block per unit, shared in proportion to the two pools'
+// work, and two per unit only where the teams have long runs (24 pairs per unit) and more work than fits beside the streams
+// at the rate of HBM (from a fifth of the streams' pairs on: 8B shape, one / two blocks, 9300 pairs of teams to 22600 of streams
+// 108 / 104 us, 12500 to 42300 168 / 157, 6400 to 23600 101 / 101, 6400 to 51800 171 / 175, 5200 to 92400 272 / 294).
+// Measured with the merge on 170 mixtures (17 to 1600 new tokens behind up to 6000 next to 1 to 256 decodes, both large shapes):
+// 9 % faster in the mean than two blocks on every unit with a team on each, where the best split of a sweep gives 11.7 %;
+// 128 tokens behind 1500 next to 16 decodes 40.8 -> 33.4 us, 1024 behind 4096 next to 64 202 -> 138, 64 decodes 97 -> 93.
+static void share_blocks(const PlanConfig& cfg, double pairs_team, double pairs_wave, double pairs_per_stream, int* n_team, int* n_wave) {
+    const int B = std::max(16, cfg.block_slots), cus = cfg.compute_units > 0 ? std::min(std::max(8, cfg.compute_units), B) : B;
+    const double long_run = 24.0 * cus;   // page pairs of the teams; without streams one / two blocks 27 / 31 us at 1200 pairs, 51 / 53 at 5900, 51 / 48 at 6400, 130 / 105 at 25600
+    if (pairs_team <= 0) {
+        // long streams keep HBM busy from 13 of 16 units (128 decodes of 2000 tokens 235, 225, 230, 234 us with 640, 832, 1024, 2048
+        // wavefronts; 64 of 2100 97, 93, 94, 96), short ones, several to a wavefront, take all (183 of 250 tokens 49, 45, 43, 44)
+        *n_wave = 4 * (cus < B && pairs_per_stream >= 24 ? 13 * cus / 16 : cus);
+    } else if (pairs_wave <= 0) {
+        *n_team = pairs_team < long_run ? cus : B;
+    } else if (cfg.n_teams > 0) {
+        *n_team = std::min(cfg.n_teams, B - 1);
+        *n_wave = 4 * (B - *n_team);
+    } else {
+        const double work = 4.0 * cfg.team_pair_ns * pairs_team / (cfg.wave_pair_ns * pairs_wave);   // of the teams against that of the streams, in blocks
+        int blocks = cus, t;
+        if (pairs_team > long_run && pairs_team > 0.2 * pairs_wave && !cfg.one_block_per_cu) {
+            blocks = B;
+            const double w = 0.73 * work;   // beside another block a stream loses more than a team
+            t = std::max(cus, (int)(B * w / (1.0 + w)));
+        } else {
+            t = (int)(cus * work / (1.0 + work));
+            // streams that HBM holds up longer than a quarter of the units needs for the teams: all the wavefronts that HBM can use
+            if (pairs_wave * cfg.hbm_pair_ns > 9000.0 + pairs_team * 1200.0 / std::max(1, cus / 4)) t = std::min(t, cus / 4);
+            t = std::max(t, (int)std::min(pairs_team / 6, cus / 8.0));   // a small chunk: a team's start takes as long as six pairs
+        }
+        // Every XCD gets the same number of either kind, rounded up, and its blocks have to be resident together: whole eighths.
+        // (349 teams and 163 blocks of streams are 65 blocks on the 64 places of an XCD: 219 us where 320 and 192 take 176.)
+        t = std::min(std::min((t + 4) / 8 * 8, blocks - 8), (int)(pairs_team / 4));
+        *n_team = std::max(1, t);
+        *n_wave = 4 * std::max(8, blocks - (*n_team + 7) / 8 * 8);
+    }
+}
+
 // Attention plan.  The KV stream of every (sequence, kv head, query block) is a segment of page
 // pairs; a decode token's cost is the bytes of its KV span (Sec. 2.2, 3.4: decode attention does
 // not batch, it scales with the KV tokens read).  Instead of fixed-size splits handed out
@@ -111,11 +156,7 @@ void build_indices(const ps_seq* seqs, int n_seqs, StepPlan& plan) {
 // There are two kinds of worker, each with its own pool of segments.  Query blocks of more than one
 // tile (prefill chunks, Sec. 2.4) go to teams: a block of four wavefronts that shares every pair of
 // pages through LDS and is bound by the matrix units.  Single-tile blocks (decodes) go to single
-// wavefronts, which are bound by HBM.  All blocks of the launch are resident at once; how many of
-// them work as teams: all of them in a step without decodes; otherwise one per CU, and more only if
-// the teams would outlast the streams (a team's time is its page pairs times a cost that grows once
-// two teams share a CU, the wavefronts' time is the larger of the HBM time of all their pairs and of
-// the per-wavefront time when few wavefronts are left).
+// wavefronts, which are bound by HBM.  All blocks of the launch are resident at once, on every CU one or two: see share_blocks.
 void build_attention_plan(const PlanConfig& cfg, StepPlan& plan) {
     plan.items.clear();
     plan.groups.clear();
@@ -155,37 +196,8 @@ void build_attention_plan(const PlanConfig& cfg, StepPlan& plan) {
         n_team = segs_team.empty() ? 0 : cfg.n_workers;
         n_wave = segs_wave.empty() ? 0 : cfg.n_workers;
     } else {
-        const int B = std::max(1, cfg.block_slots);
-        const double pairs_team = (double)units_team / W_MULTI, pairs_wave = (double)units_wave / W_SINGLE;
-        if (segs_team.empty()) {
-            n_wave = 4 * B;
-        } else if (segs_wave.empty()) {
-            n_team = B;
-        } else if (cfg.n_teams > 0) {
-            n_team = std::min(cfg.n_teams, B - 1);
-            n_wave = 4 * (B - n_team);
-        } else {
-            // One team per CU, next to a block of streaming wavefronts: half the blocks' wavefronts already keep HBM busy,
-            // and a team that finishes early costs nothing.  More teams (two on some CUs, which slows both) only when the
-            // teams would otherwise outlast the streams.
-            auto cost = [&](int t) {
-                const double crowd = t <= B / 2 ? 0.0 : (double)(t - B / 2) / (B / 2);
-                const double t_team = pairs_team * cfg.team_pair_ns * (1.0 + cfg.team_crowding * crowd) / t;
-                const double t_wave = std::max(pairs_wave * cfg.hbm_pair_ns, pairs_wave * cfg.wave_pair_ns / (4.0 * (B - t)));
-                return std::max(t_team, t_wave);
-            };
-            n_team = std::max(1, B / 2);
-            double best = cost(n_team);
-            for (int t = n_team + 1; t < B; t++)
-                if (cost(t) < 0.98 * best) { best = cost(t); n_team = t; }
-            n_wave = 4 * (B - n_team);
-            // Few decodes beside a large chunk: no more wavefronts than keep the streams inside the teams' time with a
-            // margin, so that a short stream is not cut into hundreds of pieces for the merge to put together again.
-            const double crowd = n_team <= B / 2 ? 0.0 : (double)(n_team - B / 2) / (B / 2);
-            const double t_team = pairs_team * cfg.team_pair_ns * (1.0 + cfg.team_crowding * crowd) / n_team;
-            const double need = 2.0 * pairs_wave * cfg.wave_pair_ns / std::max(t_team, 1.0);
-            if (need < n_wave) n_wave = std::max(8, (int)need);
-        }
+        share_blocks(cfg, (double)units_team / W_MULTI, (double)units_wave / W_SINGLE, segs_wave.empty() ? 0.0 : (double)units_wave / W_SINGLE / (segs_wave.size() * cfg.n_kv_heads),
+                     &n_team, &n_wave);
     }
     // do not spread thinner than ~4 page pairs per worker
     if (n_team > 0) n_team = (int)std::max<int64_t>(1, std::min<int64_t>(n_team, units_team / (4 * W_MULTI)));

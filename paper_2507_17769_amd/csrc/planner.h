@@ -34,11 +34,12 @@ struct PlanConfig {
     int n_workers = 0;         // workers of each kind; 0 = share the resident blocks between the kinds by cost
     int n_teams = 0;           // > 0: this many teams when a step has both kinds of work (0 = by cost)
     int block_slots = 512;     // blocks (of four wavefronts) of the attention kernel resident at once
+    int compute_units = 0;     // that hold them; 0 = not known: every block is taken to have one to itself
     int prefill_tokens = 32;   // query tokens per team item (all its tiles)
-    // cost model behind the split of the blocks: nanoseconds a team spends on a pair of pages while it has its CU's
-    // matrix units to itself and the streams keep HBM busy, the relative growth of that when two teams share every CU, HBM time of a pair streamed
-    // by a single wavefront (all of them together), time a lone wavefront needs for a pair
-    double team_pair_ns = 2200.0, team_crowding = 0.85, hbm_pair_ns = 2.75, wave_pair_ns = 2000.0;
+    bool one_block_per_cu = false;   // at most: fewer teams, whose partials take less memory
+    // what shares the blocks between the kinds (share_blocks): nanoseconds per pair of pages of a team and of a streaming wavefront
+    // (four to a block), and what HBM takes for a pair
+    double team_pair_ns = 2200.0, wave_pair_ns = 2900.0, hbm_pair_ns = 2.6;
 };
 
 // Validates the batch (see ps_seq in polystep.h).  On failure returns PS_EINVAL / PS_ERANGE
