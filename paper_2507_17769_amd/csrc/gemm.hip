@@ -48,7 +48,8 @@ struct GemmParams {
 };
 
 // ------------------------------------------------------------------------------------------
-// Weight streaming kernel (M <= 160: up to ten row tiles of 16).  grid (N/64/NG, splits), 64 (4 NG + 1) threads, NG = 1 or 2 column groups per block.
+// Weight streaming kernel (M <= 160: up to ten row tiles of 16).  grid (N/64/NG, splits), 64 KS (4 NG + 1) threads, NG = 1 or 2 column groups per block,
+// or one of them in KS = 2 shares of the block's K range, each with a producer and a ring of its own, added up through LDS.
 //
 // A block owns 64 output columns and a K range.  Its four computing wavefronts divide the columns
 // (16 each: one 16-byte load per lane and k-block fetches a KiB that already is a 16x16x32
@@ -70,18 +71,22 @@ __device__ __forceinline__ void ws_barrier() {
     asm volatile("" ::: "memory");
 }
 
-template <int MT, int KIND, int NG>
-__global__ __launch_bounds__(64 * (4 * NG + 1)) void gemm_wstream_kernel(GemmParams p) {
-    constexpr int NCW = 4 * NG;        // computing wavefronts: four per group of 64 columns, NG groups share the activation ring
+template <int MT, int KIND, int NG, int KS>
+__global__ __launch_bounds__(64 * KS * (4 * NG + 1)) void gemm_wstream_kernel(GemmParams p) {
+    static_assert(KS == 1 || (KS == 2 && NG == 1 && KIND == GemmOut::PARTIAL_F32), "shape");
+    constexpr int NCW = 4 * NG;        // computing wavefronts of a K share: four per group of 64 columns, NG groups share the activation ring
     constexpr int XS = MT * 2 * 1024;  // bytes of an activation stage: MT row tiles x 2 k-blocks
     constexpr int WSETS = 4;           // weight stages in registers: three requested ahead of the one in work (a
                                        // deeper ring costs registers, i.e. resident blocks, and measured slower)
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[3 * XS];
+    __shared__ __attribute__((aligned(1024))) uint8_t rings[KS * 3 * XS];
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int share = KS == 1 ? 0 : wave_in_block / (NCW + 1), wave = wave_in_block - share * (NCW + 1);
+    uint8_t* const lds = rings + share * (3 * XS);
     const int KB = p.K >> 5;
-    const int kb0 = blockIdx.y * p.kb_per_split;
-    const int n_st = (min(KB, kb0 + p.kb_per_split) - kb0) >> 1;  // kb_per_split is even
+    const int kb_block = blockIdx.y * p.kb_per_split;
+    const int n_st = (min(KB, kb_block + p.kb_per_split) - kb_block) / (2 * KS);  // kb_per_split and KB are multiples of 2 KS
+    const int kb0 = kb_block + share * 2 * n_st;
     if (n_st <= 0) return;
 
     if (wave == NCW) {
@@ -107,6 +112,10 @@ __global__ __launch_bounds__(64 * (4 * NG + 1)) void gemm_wstream_kernel(GemmPar
         }
         vm_wait<0>();
         if constexpr (KIND == GemmOut::SWIGLU_BF16) {  // the epilogue's barriers: no copy is in flight any more / sums handed over
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_s_barrier();
+        }
+        if constexpr (KS == 2) {   // likewise
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_s_barrier();
         }
@@ -186,12 +195,25 @@ __global__ __launch_bounds__(64 * (4 * NG + 1)) void gemm_wstream_kernel(GemmPar
             }
         }
     } else {
+        if constexpr (KS == 2) {
+            // the two K shares add up: either keeps every other row tile and takes the other's sums of it
+            f32x4_t* const sums = reinterpret_cast<f32x4_t*>(rings);   // [mt][wave][lane]
+            ws_barrier();   // the rings are free
+#pragma unroll
+            for (int mt = 0; mt < MT; mt++)
+                if ((mt & 1) != share) sums[(mt * NCW + wave) * 64 + lane] = acc[mt];
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the LDS writes have been made before the barrier
+            ws_barrier();
+#pragma unroll
+            for (int mt = 0; mt < MT; mt++)
+                if ((mt & 1) == share) acc[mt] += sums[(mt * NCW + wave) * 64 + lane];
+        }
         if (!have_group) return;
         float* out = static_cast<float*>(p.out) + (size_t)blockIdx.y * p.M * p.N;
 #pragma unroll
         for (int mt = 0; mt < MT; mt++) {
             const int m = mt * 16 + r;
-            if (m < p.M)
+            if (m < p.M && (KS == 1 || (mt & 1) == share))
                 *reinterpret_cast<float4*>(out + (size_t)m * p.N + ng * 64 + cw * 16 + 4 * g) = float4{acc[mt][0], acc[mt][1], acc[mt][2], acc[mt][3]};
         }
     }
@@ -654,11 +676,13 @@ hipError_t launch_gemm(const GemmArgs& a, int* n_splits, hipStream_t st) {
         // price of half as many blocks.  Measured: always a gain for the gate/up matrix (448 groups, no K split; 64
         // tokens: 54 -> 49 us), a gain for the split projections from four row tiles on, a loss below.
         const bool two = a.kind == GemmOut::SWIGLU_BF16 || mt >= 4;
-        const dim3 grid(two ? (a.N / 64 + 1) / 2 : a.N / 64, g.splits);
+        const bool shares = g.k_shares == 2;
+        const dim3 grid(two && !shares ? (a.N / 64 + 1) / 2 : a.N / 64, g.splits);
 #define PS_WS_LAUNCH(MT_)                                                                                                  \
-    if (a.kind == GemmOut::SWIGLU_BF16) hipLaunchKernelGGL((gemm_wstream_kernel<MT_, GemmOut::SWIGLU_BF16, 2>), grid, dim3(576), 0, st, p); \
-    else if (two) hipLaunchKernelGGL((gemm_wstream_kernel<MT_, GemmOut::PARTIAL_F32, 2>), grid, dim3(576), 0, st, p);             \
-    else hipLaunchKernelGGL((gemm_wstream_kernel<MT_, GemmOut::PARTIAL_F32, 1>), grid, dim3(320), 0, st, p);
+    if (a.kind == GemmOut::SWIGLU_BF16) hipLaunchKernelGGL((gemm_wstream_kernel<MT_, GemmOut::SWIGLU_BF16, 2, 1>), grid, dim3(576), 0, st, p); \
+    else if (shares) hipLaunchKernelGGL((gemm_wstream_kernel<MT_, GemmOut::PARTIAL_F32, 1, 2>), grid, dim3(640), 0, st, p);       \
+    else if (two) hipLaunchKernelGGL((gemm_wstream_kernel<MT_, GemmOut::PARTIAL_F32, 2, 1>), grid, dim3(576), 0, st, p);          \
+    else hipLaunchKernelGGL((gemm_wstream_kernel<MT_, GemmOut::PARTIAL_F32, 1, 1>), grid, dim3(320), 0, st, p);
         switch (mt) {
             case 1: PS_WS_LAUNCH(1) break;
             case 2: PS_WS_LAUNCH(2) break;

@@ -61,6 +61,7 @@ struct GemmPlan {
     bool wreg;          // weights in registers (gemm_wreg.hip), with the plan below
     WregPlan wreg_plan;
     bool big_tile;      // tiled: 256x256 blocks (else 128x128)
+    int k_shares;       // weight streaming: K shares that a block adds up (1 or 2)
     int splits;         // partial buffers written
     int kb_per_split;   // 32-wide k-blocks per split
     bool cut_tail;      // tiled: cut the K loops of the last, partial wave of tiles over the blocks (one split only)
@@ -185,6 +186,7 @@ inline GemmPlan plan_gemm(int M, int N, int K, int kind, const GemmOptions& o, i
     // above all for the gate/up matrix (129 tokens: 61 vs 75 us) and the down projection (42 vs 46)
     g.wstream = M <= 64 || (tile_opt == 0 && (M <= 96 || (M <= 160 && (kind == GemmOut::SWIGLU_BF16 || N <= K))));
     g.big_tile = false;
+    g.k_shares = 1;
     g.splits = 1;
     g.kb_per_split = K / 32;
     g.cut_tail = false;
@@ -210,8 +212,19 @@ inline GemmPlan plan_gemm(int M, int N, int K, int kind, const GemmOptions& o, i
             s = std::min(s, std::max(1, KB / 8));  // keep at least two k-blocks per wavefront slice
             s = std::max(s, 1);
         }
+        const bool wide = N > K && (double)N * K >= 16e6;   // from 65 tokens on a case for the weights in registers, see below
+        // A wavefront with a short run of K (up to 24 k-blocks) spends as long on its start and on writing its partial sums as on
+        // the weights: two K shares inside a block add up through LDS, and three quarters as many blocks as compute units
+        // take the place of two each.  Measured with the kernel behind it (us, one share in 8 splits / two shares in 3): O of the 8B
+        // shape 13.5 / 12.5 at 8 tokens, 18.1 / 16.0 at 64, 21.9 / 19.3 at 97, 24.6 / 21.5 at 144; QKV up to 32 tokens 11.4 /
+        // 12.6, from there on 16.4 / 16.3 with a third of the partial sums; of the tiny shape each product 0.4 to 0.6 less.
+        // Longer runs lose: O of the 70B shape 28.0 / 28.9 at 16 tokens, down of the 8B shape 28.4 / 29.9 at 64.
+        if (kind != GemmOut::SWIGLU_BF16 && KB % 4 == 0 && (KB + s - 1) / s <= 24 && (N <= K || (M > 32 && (M <= 64 || !wide)))) {
+            g.k_shares = 2;
+            if (split_opt == 0) s = std::max(1, std::min(s, (192 + groups / 2) / groups));
+        }
         int kps = (KB + s - 1) / s;
-        kps += kps & 1;  // whole stages of two k-blocks
+        kps = (kps + 2 * g.k_shares - 1) / (2 * g.k_shares) * (2 * g.k_shares);  // whole stages of two k-blocks for every share
         g.kb_per_split = kps;
         g.splits = (KB + kps - 1) / kps;
         // Measured against streaming (kernel and consumer, us, streaming / weights in registers): gate/up of the 8B shape 45 / 45 at
@@ -221,7 +234,7 @@ inline GemmPlan plan_gemm(int M, int N, int K, int kind, const GemmOptions& o, i
         // 128256 columns 239 / 204 at 65 and 240 / 210 at 96 (4096 deep), 432 / 356 and 398 / 364 (8192 deep); 4096 columns 2048
         // deep 19 / 21 and 22 / 21, so that small ones stay, as do the O and down projections.
         const bool gate_up = kind == GemmOut::SWIGLU_BF16;
-        if (allow_wreg && ((gate_up && (M > 96 || N / 128 > cus)) || (!gate_up && N > K && (double)N * K >= 16e6)))
+        if (allow_wreg && ((gate_up && (M > 96 || N / 128 > cus)) || (!gate_up && wide)))
             g.wreg = std::isfinite(wreg_best(M, N, K, kind, split_opt, o.cap_splits ? g.splits : 8, cus, &g.wreg_plan));
         if (g.wreg) {
             g.wstream = false;

@@ -387,6 +387,15 @@ def test_weights_in_registers_gemm_every_block(tm, nc):
     _wreg_case(small, 16 * tm + 1, {"gemm_wreg": 10 * tm + nc})
 
 
+@pytest.mark.parametrize("tokens", [5, 16, 17, 48, 49, 64, 65, 97, 160])
+def test_streaming_gemm_two_k_shares(tokens):
+    # O (and QKV from 33 to 64 tokens) on weight streaming with two K shares in a block: one row tile, which one share keeps, to ten;
+    # K of 36 blocks, cut into three splits of 12, and of 32 in four of 8, and one split alone
+    _wreg_case(dict(hidden=1152, n_q=18, n_kv=9, head_dim=64, ffn=1344, rope_base=10000.0, n_layers=1), tokens, {})
+    for split in (0, 1):
+        _wreg_case(dict(hidden=1024, n_q=16, n_kv=1, head_dim=64, ffn=1024, rope_base=10000.0, n_layers=1), tokens, {"gemm_split_k": split})
+
+
 @pytest.mark.parametrize("chunk,splits", [(0, [1, 2, 8]), (0, [9, 16, 17]), (40, [2, 64, 65]), (40, [128, 129, 257])])
 def test_merge_groups_with_different_numbers_of_splits(chunk, splits):
     # decodes of 128 tokens per split (workers take at least four pairs of pages each) next to each other and to a chunk in few
