@@ -1073,11 +1073,12 @@ static ps_status step_impl(ps_ctx* c, const ps_seq* seqs, int32_t n_seqs, const 
         g.A = W.xn; g.Wp = L.wqkv_t; g.M = T; g.N = NQKV; g.K = H; g.kind = GemmOut::PARTIAL_F32;
         g.out = W.part; g.out_bytes = W.part_bytes; g.opt = W.gemm;
         g.sk_frag = W.skfrag; g.sk_frag_bytes = W.skfrag_bytes; g.sk_counters = W.skcnt; g.sk_n_counters = W.skcnt_n;
+        g.rope = RopeOut{W.q, pool_slot, d_pos, d_slots, reinterpret_cast<const float2*>(c->rope_cs), d.n_q_heads, d.n_kv_heads, d.head_dim};
         HIP_TRY(c, run_gemm(g, &n_splits, 0));
         if (stats) HIP_TRY(c, hipEventRecord(c->ev[++e], s));
         // 2: sum the partials, rotate, round once to bf16, append k/v to the pages
-        HIP_TRY(c, launch_rope_append(W.part, n_splits, W.q, T, d.n_q_heads, d.n_kv_heads, d.head_dim, d_pos,
-                                      d_slots, c->rope_cs, pool_slot, s));
+        if (n_splits > 0) HIP_TRY(c, launch_rope_append(W.part, n_splits, g.rope, T, s));   // 0: the GEMM has done it
+        g.rope = RopeOut{};
         if (tap && c->taps.q) HIP_TRY(c, launch_copy_bytes(W.q, c->taps.q, (size_t)T * NQ * 2, s));
         if (stats) HIP_TRY(c, hipEventRecord(c->ev[++e], s));
         // 3: attention

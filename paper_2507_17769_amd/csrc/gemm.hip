@@ -32,6 +32,7 @@
 // residual, normalises, rotates ...) or, for the fused gate/up matrix, silu(gate) * up in bf16.
 #include "ps_device.h"
 #include "gemm_wreg.h"
+#include "rope_store.h"
 
 #include <algorithm>
 #include <mutex>
@@ -45,6 +46,7 @@ struct GemmParams {
     int kind;          // GemmOut::Kind
     void* out;         // fp32 [split][M][N] row-major, or bf16 [M][N/2] in operand order
     int kb_per_split;  // 32-wide k-blocks per block
+    RopeOut rope;      // weight streaming: q null unless this is a QKV product in one split, of head dim 64
 };
 
 // ------------------------------------------------------------------------------------------
@@ -115,9 +117,10 @@ __global__ __launch_bounds__(64 * KS * (4 * NG + 1)) void gemm_wstream_kernel(Ge
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_s_barrier();
         }
-        if constexpr (KS == 2) {   // likewise
-            __builtin_amdgcn_s_barrier();
-            __builtin_amdgcn_s_barrier();
+        if constexpr (KIND == GemmOut::PARTIAL_F32) {   // likewise
+            if (KS == 2 || p.rope.q) __builtin_amdgcn_s_barrier();
+            if (KS == 2) __builtin_amdgcn_s_barrier();
+            if (p.rope.q) __builtin_amdgcn_s_barrier();
         }
         return;
     }
@@ -197,7 +200,7 @@ __global__ __launch_bounds__(64 * KS * (4 * NG + 1)) void gemm_wstream_kernel(Ge
     } else {
         if constexpr (KS == 2) {
             // the two K shares add up: either keeps every other row tile and takes the other's sums of it
-            f32x4_t* const sums = reinterpret_cast<f32x4_t*>(rings);   // [mt][wave][lane]
+            f32x4_t* const sums = reinterpret_cast<f32x4_t*>(rings);   // [mt][wave][lane]: a third of the rings
             ws_barrier();   // the rings are free
 #pragma unroll
             for (int mt = 0; mt < MT; mt++)
@@ -207,6 +210,33 @@ __global__ __launch_bounds__(64 * KS * (4 * NG + 1)) void gemm_wstream_kernel(Ge
 #pragma unroll
             for (int mt = 0; mt < MT; mt++)
                 if ((mt & 1) == share) acc[mt] += sums[(mt * NCW + wave) * 64 + lane];
+        }
+        if (p.rope.q) {
+            // A group of 64 columns is a head: column tiles 0, 1 hold its lower half and 2, 3 what that is rotated with, so wavefronts 2
+            // and 3 of a group hand their sums over.  No partial sums, no launch behind: tiny shape, 68 tokens, 8.4 -> 6.5 us.
+            // (Larger products, of the two other kernels, pay for the scattered stores at their end: QKV of the 8B shape at 2048
+            // tokens 92.7 -> 113.8 us for 20.3 of rope_append.)
+            const int gi = wave / 4;
+            f32x4_t* const upper = reinterpret_cast<f32x4_t*>(rings + (KS == 2 ? MT * NCW * 1024 : 0));   // [group in block][cw - 2][mt][lane]
+            if (KS == 1) ws_barrier();   // the rings are free
+            if (cw >= 2) {
+#pragma unroll
+                for (int mt = 0; mt < MT; mt++)
+                    if (KS == 1 || (mt & 1) == share) upper[((gi * 2 + cw - 2) * MT + mt) * 64 + lane] = acc[mt];
+            }
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+            ws_barrier();
+            if (cw >= 2 || !have_group) return;
+            const int j = 16 * cw + 4 * g;
+#pragma unroll
+            for (int mt = 0; mt < MT; mt++) {
+                const int m = mt * 16 + r;
+                if (m >= p.M || (KS == 2 && (mt & 1) != share)) continue;
+                const f32x4_t up = upper[((gi * 2 + cw) * MT + mt) * 64 + lane];
+                const float lo[4] = {acc[mt][0], acc[mt][1], acc[mt][2], acc[mt][3]}, hi[4] = {up[0], up[1], up[2], up[3]};
+                rope_store(p.rope, m, ng, j, lo, hi, rope_angles(p.rope, p.rope.positions[m], j));
+            }
+            return;
         }
         if (!have_group) return;
         float* out = static_cast<float*>(p.out) + (size_t)blockIdx.y * p.M * p.N;
@@ -668,7 +698,9 @@ hipError_t launch_gemm(const GemmArgs& a, int* n_splits, hipStream_t st) {
     GemmParams p;
     p.A = a.A; p.Wp = a.Wp; p.M = a.M; p.N = a.N; p.K = a.K; p.kind = a.kind; p.out = a.out;
     p.kb_per_split = g.kb_per_split;
-    if (n_splits) *n_splits = g.splits;
+    p.rope = a.rope;
+    if (!g.wstream || g.splits != 1 || a.rope.d != 64) p.rope.q = nullptr;
+    if (n_splits) *n_splits = p.rope.q ? 0 : g.splits;
     if (g.wreg) return launch_gemm_wreg(a, g.wreg_plan, st);
     if (g.wstream) {
         const int mt = (a.M + 15) / 16;

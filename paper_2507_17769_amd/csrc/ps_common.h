@@ -91,10 +91,17 @@ hipError_t launch_embed_gather(const bf16_t* table, const int32_t* ids, bf16_t* 
 hipError_t launch_argmax_rows(const float* x, int M, int N, int32_t* out, hipStream_t st);
 // operand-order [M][K] bf16 matrix -> row-major (for the debug taps)
 hipError_t launch_untile(const bf16_t* src, bf16_t* dst, int M, int K, hipStream_t st);
+// Where the QKV projection goes beside its fp32 form: rotated queries [T][n_q * d], keys and values appended to the cache.
+struct RopeOut {
+    bf16_t* q;                 // null: not wanted
+    bf16_t* pool;              // of the layer
+    const int32_t* positions;  // [T]
+    const int32_t* slots;      // [T] cache slot (page * 16 + place)
+    const float2* cs;          // [position][d/2] (cos, sin)
+    int n_q, n_kv, d;
+};
 // qkv: fp32 partials [n_splits][T][(n_q + 2 n_kv) d] of the QKV projection (summed here)
-hipError_t launch_rope_append(const float* qkv, int n_splits, bf16_t* q_out, int T, int n_q, int n_kv, int d,
-                              const int32_t* positions, const int32_t* slots, const float* rope_cs, bf16_t* pool_slot,
-                              hipStream_t st);
+hipError_t launch_rope_append(const float* qkv, int n_splits, const RopeOut& out, int T, hipStream_t st);
 // x = resid + sum of n_splits fp32 partials [n_splits][T][H]; writes any of: x as fp32, x as bf16,
 // rmsnorm(x) * gain as bf16 (gain == null: no normalisation)
 struct ReduceAddNormArgs {
@@ -128,6 +135,7 @@ struct GemmArgs {
     void* out;         // PARTIAL_F32: fp32 [splits][M][N] row-major; SWIGLU_BF16: bf16 [M][N/2] in operand order
     size_t out_bytes;  // capacity of out; at least gemm_out_bytes(...)
     GemmOptions opt;
+    RopeOut rope;      // QKV only: where the GEMM can, it rotates and appends itself instead of writing out
     // tiled kernel only (see gemm_workspace): parked accumulators of K runs that cover part of a tile, and one counter
     // per tile that must be zero on entry (the kernel leaves it zero)
     float* sk_frag;
@@ -135,7 +143,7 @@ struct GemmArgs {
     int* sk_counters;
     int sk_n_counters;
 };
-// *n_splits receives the number of partial buffers written (1 for SWIGLU_BF16)
+// *n_splits receives the number of partial buffers written (1 for SWIGLU_BF16; 0 where rope took the product)
 hipError_t launch_gemm(const GemmArgs& a, int* n_splits, hipStream_t st);
 size_t gemm_out_bytes(int M, int N, int K, int kind, const GemmOptions& o);
 // what launch_gemm needs in sk_frag / sk_counters for this shape (both 0 unless the tiled kernel serves it)

@@ -396,6 +396,17 @@ def test_streaming_gemm_two_k_shares(tokens):
         _wreg_case(dict(hidden=1024, n_q=16, n_kv=1, head_dim=64, ffn=1024, rope_base=10000.0, n_layers=1), tokens, {"gemm_split_k": split})
 
 
+@pytest.mark.parametrize("tokens", [5, 16, 17, 33, 64, 65, 97, 160])
+def test_streaming_gemm_rotates_and_appends(tokens):
+    # QKV of head dim 64 in one split, which the GEMM itself rotates and appends: one K share (34 k-blocks; with 15 heads the last
+    # block of two column groups has one) and two (32), pairs of query, key and value heads in one block; by default where the
+    # shape gives one split (shallow, 192 heads).  Head dim 128 in one split, and what other kernels serve, rotate separately
+    for hidden, n_q, n_kv in ((1088, 8, 2), (1088, 5, 5), (1024, 14, 7), (1024, 1, 1)):
+        _wreg_case(dict(hidden=hidden, n_q=n_q, n_kv=n_kv, head_dim=64, ffn=320, rope_base=10000.0, n_layers=1), tokens, {"gemm_split_k": 1})
+    _wreg_case(dict(hidden=256, n_q=64, n_kv=64, head_dim=64, ffn=320, rope_base=10000.0, n_layers=1), tokens, {})
+    _wreg_case(dict(hidden=256, n_q=4, n_kv=1, head_dim=128, ffn=320, rope_base=10000.0, n_layers=1), tokens, {"gemm_split_k": 1})
+
+
 @pytest.mark.parametrize("chunk,splits", [(0, [1, 2, 8]), (0, [9, 16, 17]), (40, [2, 64, 65]), (40, [128, 129, 257])])
 def test_merge_groups_with_different_numbers_of_splits(chunk, splits):
     # decodes of 128 tokens per split (workers take at least four pairs of pages each) next to each other and to a chunk in few
