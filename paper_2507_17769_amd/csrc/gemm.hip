@@ -46,7 +46,7 @@ struct GemmParams {
     int kind;          // GemmOut::Kind
     void* out;         // fp32 [split][M][N] row-major, or bf16 [M][N/2] in operand order
     int kb_per_split;  // 32-wide k-blocks per block
-    RopeOut rope;      // weight streaming: q null unless this is a QKV product in one split, of head dim 64
+    RopeOut rope;      // weight streaming: q null unless this is a QKV product in one split, of head dim 64, up to 96 tokens
 };
 
 // ------------------------------------------------------------------------------------------
@@ -73,9 +73,10 @@ __device__ __forceinline__ void ws_barrier() {
     asm volatile("" ::: "memory");
 }
 
-template <int MT, int KIND, int NG, int KS>
+template <int MT, int KIND, int NG, int KS, bool ROPE = false>
 __global__ __launch_bounds__(64 * KS * (4 * NG + 1)) void gemm_wstream_kernel(GemmParams p) {
     static_assert(KS == 1 || (KS == 2 && NG == 1 && KIND == GemmOut::PARTIAL_F32), "shape");
+    static_assert(!ROPE || KIND == GemmOut::PARTIAL_F32, "shape");
     constexpr int NCW = 4 * NG;        // computing wavefronts of a K share: four per group of 64 columns, NG groups share the activation ring
     constexpr int XS = MT * 2 * 1024;  // bytes of an activation stage: MT row tiles x 2 k-blocks
     constexpr int WSETS = 4;           // weight stages in registers: three requested ahead of the one in work (a
@@ -117,11 +118,9 @@ __global__ __launch_bounds__(64 * KS * (4 * NG + 1)) void gemm_wstream_kernel(Ge
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_s_barrier();
         }
-        if constexpr (KIND == GemmOut::PARTIAL_F32) {   // likewise
-            if (KS == 2 || p.rope.q) __builtin_amdgcn_s_barrier();
-            if (KS == 2) __builtin_amdgcn_s_barrier();
-            if (p.rope.q) __builtin_amdgcn_s_barrier();
-        }
+        if constexpr (KS == 2 || ROPE) __builtin_amdgcn_s_barrier();   // likewise
+        if constexpr (KS == 2) __builtin_amdgcn_s_barrier();
+        if constexpr (ROPE) __builtin_amdgcn_s_barrier();
         return;
     }
 
@@ -211,11 +210,12 @@ __global__ __launch_bounds__(64 * KS * (4 * NG + 1)) void gemm_wstream_kernel(Ge
             for (int mt = 0; mt < MT; mt++)
                 if ((mt & 1) == share) acc[mt] += sums[(mt * NCW + wave) * 64 + lane];
         }
-        if (p.rope.q) {
+        if constexpr (ROPE) {
             // A group of 64 columns is a head: column tiles 0, 1 hold its lower half and 2, 3 what that is rotated with, so wavefronts 2
             // and 3 of a group hand their sums over.  No partial sums, no launch behind: tiny shape, 68 tokens, 8.4 -> 6.5 us.
             // (Larger products, of the two other kernels, pay for the scattered stores at their end: QKV of the 8B shape at 2048
-            // tokens 92.7 -> 113.8 us for 20.3 of rope_append.)
+            // tokens 92.7 -> 113.8 us for 20.3 of rope_append.)  A kernel of its own, up to six row tiles: in the common one the
+            // angles that are loaded ahead spill at seven and eight (O of the 8B shape at 97 tokens 14.5 -> 25 us).
             const int gi = wave / 4;
             f32x4_t* const upper = reinterpret_cast<f32x4_t*>(rings + (KS == 2 ? MT * NCW * 1024 : 0));   // [group in block][cw - 2][mt][lane]
             if (KS == 1) ws_barrier();   // the rings are free
@@ -699,7 +699,7 @@ hipError_t launch_gemm(const GemmArgs& a, int* n_splits, hipStream_t st) {
     p.A = a.A; p.Wp = a.Wp; p.M = a.M; p.N = a.N; p.K = a.K; p.kind = a.kind; p.out = a.out;
     p.kb_per_split = g.kb_per_split;
     p.rope = a.rope;
-    if (!g.wstream || g.splits != 1 || a.rope.d != 64) p.rope.q = nullptr;
+    if (!g.wstream || g.splits != 1 || a.rope.d != 64 || a.M > 96) p.rope.q = nullptr;
     if (n_splits) *n_splits = p.rope.q ? 0 : g.splits;
     if (g.wreg) return launch_gemm_wreg(a, g.wreg_plan, st);
     if (g.wstream) {
@@ -710,6 +710,22 @@ hipError_t launch_gemm(const GemmArgs& a, int* n_splits, hipStream_t st) {
         const bool two = a.kind == GemmOut::SWIGLU_BF16 || mt >= 4;
         const bool shares = g.k_shares == 2;
         const dim3 grid(two && !shares ? (a.N / 64 + 1) / 2 : a.N / 64, g.splits);
+#define PS_WS_ROPE(MT_)                                                                                                    \
+    if (shares) hipLaunchKernelGGL((gemm_wstream_kernel<MT_, GemmOut::PARTIAL_F32, 1, 2, true>), grid, dim3(640), 0, st, p);      \
+    else if (two) hipLaunchKernelGGL((gemm_wstream_kernel<MT_, GemmOut::PARTIAL_F32, 2, 1, true>), grid, dim3(576), 0, st, p);    \
+    else hipLaunchKernelGGL((gemm_wstream_kernel<MT_, GemmOut::PARTIAL_F32, 1, 1, true>), grid, dim3(320), 0, st, p);
+        if (p.rope.q) {
+            switch (mt) {
+                case 1: PS_WS_ROPE(1) break;
+                case 2: PS_WS_ROPE(2) break;
+                case 3: PS_WS_ROPE(3) break;
+                case 4: PS_WS_ROPE(4) break;
+                case 5: PS_WS_ROPE(5) break;
+                default: PS_WS_ROPE(6) break;
+            }
+            return hipGetLastError();
+        }
+#undef PS_WS_ROPE
 #define PS_WS_LAUNCH(MT_)                                                                                                  \
     if (a.kind == GemmOut::SWIGLU_BF16) hipLaunchKernelGGL((gemm_wstream_kernel<MT_, GemmOut::SWIGLU_BF16, 2, 1>), grid, dim3(576), 0, st, p); \
     else if (shares) hipLaunchKernelGGL((gemm_wstream_kernel<MT_, GemmOut::PARTIAL_F32, 1, 2>), grid, dim3(640), 0, st, p);       \

@@ -249,3 +249,11 @@ def test_no_register_is_used_while_an_lds_read_is_still_writing_it(gemm_asm, wre
             assert not bad, (m.group(1), bad[:3])
             n += 1
     assert n >= 4 + 48 + 10
+
+
+def test_weight_streaming_keeps_everything_in_registers(gemm_asm):
+    kernels = re.findall(r"\.amdhsa_kernel (\S*gemm_wstream_kernel\S*)(.*?)\.end_amdhsa_kernel", gemm_asm, re.S)
+    # ten row tiles of four forms, and one to six of the three that rotate and append
+    assert len(kernels) == 10 * 4 + 6 * 3
+    for name, body in kernels:
+        assert re.search(r"\.amdhsa_private_segment_fixed_size 0\b", body), name
