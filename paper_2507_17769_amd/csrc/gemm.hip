@@ -234,7 +234,7 @@ __global__ __launch_bounds__(64 * KS * (4 * NG + 1)) void gemm_wstream_kernel(Ge
                 if (m >= p.M || (KS == 2 && (mt & 1) != share)) continue;
                 const f32x4_t up = upper[((gi * 2 + cw) * MT + mt) * 64 + lane];
                 const float lo[4] = {acc[mt][0], acc[mt][1], acc[mt][2], acc[mt][3]}, hi[4] = {up[0], up[1], up[2], up[3]};
-                rope_store(p.rope, m, ng, j, lo, hi, rope_angles(p.rope, p.rope.positions[m], j));
+                rope_store(p.rope, m, p.rope.slots[m], ng, j, lo, hi, rope_angles(p.rope, p.rope.positions[m], j));
             }
             return;
         }

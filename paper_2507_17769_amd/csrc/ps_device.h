@@ -2,6 +2,8 @@
 #pragma once
 #include "ps_common.h"
 
+#include <type_traits>
+
 namespace ps {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
@@ -34,12 +36,24 @@ __device__ __forceinline__ uint4 ldg16_stream(const void* p) {
 
 __device__ __forceinline__ float silu_f(float z) { return z / (1.0f + __expf(-z)); }
 
+// Sum over the wavefront: rotations within each row of 16 lanes (DPP, no trip through LDS as a shuffle takes), then the four rows.
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    const auto ror = [](float x, auto n) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + decltype(n)::value, 0xf, 0xf, true));
+    };
+    v += ror(v, std::integral_constant<int, 8>{});
+    v += ror(v, std::integral_constant<int, 4>{});
+    v += ror(v, std::integral_constant<int, 2>{});
+    v += ror(v, std::integral_constant<int, 1>{});
+    const auto row = [&](int i) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16 * i)); };
+    return (row(0) + row(1)) + (row(2) + row(3));
 }
 
+
+// A word at a wavefront-uniform address that no kernel writes while this one runs, through the scalar cache.
+__device__ __forceinline__ int scalar_read(const int32_t* p) {
+    return *(const __attribute__((address_space(4))) int32_t*)p;
+}
 
 // ---- HBM -> LDS copies without a register hop, and the LDS reads that go with them -------------
 // global_load_lds writes lane l's 16 bytes at the (wavefront-uniform) LDS address + 16 l and counts

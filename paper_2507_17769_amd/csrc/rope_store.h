@@ -14,7 +14,7 @@ __device__ __forceinline__ RopeAngles rope_angles(const RopeOut& o, int position
 
 // Token t's head hh (query heads, then key, then value heads), pairs j .. j + 3 (j a multiple of 4): every value is rounded to bf16
 // once, after the rotation; queries go to q, keys and values to the token's cache slot.
-__device__ __forceinline__ void rope_store(const RopeOut& o, int t, int hh, int j, const float (&lo)[4], const float (&hi)[4], const RopeAngles& a) {
+__device__ __forceinline__ void rope_store(const RopeOut& o, int t, int slot, int hh, int j, const float (&lo)[4], const float (&hi)[4], const RopeAngles& a) {
     const int half = o.d >> 1;
     uint2 plo, phi;
     if (hh < o.n_q + o.n_kv) {
@@ -36,13 +36,11 @@ __device__ __forceinline__ void rope_store(const RopeOut& o, int t, int hh, int 
         *reinterpret_cast<uint2*>(qr + j) = plo;
         *reinterpret_cast<uint2*>(qr + j + half) = phi;
     } else if (hh < o.n_q + o.n_kv) {
-        const int slot = o.slots[t];
         bf16_t* kc = o.pool + (((size_t)(slot >> 4) * o.n_kv + (hh - o.n_q)) * 2 + 0) * (size_t)(16 * o.d);
         // j is a multiple of 4: the four elements sit in one 8-element group of the key chunk
         *reinterpret_cast<uint2*>(kc + k_elem_offset(slot & 15, j)) = plo;
         *reinterpret_cast<uint2*>(kc + k_elem_offset(slot & 15, j + half)) = phi;
     } else {
-        const int slot = o.slots[t];
         bf16_t* vc = o.pool + (((size_t)(slot >> 4) * o.n_kv + (hh - o.n_q - o.n_kv)) * 2 + 1) * (size_t)(16 * o.d);
         const uint32_t wl[2] = {plo.x, plo.y}, wh[2] = {phi.x, phi.y};
 #pragma unroll
