@@ -132,9 +132,9 @@ const char* ps_last_error(const ps_ctx* ctx);
  * KV streams are cut across, 0 = share the resident blocks between the kinds; different values cut
  * the streams in different places and must give the same results within rounding),
  * "attn_teams" (> 0: this many four-wavefront teams for the prefill query blocks of a step that also has
- * decodes, the other resident blocks streaming the decodes' KV; 0 = one per CU, more if the teams would
- * outlast the streams), "attn_prefill_weight" (what the planner charges a team for a pair of pages, in
- * units of 100 ns, when it decides whether more than one team per CU is needed; it only moves the cuts),
+ * decodes, the other resident blocks streaming the decodes' KV; 0 = one block per CU shared between the two by their work, two
+ * where the teams have long runs), "attn_prefill_weight" (what the planner charges a team for a pair of pages, in
+ * units of 100 ns, when it shares the blocks; it only moves the cuts),
  * "gemm_split_k" (0 = automatic; N = the K splits, at most 8, i.e. the fp32 partial buffers of every projection but gate/up,
  * where the kernel that serves it can be split that way),
  * "gemm_tile" (0 = automatic; 128 or 256 = block tile edge: steps of more than 64 tokens then use the tiled GEMM kernel for

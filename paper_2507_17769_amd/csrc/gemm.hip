@@ -29,7 +29,8 @@
 //    Blocks are resident once per compute unit and take whole tiles in waves; the K loops of the tiles
 //    that do not fill a wave are cut evenly over the blocks ("stream-K"), see SkParams.
 // Output is either fp32 partials [split][M][N] (one per K split; the consumer kernel sums the splits, adds the
-// residual, normalises, rotates ...) or, for the fused gate/up matrix, silu(gate) * up in bf16.
+// residual, normalises, rotates ...) or, for the fused gate/up matrix, silu(gate) * up in bf16, or, for a small QKV matrix that
+// is streamed in one split, the rotated queries and the appended keys and values themselves.
 #include "ps_device.h"
 #include "gemm_wreg.h"
 #include "rope_store.h"
