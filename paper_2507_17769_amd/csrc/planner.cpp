@@ -140,7 +140,9 @@ static void share_blocks(const PlanConfig& cfg, double pairs_team, double pairs_
         }
         // Every XCD gets the same number of either kind, rounded up, and its blocks have to be resident together: whole eighths.
         // (349 teams and 163 blocks of streams are 65 blocks on the 64 places of an XCD: 219 us where 320 and 192 take 176.)
-        t = std::min(std::min((t + 4) / 8 * 8, blocks - 8), (int)(pairs_team / 4));
+        // One eighth at least: it is set aside for any number of teams, and a chunk of a few pairs is not to wait for one team
+        // (16 pairs, 48 new tokens next to 64 decodes of 200: attention and merge 56.7 us with one team, 20.6 with four).
+        t = std::min(std::min(std::max(8, (t + 4) / 8 * 8), blocks - 8), (int)(pairs_team / 4));
         *n_team = std::max(1, t);
         *n_wave = 4 * std::max(8, blocks - (*n_team + 7) / 8 * 8);
     }

@@ -1,6 +1,6 @@
 // Checks of the attention plan on a device whose compute units are known, compiled for the host by test_host_attn_plan.py:
-// every page pair of every (decode or query block, KV head) is given out once, in order, and the blocks of either kind fit the
-// places of an XCD, however the batch is mixed.
+// every page pair of every (decode or query block, KV head) is given out once, in order, the blocks of either kind fit the
+// places of an XCD, and no team has more than its part of what eight teams would share, however the batch is mixed.
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
@@ -50,6 +50,16 @@ int main() {
         REQUIRE(per_xcd <= 64);
         REQUIRE(!cfg.one_block_per_cu || chunks == 0 || decodes == 0 || per_xcd <= 32);
         crowded += per_xcd > 32;
+        // a small chunk is spread over eight teams, or as many as there are four pairs for
+        int pairs_team = 0, longest = 0;
+        for (int w = 0; w < plan.n_team_workers; w++) {
+            int run = 0;
+            for (int i = plan.worker_begin[w]; i < plan.worker_begin[w + 1]; i++) run += (plan.items[i].page_end - plan.items[i].page_begin + 1) / 2;
+            pairs_team += run;
+            longest = std::max(longest, run);
+        }
+        const int spread = std::max(1, std::min(8, pairs_team / 4));
+        REQUIRE(longest <= (pairs_team + spread - 1) / spread + 1);
         std::map<std::tuple<int, int, int>, int> next;   // (sequence, head, query block) -> page its items have reached
         for (const AttnItem& it : plan.items) {
             int& at = next[std::make_tuple(it.seq, it.kv_head, it.q_tok0)];
