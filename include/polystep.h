@@ -268,7 +268,8 @@ ps_status ps_step_tokens(ps_ctx* ctx, const ps_seq* seqs, int32_t n_seqs, const 
  * may be null.  Same validation as ps_step (the pool-size check is skipped when no pool exists). */
 ps_status ps_step_indices(ps_ctx* ctx, const ps_seq* seqs, int32_t n_seqs, int32_t* cu_seqlens, int32_t* positions, int32_t* slot_mapping);
 
-/* The attention work list the step would launch, host only.  Each item is 8 int32:
+/* The attention work list the step would launch, host only (a context without a device plans for the 256 compute
+ * units of a whole MI355X).  Each item is 8 int32:
  * {seq index, kv head, first new-token index of its query block, number of query tokens,
  *  first KV page (logical), one past last KV page, partial slot or -1 when the item
  *  writes final output, worker}.  Items are listed worker by worker.  Query blocks of sequences with more

@@ -89,7 +89,7 @@ struct ps_ctx {
     int opt_attn_workers = 0;
     int opt_attn_teams = 0;
     int opt_attn_prefill_weight = 22;
-    int worker_slots = 2048;
+    int worker_slots = 2048;   // eight to a compute unit; without a device those of a whole MI355X
     int opt_gemm_split_k = 0;
     int opt_gemm_tile = 0;
     int opt_gemm_whole_tiles = 0;
@@ -181,7 +181,7 @@ static PlanConfig plan_config(const ps_ctx* c) {
     pc.n_teams = c->opt_attn_teams;
     pc.team_pair_ns = 100.0 * c->opt_attn_prefill_weight;
     pc.block_slots = c->worker_slots / 4;
-    pc.compute_units = c->host_only ? 0 : pc.block_slots / 2;   // two blocks to a unit
+    pc.compute_units = pc.block_slots / 2;   // two blocks to a unit
     pc.prefill_tokens = attn_prefill_tokens_per_item(pc.group);
     return pc;
 }
@@ -640,7 +640,7 @@ static ps_status make_plan(ps_ctx* c, const ps_seq* seqs, int32_t n_seqs, bool w
     build_attention_plan(pc, c->plan);
     // A step that would fit the static scratch with the partials of fewer teams gets those, whichever call runs it, so that
     // ps_step_static takes it and gives the bits of ps_step.
-    if (!c->host_only && n_seqs > 0 && c->plan.n_team_workers > pc.block_slots / 2 && static_fits(c, c->plan, false) && !static_fits(c, c->plan, true)) {
+    if (n_seqs > 0 && c->plan.n_team_workers > pc.block_slots / 2 && static_fits(c, c->plan, false) && !static_fits(c, c->plan, true)) {
         PlanConfig one = pc;
         one.one_block_per_cu = true;
         build_attention_plan(one, c->plan);
@@ -688,6 +688,7 @@ static GemmOptions gemm_options(const ps_ctx* c) {
     GemmOptions o;
     o.split_k = c->opt_gemm_split_k; o.tile = c->opt_gemm_tile; o.sk_mode = c->opt_gemm_whole_tiles;
     o.wreg = c->opt_gemm_wreg;
+    if (c->host_only) o.cus = c->worker_slots / 8;
     return o;
 }
 // The output projection of the model writes one partial buffer: it is the logits.

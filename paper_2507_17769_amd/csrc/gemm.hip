@@ -649,10 +649,12 @@ static int device_cus() {
     return cus;
 }
 
-size_t gemm_out_bytes(int M, int N, int K, int kind, const GemmOptions& o) { return gemm_plan_out_bytes(M, N, K, kind, o, device_cus()); }
+static int plan_cus(const GemmOptions& o) { return o.cus > 0 ? o.cus : device_cus(); }
+
+size_t gemm_out_bytes(int M, int N, int K, int kind, const GemmOptions& o) { return gemm_plan_out_bytes(M, N, K, kind, o, plan_cus(o)); }
 
 void gemm_workspace(int M, int N, int K, int kind, const GemmOptions& o, size_t* frag_bytes, int* n_counters) {
-    gemm_plan_workspace(M, N, K, kind, o, device_cus(), frag_bytes, n_counters);
+    gemm_plan_workspace(M, N, K, kind, o, plan_cus(o), frag_bytes, n_counters);
 }
 
 template <int BM, int BN, int NS, int KIND>

@@ -27,6 +27,7 @@ struct GemmOptions {
     // The weights-in-registers kernel takes no more K splits than the kernel that it replaces would: the partial sums then need
     // no more memory than without it.  Set for every step that a static step's scratch can hold, whichever call runs it.
     bool cap_splits = false;
+    int cus = 0;       // compute units to plan for: 0 = the current device's (contexts without a device name them)
 };
 
 // ------------------------------------------------------------------------- weights in registers (gemm_wreg.hip)

@@ -114,7 +114,7 @@ void build_indices(const ps_seq* seqs, int n_seqs, StepPlan& plan) {
 // 9 % faster in the mean than two blocks on every unit with a team on each, where the best split of a sweep gives 11.7 %;
 // 128 tokens behind 1500 next to 16 decodes 40.8 -> 33.4 us, 1024 behind 4096 next to 64 202 -> 138, 64 decodes 97 -> 93.
 static void share_blocks(const PlanConfig& cfg, double pairs_team, double pairs_wave, double pairs_per_stream, int* n_team, int* n_wave) {
-    const int B = std::max(16, cfg.block_slots), cus = cfg.compute_units > 0 ? std::min(std::max(8, cfg.compute_units), B) : B;
+    const int B = std::max(16, cfg.block_slots), cus = std::min(std::max(8, cfg.compute_units), B);
     const double long_run = 24.0 * cus;   // page pairs of the teams; without streams one / two blocks 27 / 31 us at 1200 pairs, 51 / 53 at 5900, 51 / 48 at 6400, 130 / 105 at 25600
     if (pairs_team <= 0) {
         // long streams keep HBM busy from 13 of 16 units (128 decodes of 2000 tokens 235, 225, 230, 234 us with 640, 832, 1024, 2048

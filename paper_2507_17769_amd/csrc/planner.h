@@ -34,7 +34,7 @@ struct PlanConfig {
     int n_workers = 0;         // workers of each kind; 0 = share the resident blocks between the kinds by cost
     int n_teams = 0;           // > 0: this many teams when a step has both kinds of work (0 = by cost)
     int block_slots = 512;     // blocks (of four wavefronts) of the attention kernel resident at once
-    int compute_units = 0;     // that hold them; 0 = not known: every block is taken to have one to itself
+    int compute_units = 256;   // that hold them, two each
     int prefill_tokens = 32;   // query tokens per team item (all its tiles)
     bool one_block_per_cu = false;   // at most: fewer teams, whose partials take less memory
     // what shares the blocks between the kinds (share_blocks): nanoseconds per pair of pages of a team and of a streaming wavefront

@@ -1,4 +1,4 @@
-// Checks of the attention plan on a device whose compute units are known, compiled for the host by test_host_attn_plan.py:
+// Checks of the attention plan, compiled for the host by test_host_attn_plan.py:
 // every page pair of every (decode or query block, KV head) is given out once, in order, the blocks of either kind fit the
 // places of an XCD, and no team has more than its part of what eight teams would share, however the batch is mixed.
 #include <algorithm>

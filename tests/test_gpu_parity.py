@@ -117,6 +117,17 @@ def test_split_plans_agree_and_runs_are_deterministic():
         assert rel_err(o, outs[0]) <= TOL
 
 
+@pytest.mark.parametrize("chunk,prefix,decodes", [(512, 2048, [1024] * 128), (0, 0, [700] * 64), (2048, 0, []), (48, 0, [200] * 64), (200, 8192, [1000])])
+def test_a_context_without_a_device_plans_what_the_device_launches(chunk, prefix, decodes):
+    m = W.MODELS["8b"]
+    b = W.custom_batch("8b", 17, chunk, prefix, decodes, name="plan")
+    desc = (m["hidden"], m["n_q"], m["n_kv"], m["head_dim"], m["ffn"], 1, 16384)
+    dev, host = B.Context(*desc), B.Context(*desc, host_only=True)
+    assert np.array_equal(dev.plan_attention(b.seqs), host.plan_attention(b.seqs))
+    dev.destroy()
+    host.destroy()
+
+
 def test_chunked_prefill_on_gpu_matches_one_shot_and_oracle():
     # Sec. 2.4 / 4.7: any chunking of a prompt must give the same cache and outputs
     L = 150

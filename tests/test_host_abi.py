@@ -211,8 +211,9 @@ def test_attention_plan_covers_everything_once():
         b8 = W.config_batch(cfg)
         items = _check_plan_covers(b8, c8)
         team, wave = _worker_weights(items, b8, 4)
-        # all 512 resident blocks are used: a team is one block, four single-wavefront workers share one
-        assert len(team) + len(wave) // 4 == 512 and len(wave) % 4 == 0, (len(team), len(wave))
+        # the blocks of the launch on 256 compute units: long decode streams alone on 13 of 16, a mixture on every one; a team is one
+        # block, four single-wavefront workers share one
+        assert len(team) + len(wave) // 4 == {1: 208, 2: 256}[cfg] and len(wave) % 4 == 0, (len(team), len(wave))
         assert (len(team) > 0) == (cfg == 2)
         for w in (team, wave):
             assert len(w) == 0 or w.max() - w.min() <= 2, (len(w), w.min(), w.max())

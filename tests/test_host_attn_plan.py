@@ -1,5 +1,4 @@
-"""The attention plan for a device whose compute units are known (contexts without a GPU plan for blocks alone), checked on the
-host over random mixtures of chunks and decodes."""
+"""The attention plan checked on the host over random mixtures of chunks and decodes."""
 import os
 import subprocess
 
