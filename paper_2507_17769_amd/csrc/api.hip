@@ -640,7 +640,7 @@ static ps_status make_plan(ps_ctx* c, const ps_seq* seqs, int32_t n_seqs, bool w
     build_attention_plan(pc, c->plan);
     // A step that would fit the static scratch with the partials of fewer teams gets those, whichever call runs it, so that
     // ps_step_static takes it and gives the bits of ps_step.
-    if (n_seqs > 0 && c->plan.n_team_workers > pc.block_slots / 2 && static_fits(c, c->plan, false) && !static_fits(c, c->plan, true)) {
+    if (c->plan.two_blocks_per_cu && static_fits(c, c->plan, false) && !static_fits(c, c->plan, true)) {
         PlanConfig one = pc;
         one.one_block_per_cu = true;
         build_attention_plan(one, c->plan);

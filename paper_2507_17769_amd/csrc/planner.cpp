@@ -102,7 +102,7 @@ void build_indices(const ps_seq* seqs, int n_seqs, StepPlan& plan) {
 }
 
 // Blocks of the attention launch: how many work as teams and how many wavefronts stream.  pairs_*: page pairs of either pool, and of
-// a decode and KV head in the mean.
+// a decode and KV head in the mean.  Returns whether compute units get a second block by the rule below.
 //
 // A compute unit holds two blocks, but a second one mostly does not pay: two teams on a unit take 1.8 us per pair of pages where
 // one takes 1.2, a team slows down beside streaming wavefronts, and twice the workers leave twice the partials to merge, while
@@ -113,7 +113,7 @@ void build_indices(const ps_seq* seqs, int n_seqs, StepPlan& plan) {
 // Measured with the merge on 170 mixtures (17 to 1600 new tokens behind up to 6000 next to 1 to 256 decodes, both large shapes):
 // 9 % faster in the mean than two blocks on every unit with a team on each, where the best split of a sweep gives 11.7 %;
 // 128 tokens behind 1500 next to 16 decodes 40.8 -> 33.4 us, 1024 behind 4096 next to 64 202 -> 138, 64 decodes 97 -> 93.
-static void share_blocks(const PlanConfig& cfg, double pairs_team, double pairs_wave, double pairs_per_stream, int* n_team, int* n_wave) {
+static bool share_blocks(const PlanConfig& cfg, double pairs_team, double pairs_wave, double pairs_per_stream, int* n_team, int* n_wave) {
     const int B = std::max(16, cfg.block_slots), cus = std::min(std::max(8, cfg.compute_units), B);
     const double long_run = 24.0 * cus;   // page pairs of the teams; without streams one / two blocks 27 / 31 us at 1200 pairs, 51 / 53 at 5900, 51 / 48 at 6400, 130 / 105 at 25600
     if (pairs_team <= 0) {
@@ -122,6 +122,7 @@ static void share_blocks(const PlanConfig& cfg, double pairs_team, double pairs_
         *n_wave = 4 * (cus < B && pairs_per_stream >= 24 ? 13 * cus / 16 : cus);
     } else if (pairs_wave <= 0) {
         *n_team = pairs_team < long_run ? cus : B;
+        return *n_team > cus;
     } else if (cfg.n_teams > 0) {
         *n_team = std::min(cfg.n_teams, B - 1);
         *n_wave = 4 * (B - *n_team);
@@ -145,7 +146,9 @@ static void share_blocks(const PlanConfig& cfg, double pairs_team, double pairs_
         t = std::min(std::min(std::max(8, (t + 4) / 8 * 8), blocks - 8), (int)(pairs_team / 4));
         *n_team = std::max(1, t);
         *n_wave = 4 * std::max(8, blocks - (*n_team + 7) / 8 * 8);
+        return blocks > cus;
     }
+    return false;
 }
 
 // Attention plan.  The KV stream of every (sequence, kv head, query block) is a segment of page
@@ -166,6 +169,7 @@ void build_attention_plan(const PlanConfig& cfg, StepPlan& plan) {
     plan.n_partial_slots = 0;
     plan.n_partial_items = 0;
     plan.n_team_workers = 0;
+    plan.two_blocks_per_cu = false;
     const int TQ = 16 / cfg.group;                 // tokens per 16-row query tile
     const int multi_nt = cfg.prefill_tokens / TQ;  // tiles a team item always reserves
     const int W_SINGLE = 2, W_MULTI = 3;           // nominal weight of a page pair (the pools are cut separately)
@@ -198,8 +202,8 @@ void build_attention_plan(const PlanConfig& cfg, StepPlan& plan) {
         n_team = segs_team.empty() ? 0 : cfg.n_workers;
         n_wave = segs_wave.empty() ? 0 : cfg.n_workers;
     } else {
-        share_blocks(cfg, (double)units_team / W_MULTI, (double)units_wave / W_SINGLE, segs_wave.empty() ? 0.0 : (double)units_wave / W_SINGLE / (segs_wave.size() * cfg.n_kv_heads),
-                     &n_team, &n_wave);
+        plan.two_blocks_per_cu = share_blocks(cfg, (double)units_team / W_MULTI, (double)units_wave / W_SINGLE,
+                                              segs_wave.empty() ? 0.0 : (double)units_wave / W_SINGLE / (segs_wave.size() * cfg.n_kv_heads), &n_team, &n_wave);
     }
     // do not spread thinner than ~4 page pairs per worker
     if (n_team > 0) n_team = (int)std::max<int64_t>(1, std::min<int64_t>(n_team, units_team / (4 * W_MULTI)));

@@ -21,6 +21,7 @@ struct StepPlan {
     std::vector<int32_t> worker_begin;  // [n_workers + 1]; the first n_team_workers workers are teams (blocks of four
                                         // wavefronts), the others single wavefronts
     int n_team_workers = 0;
+    bool two_blocks_per_cu = false;     // the teams' runs were long enough for it (never with cfg.one_block_per_cu)
     std::vector<MergeGroup> groups;
     int n_partial_slots = 0;
     int n_partial_items = 0;

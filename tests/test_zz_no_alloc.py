@@ -107,3 +107,31 @@ def test_static_step_8b_layer_runs_the_kernels_of_ps_step_also_where_scratch_is_
             eng.close()
     finally:
         del W.MODELS["_s"]
+
+
+def _random_cache(eng, n_pages):
+    """N(0, 1) keys and values in every page of layer 0."""
+    m = eng.model
+    gen = torch.Generator(device=eng.device)
+    gen.manual_seed(n_pages)
+    k, v = (torch.randn((16 * n_pages, m["n_kv"], m["head_dim"]), generator=gen, device=eng.device).to(torch.bfloat16) for _ in range(2))
+    eng.ctx.kv_write(0, np.arange(n_pages, dtype=np.int32), 0, 16 * n_pages, k.data_ptr(), v.data_ptr())
+    eng.ctx.sync()
+
+
+@pytest.mark.parametrize("chunk,prefix,decodes,blocks", [(128, 8192, [1000] * 4, 1), (128, 8192, [2000] * 32, 1)])
+def test_static_step_8b_layer_of_a_chunk_behind_a_long_prefix(chunk, prefix, decodes, blocks):
+    """Chunks whose attention plan has two blocks on a compute unit, 480 teams and exactly as many teams as compute units, and
+    leaves partials that the array cannot hold: both calls run the plan with one block instead."""
+    b = W.custom_batch("8b", 7, chunk, prefix, decodes, name="long")
+    eng = Engine(b.model, b.n_pool_pages, 1, 1, max_position=prefix + chunk + 16)
+    eng.n_kv_layers = 1
+    eng.load_layer(0, W.layer_weights(b.model, 7, 0))
+    try:
+        items = eng.ctx.plan_attention(b.seqs)
+        team = {w for q0, w in zip(items[:, 0], items[:, 7]) if q0 == 0}   # the chunk is the first sequence
+        assert (len(team) + (items[:, 7].max() + 1 - len(team) + 3) // 4 + 255) // 256 == blocks
+        _random_cache(eng, b.n_pool_pages)
+        _assert_same(_both_ways(eng, b, b.activations()), f"{chunk} tokens behind {prefix}, {len(decodes)} decodes")
+    finally:
+        eng.close()
