@@ -628,7 +628,8 @@ extern "C" ps_status ps_kv_read(ps_ctx* c, int32_t layer, const ps_seq* seq, int
 }
 
 // ------------------------------------------------------------------------------ planning
-static bool static_fits(const ps_ctx* c, const StepPlan& p, bool with_partials);
+static bool static_fits(const ps_ctx* c, const StepPlan& p);
+static bool static_fits_without_partials(const ps_ctx* c, const StepPlan& p);
 
 static ps_status make_plan(ps_ctx* c, const ps_seq* seqs, int32_t n_seqs, bool with_attention) {
     const PlanConfig pc = plan_config(c);
@@ -638,13 +639,13 @@ static ps_status make_plan(ps_ctx* c, const ps_seq* seqs, int32_t n_seqs, bool w
     build_indices(seqs, n_seqs, c->plan);
     if (!with_attention) return PS_OK;
     build_attention_plan(pc, c->plan);
-    // A step that would fit the static scratch with the partials of fewer teams gets those, whichever call runs it, so that
-    // ps_step_static takes it and gives the bits of ps_step.
-    if (c->plan.two_blocks_per_cu && static_fits(c, c->plan, false) && !static_fits(c, c->plan, true)) {
+    // A step whose partials the static scratch cannot hold even so (see step_static_layout), but could hold those of one block per
+    // compute unit, gets those, whichever call runs it, so that ps_step_static takes it and gives the bits of ps_step.
+    if (c->plan.two_blocks_per_cu && static_fits_without_partials(c, c->plan) && !static_fits(c, c->plan)) {
         PlanConfig one = pc;
         one.one_block_per_cu = true;
         build_attention_plan(one, c->plan);
-        if (!static_fits(c, c->plan, true)) build_attention_plan(pc, c->plan);
+        if (!static_fits(c, c->plan)) build_attention_plan(pc, c->plan);
     }
     return PS_OK;
 }
@@ -844,7 +845,9 @@ struct StaticLayout {
     size_t act_bytes, part_bytes, skfrag_bytes;
     int skcnt_n;
 };
-static StaticLayout static_layout(const ps_ctx* c, int T, int n_part_slots, size_t meta_bytes, const GemmOptions& o) {
+// partials_shared: the attention partials, which live from the attention launch to its merge, lie over what only the projections
+// use, none of which runs in between (the counters of the tiled GEMM keep a place of their own: they have to stay zero).
+static StaticLayout static_layout(const ps_ctx* c, int T, int n_part_slots, size_t meta_bytes, const GemmOptions& o, bool partials_shared) {
     const ps_model_desc& d = c->desc;
     const int H = d.hidden, F = d.ffn, NQ = d.n_q_heads * d.head_dim, NQKV = qkv_cols(d);
     const size_t T16 = (size_t)((T + 15) & ~15);
@@ -852,28 +855,25 @@ static StaticLayout static_layout(const ps_ctx* c, int T, int n_part_slots, size
     size_t at = 0;
     auto take = [&](size_t bytes) { const size_t r = at; at = (at + bytes + 255) & ~(size_t)255; return r; };
     m.xn = take(T16 * H * 2); m.q = take((size_t)T * NQ * 2); m.attn = take(T16 * NQ * 2);
-    m.act_bytes = gemm_out_bytes(T, 2 * F, H, GemmOut::SWIGLU_BF16, o);
-    m.act = take(m.act_bytes); m.x1 = take((size_t)T * H * 4); m.xmid = take(d.n_layers > 1 ? (size_t)T * H * 4 : 0);
-    m.part_bytes = gemm_out_bytes(T, NQKV, H, GemmOut::PARTIAL_F32, o);
-    m.part_bytes = std::max(m.part_bytes, gemm_out_bytes(T, H, NQ, GemmOut::PARTIAL_F32, o));
-    m.part_bytes = std::max(m.part_bytes, gemm_out_bytes(T, H, F, GemmOut::PARTIAL_F32, o));
-    m.part = take(m.part_bytes);
-    m.part_o = take((size_t)n_part_slots * 16 * d.head_dim * 4); m.part_ml = take((size_t)n_part_slots * 16 * 2 * 4);
+    m.x1 = take((size_t)T * H * 4); m.xmid = take(d.n_layers > 1 ? (size_t)T * H * 4 : 0);
     m.meta = take(meta_bytes);
     int n_cnt = 0;
     sk_need(c, T, 0, o, &m.skfrag_bytes, &n_cnt);
     m.skcnt_n = (n_cnt + 3) & ~3;
-    m.skfrag = take(m.skfrag_bytes); m.skcnt = take((size_t)m.skcnt_n * sizeof(int));
-    m.total = at;
+    m.skcnt = take((size_t)m.skcnt_n * sizeof(int));
+    const size_t shared = at;
+    m.part_o = take((size_t)n_part_slots * 16 * d.head_dim * 4); m.part_ml = take((size_t)n_part_slots * 16 * 2 * 4);
+    const size_t partials_end = at;
+    if (partials_shared) at = shared;
+    m.act_bytes = gemm_out_bytes(T, 2 * F, H, GemmOut::SWIGLU_BF16, o);
+    m.act = take(m.act_bytes);
+    m.part_bytes = gemm_out_bytes(T, NQKV, H, GemmOut::PARTIAL_F32, o);
+    m.part_bytes = std::max(m.part_bytes, gemm_out_bytes(T, H, NQ, GemmOut::PARTIAL_F32, o));
+    m.part_bytes = std::max(m.part_bytes, gemm_out_bytes(T, H, F, GemmOut::PARTIAL_F32, o));
+    m.part = take(m.part_bytes);
+    m.skfrag = take(m.skfrag_bytes);
+    m.total = std::max(at, partials_end);
     return m;
-}
-
-// Whether the static scratch holds a step's buffers (with_partials: those of the attention splits, and the metadata, too).
-static bool static_fits(const ps_ctx* c, const StepPlan& p, bool with_partials) {
-    GemmOptions o = gemm_options(c);
-    o.cap_splits = true;
-    const size_t meta = with_partials ? meta_layout(p, false).total : 0;
-    return meta <= STATIC_META_SLOT && static_layout(c, p.n_tokens, with_partials ? p.n_partial_slots : 0, meta, o).total <= (size_t)PS_STATIC_SCRATCH_BYTES;
 }
 
 // GEMM options of a step's layers.  A function of the batch and the options of the context alone, not of the call: a batch
@@ -881,16 +881,37 @@ static bool static_fits(const ps_ctx* c, const StepPlan& p, bool with_partials) 
 static GemmOptions layer_gemm_options(const ps_ctx* c, const StepPlan& p) {
     GemmOptions o = gemm_options(c);
     o.cap_splits = true;
-    o.cap_splits = static_layout(c, p.n_tokens, p.n_partial_slots, meta_layout(p, false).total, o).total <= (size_t)PS_STATIC_SCRATCH_BYTES;
+    o.cap_splits = static_layout(c, p.n_tokens, p.n_partial_slots, meta_layout(p, false).total, o, false).total <= (size_t)PS_STATIC_SCRATCH_BYTES;
     return o;
 }
 
+// The layout of a static step.  Where its buffers do not fit side by side, the partials of a plan with two blocks on a compute
+// unit, twice those of one, share their place: the plan stays what is fastest for ps_step, which has to run the same one.
+static StaticLayout step_static_layout(const ps_ctx* c, const StepPlan& p, size_t meta_bytes, const GemmOptions& o) {
+    const StaticLayout m = static_layout(c, p.n_tokens, p.n_partial_slots, meta_bytes, o, false);
+    if (m.total <= (size_t)PS_STATIC_SCRATCH_BYTES || !p.two_blocks_per_cu) return m;
+    return static_layout(c, p.n_tokens, p.n_partial_slots, meta_bytes, o, true);
+}
+
+// Whether a plan with fewer partials could make the step fit.
+static bool static_fits_without_partials(const ps_ctx* c, const StepPlan& p) {
+    GemmOptions o = gemm_options(c);
+    o.cap_splits = true;
+    return static_layout(c, p.n_tokens, 0, 0, o, false).total <= (size_t)PS_STATIC_SCRATCH_BYTES;
+}
+
+// Whether ps_step_static takes a step with this plan.
+static bool static_fits(const ps_ctx* c, const StepPlan& p) {
+    const size_t meta = meta_layout(p, false).total;
+    return meta <= STATIC_META_SLOT && step_static_layout(c, p, meta, layer_gemm_options(c, p)).total <= (size_t)PS_STATIC_SCRATCH_BYTES;
+}
+
 // The buffers of a static step.  Nothing is allocated: a step whose buffers do not fit PS_STATIC_SCRATCH_BYTES is refused.
-static ps_status carve_static(ps_ctx* c, int T, int n_part_slots, size_t meta_bytes, StepBufs* w) {
+static ps_status carve_static(ps_ctx* c, const StepPlan& p, size_t meta_bytes, StepBufs* w) {
     if (meta_bytes > STATIC_META_SLOT)
         return fail(c, PS_ERANGE, "ps_step_static: the step's metadata (" + std::to_string(meta_bytes) + " bytes: positions, page lists, attention work list) exceeds " +
                                       std::to_string(STATIC_META_SLOT) + " bytes; use ps_step for batches of this size");
-    const StaticLayout m = static_layout(c, T, n_part_slots, meta_bytes, w->gemm);
+    const StaticLayout m = step_static_layout(c, p, meta_bytes, w->gemm);
     if (m.total > (size_t)PS_STATIC_SCRATCH_BYTES)
         return fail(c, PS_ERANGE, "ps_step_static: the step needs " + std::to_string(m.total) + " bytes of scratch, the static array holds " +
                                       std::to_string((size_t)PS_STATIC_SCRATCH_BYTES) + "; use ps_step for batches of this size");
@@ -946,7 +967,7 @@ static ps_status step_impl(ps_ctx* c, const ps_seq* seqs, int32_t n_seqs, const 
     StepBufs W;
     W.gemm = layer_gemm_options(c, p);
     if (use_static) {
-        if ((st = carve_static(c, T, p.n_partial_slots, ml.total, &W)) != PS_OK) return st;
+        if ((st = carve_static(c, p, ml.total, &W)) != PS_OK) return st;
     } else {
         if ((st = ensure_workspaces(c, T, p.n_partial_slots, tio ? p.n_seqs : 0, W.gemm)) != PS_OK) return st;
         W.xn = c->ws_xn; W.q = c->ws_q; W.attn = c->ws_attn; W.act = c->ws_act; W.x1 = c->ws_x1; W.xmid = c->ws_xmid;

@@ -110,28 +110,37 @@ def test_static_step_8b_layer_runs_the_kernels_of_ps_step_also_where_scratch_is_
 
 
 def _random_cache(eng, n_pages):
-    """N(0, 1) keys and values in every page of layer 0."""
+    """N(0, 1) keys and values in every page of every layer."""
     m = eng.model
     gen = torch.Generator(device=eng.device)
     gen.manual_seed(n_pages)
-    k, v = (torch.randn((16 * n_pages, m["n_kv"], m["head_dim"]), generator=gen, device=eng.device).to(torch.bfloat16) for _ in range(2))
-    eng.ctx.kv_write(0, np.arange(n_pages, dtype=np.int32), 0, 16 * n_pages, k.data_ptr(), v.data_ptr())
-    eng.ctx.sync()
+    for layer in range(eng.n_kv_layers):
+        k, v = (torch.randn((16 * n_pages, m["n_kv"], m["head_dim"]), generator=gen, device=eng.device).to(torch.bfloat16) for _ in range(2))
+        eng.ctx.kv_write(layer, np.arange(n_pages, dtype=np.int32), 0, 16 * n_pages, k.data_ptr(), v.data_ptr())
+        eng.ctx.sync()
 
 
-@pytest.mark.parametrize("chunk,prefix,decodes,blocks", [(128, 8192, [1000] * 4, 1), (128, 8192, [2000] * 32, 1)])
-def test_static_step_8b_layer_of_a_chunk_behind_a_long_prefix(chunk, prefix, decodes, blocks):
-    """Chunks whose attention plan has two blocks on a compute unit, 480 teams and exactly as many teams as compute units, and
-    leaves partials that the array cannot hold: both calls run the plan with one block instead."""
-    b = W.custom_batch("8b", 7, chunk, prefix, decodes, name="long")
-    eng = Engine(b.model, b.n_pool_pages, 1, 1, max_position=prefix + chunk + 16)
-    eng.n_kv_layers = 1
-    eng.load_layer(0, W.layer_weights(b.model, 7, 0))
+@pytest.mark.parametrize("chunks,decodes,blocks", [
+    ([(128, 8192)], [1000] * 4, 2),      # 480 teams
+    ([(128, 8192)], [2000] * 32, 2),     # as many teams as compute units, and as many blocks of streams
+    ([(150, 8192)], [], 2),              # 512 teams
+    ([(5, 4000)] * 20, [500], 1),        # the partials of two blocks fit nowhere
+])
+def test_static_step_8b_layers_of_chunks_behind_long_prefixes(chunks, decodes, blocks):
+    """Chunks with runs long enough for two blocks on a compute unit, whose partials do not fit beside the other buffers: they lie
+    over those that only the projections use or, if that is not enough, the plan has one block per unit.  Two layers, so that the
+    shared place is used by either side in turn."""
+    b = W.multi_batch("8b", 7, chunks, decodes, name="long")
+    eng = Engine(b.model, b.n_pool_pages, 2, 2, max_position=max(s.kv_len for s in b.seqs) + 16)
+    eng.n_kv_layers = 2
+    for layer in range(2):
+        eng.load_layer(layer, W.layer_weights(b.model, 7, layer))
     try:
         items = eng.ctx.plan_attention(b.seqs)
-        team = {w for q0, w in zip(items[:, 0], items[:, 7]) if q0 == 0}   # the chunk is the first sequence
-        assert (len(team) + (items[:, 7].max() + 1 - len(team) + 3) // 4 + 255) // 256 == blocks
+        n_team = len(set(items[items[:, 0] < len(chunks), 7].tolist()))
+        assert (n_team + (int(items[:, 7].max()) + 1 - n_team + 3) // 4 + 255) // 256 == blocks
         _random_cache(eng, b.n_pool_pages)
-        _assert_same(_both_ways(eng, b, b.activations()), f"{chunk} tokens behind {prefix}, {len(decodes)} decodes")
+        eng.ctx.set_option("poison_workspaces", 1)
+        _assert_same(_both_ways(eng, b, b.activations()), f"{chunks} {len(decodes)} decodes")
     finally:
         eng.close()
