@@ -121,7 +121,7 @@ static bool share_blocks(const PlanConfig& cfg, double pairs_team, double pairs_
         // wavefronts; 64 of 2100 97, 93, 94, 96), short ones, several to a wavefront, take all (183 of 250 tokens 49, 45, 43, 44)
         *n_wave = 4 * (cus < B && pairs_per_stream >= 24 ? 13 * cus / 16 : cus);
     } else if (pairs_wave <= 0) {
-        *n_team = pairs_team < long_run ? cus : B;
+        *n_team = pairs_team < long_run || cfg.one_block_per_cu ? cus : B;
         return *n_team > cus;
     } else if (cfg.n_teams > 0) {
         *n_team = std::min(cfg.n_teams, B - 1);

@@ -48,7 +48,7 @@ int main() {
         // places of an XCD: 32 compute units of two blocks each
         const int per_xcd = (plan.n_team_workers + 7) / 8 + ((workers - plan.n_team_workers + 3) / 4 + 7) / 8;
         REQUIRE(per_xcd <= 64);
-        REQUIRE(!cfg.one_block_per_cu || chunks == 0 || decodes == 0 || per_xcd <= 32);
+        REQUIRE(!cfg.one_block_per_cu || per_xcd <= 32);
         crowded += per_xcd > 32;
         // a small chunk is spread over eight teams, or as many as there are four pairs for
         int pairs_team = 0, longest = 0;

@@ -125,6 +125,7 @@ def _random_cache(eng, n_pages):
     ([(128, 8192)], [2000] * 32, 2),     # as many teams as compute units, and as many blocks of streams
     ([(150, 8192)], [], 2),              # 512 teams
     ([(5, 4000)] * 20, [500], 1),        # the partials of two blocks fit nowhere
+    ([(5, 4000)] * 20, [], 1),
 ])
 def test_static_step_8b_layers_of_chunks_behind_long_prefixes(chunks, decodes, blocks):
     """Chunks with runs long enough for two blocks on a compute unit, whose partials do not fit beside the other buffers: they lie
