@@ -298,6 +298,12 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
     return r;
 }
 
+// a * b, rounded, whatever it is added to (the compiler would make an fma of it)
+__device__ __forceinline__ float rounded_product(float a, float b) {
+#pragma clang fp contract(off)
+    return a * b;
+}
+
 // Softmax update of one query tile for a pair of pages: raw scores sa (page a, keys 4g..4g+3 of this lane's query row) and
 // sb (page b) -> P as a packed B operand, reference maximum updated, alpha = the factor the accumulators take.  The row
 // sums are not taken here: the matrix unit adds up the rounded P it multiplies V with (see team_pair), so that the
@@ -315,9 +321,11 @@ __device__ __forceinline__ bf16x8_t team_softmax(const f32x4_t& sa, const f32x4_
     // The reference is the exact running maximum, so a row's largest P is exactly 1 and carries no rounding error into
     // P.V.  (A reference that follows lazily, moving only after the maximum has grown by some factor, saves most of the
     // accumulator rescaling: measured 6 % faster on long prefixes, with 10 % more rounding error in the layer's output.)
-    alpha = __builtin_amdgcn_exp2f((m - mx) * scale2);
+    // In the exponent's units it is rounded once (ms), and what came before is rescaled between two such numbers: the weights of
+    // all pairs then carry the same rounding, which at large scores is that of the reference and not small (5e5: 3 % of a weight).
+    const float ms = rounded_product(mx, scale2);
+    alpha = __builtin_amdgcn_exp2f(rounded_product(m, scale2) - ms);
     m = mx;
-    const float ms = mx * scale2;
     float pv[8];
 #pragma unroll
     for (int i = 0; i < 8; i++) pv[i] = __builtin_amdgcn_exp2f(fmaf(sv[i], scale2, -ms));
@@ -522,7 +530,7 @@ __device__ __forceinline__ void team_item(const AttnArgs& a, const AttnItem it, 
 #pragma unroll
     for (int nt = 0; nt < NT; nt++) {
         st.lsum[nt] = lacc[nt][0];
-        st.m[nt] *= scale2;   // the merge works in the exponent's units
+        st.m[nt] = rounded_product(st.m[nt], scale2);   // the merge works in the exponent's units
         rvalid[nt] = tok_row + nt * TQ < it.q_ntok;
         qi[nt] = it.tok_g0 + min(tok_row + nt * TQ, it.q_ntok - 1);
     }

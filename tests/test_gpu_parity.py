@@ -10,6 +10,7 @@ import torch
 from paper_2507_17769_amd import binding as B
 from paper_2507_17769_amd import workloads as W
 from gpu_harness import TOL, Case, bits_to_dev, dev_to_bits, f32, rel_err
+from oracle.bf16 import to_bits
 from paper_2507_17769_amd.runner import Engine
 
 pytestmark = pytest.mark.gpu
@@ -126,6 +127,48 @@ def test_a_context_without_a_device_plans_what_the_device_launches(chunk, prefix
     assert np.array_equal(dev.plan_attention(b.seqs), host.plan_attention(b.seqs))
     dev.destroy()
     host.destroy()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_team_softmax_weights_at_large_scores(d):
+    """Scores of some 5e5 in units of the exponent, where one rounding of the reference maximum is 3 % of a weight, that grow by
+    less than one from one pair of pages to the next.  The reference a pair's weights are taken against and the rescaling of what
+    came before must round alike.  Scores are exact: every query is 1024 and 1 in the two slowest dimensions (which a base of 1e30
+    does not rotate), the keys of pair p are 4096 and 2p there and zero elsewhere, the values of pair p are one in dimension p.
+    Left to differ by are the weights' bf16 rounding, 2^-8 of each and of their sum, and the output's: 2.5 x 2^-8."""
+    model = dict(hidden=256, n_q=4, n_kv=1, head_dim=d, ffn=320, rope_base=1e30, n_layers=1)
+    n_new, pairs = 48, 16
+    W.MODELS["_s"] = model
+    try:
+        b = W.custom_batch("_s", 1, n_new, 32 * pairs, [], name="scores")
+        w = W.layer_weights(model, 1)
+    finally:
+        del W.MODELS["_s"]
+    bits = lambda a: to_bits(np.asarray(a, dtype=np.float32))
+    qkv = np.zeros((256, 6, d), dtype=np.float32)
+    qkv[0, :4, d // 2 - 1], qkv[0, :4, d // 2 - 2] = 1024.0, 1.0
+    w["w_qkv"] = bits(qkv.reshape(256, 6 * d))
+    k, v = (np.zeros((32 * pairs, 1, d), dtype=np.float32) for _ in range(2))
+    pair = np.arange(32 * pairs) // 32
+    k[:, 0, d // 2 - 1], k[:, 0, d // 2 - 2] = 4096.0, 2.0 * pair
+    v[np.arange(32 * pairs), 0, pair] = 1.0
+    eng = Engine(model, b.n_pool_pages, 1, 1, max_position=32 * pairs + 64)
+    eng.ctx.set_option("attn_workers", 1)      # one team goes through all pairs
+    eng.load_layer(0, w)
+    eng.write_kv(0, b.seqs[0].pages, 0, bits(k), bits(v))
+    taps = eng.alloc_taps(n_new)
+    eng.ctx.set_taps(0, q=taps["q"].data_ptr(), attn=taps["attn"].data_ptr())
+    eng.step(b.seqs, bits_to_dev(bits(np.ones((n_new, 256))), eng.device))
+    eng.ctx.sync()
+    q, got = f32(dev_to_bits(taps["q"])), f32(dev_to_bits(taps["attn"])).astype(np.float64).reshape(n_new, 4, d)
+    eng.close()
+    assert (q[:, :, d // 2 - 1] == 1024).all() and (q[:, :, d // 2 - 2] == 1).all()
+    score = 2.0 * np.arange(pairs) / np.sqrt(d)
+    want = np.exp(score - score.max())
+    want /= want.sum()
+    rel = np.abs(got[:, :, :pairs] / want - 1.0).max()
+    assert rel <= 2.5 * 2.0 ** -8, rel
+    assert not got[:, :, pairs:].any()
 
 
 def test_chunked_prefill_on_gpu_matches_one_shot_and_oracle():
