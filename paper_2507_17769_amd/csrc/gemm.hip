@@ -712,6 +712,8 @@ hipError_t launch_gemm(const GemmArgs& a, int* n_splits, hipStream_t st) {
         // tokens: 54 -> 49 us), a gain for the split projections from four row tiles on, a loss below.
         const bool two = a.kind == GemmOut::SWIGLU_BF16 || mt >= 4;
         const bool shares = g.k_shares == 2;
+        // every share takes whole stages of two k-blocks and the same number of them
+        if (a.K / 32 % (2 * g.k_shares) || g.kb_per_split % (2 * g.k_shares)) return hipErrorInvalidValue;
         const dim3 grid(two && !shares ? (a.N / 64 + 1) / 2 : a.N / 64, g.splits);
 #define PS_WS_ROPE(MT_)                                                                                                    \
     if (shares) hipLaunchKernelGGL((gemm_wstream_kernel<MT_, GemmOut::PARTIAL_F32, 1, 2, true>), grid, dim3(640), 0, st, p);      \

@@ -222,7 +222,7 @@ inline GemmPlan plan_gemm(int M, int N, int K, int kind, const GemmOptions& o, i
         // Longer runs lose: O of the 70B shape 28.0 / 28.9 at 16 tokens, down of the 8B shape 28.4 / 29.9 at 64.
         if (kind != GemmOut::SWIGLU_BF16 && KB % 4 == 0 && (KB + s - 1) / s <= 24 && (N <= K || (M > 32 && (M <= 64 || !wide)))) {
             g.k_shares = 2;
-            if (split_opt == 0) s = std::max(1, std::min(s, (192 + groups / 2) / groups));
+            if (split_opt == 0) s = std::max(1, std::min(s, (3 * cus / 4 + groups / 2) / groups));
         }
         int kps = (KB + s - 1) / s;
         kps = (kps + 2 * g.k_shares - 1) / (2 * g.k_shares) * (2 * g.k_shares);  // whole stages of two k-blocks for every share

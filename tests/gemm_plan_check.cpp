@@ -10,11 +10,13 @@ using namespace ps;
 
 struct Shape { int N, K, kind; };
 constexpr int P = GemmOut::PARTIAL_F32, G = GemmOut::SWIGLU_BF16;
-// QKV, O, gate/up, down of the 8B shape, the 70B shape, the tiny one and one whose K loops divide evenly nowhere
+// QKV, O, gate/up, down of the 8B shape, the 70B shape, the tiny one and one whose K loops divide evenly nowhere; some whose
+// k-blocks are two more than a multiple of four
 const Shape shapes[] = {{6144, 4096, P}, {4096, 4096, P}, {28672, 4096, G}, {4096, 14336, P},
                         {10240, 8192, P}, {8192, 8192, P}, {57344, 8192, G}, {8192, 28672, P},
                         {512, 256, P}, {256, 256, P}, {1408, 256, G}, {256, 704, P},
-                        {3456, 1152, P}, {1152, 1152, P}, {6400, 1152, G}, {1152, 3200, P}};
+                        {3456, 1152, P}, {1152, 1152, P}, {6400, 1152, G}, {1152, 3200, P},
+                        {1344, 1088, P}, {1088, 1088, P}, {1088, 960, P}, {320, 704, P}};
 
 static int n_checked = 0;
 #define REQUIRE(cond)                                                                                                              \
@@ -33,6 +35,13 @@ static void check(int M, const Shape& s, const GemmOptions& o, int cus) {
         REQUIRE(16 * w.tm * (w.row_tiles - 1) < M);   // no row block without a row
     } else {
         REQUIRE((g.splits - 1) * g.kb_per_split < s.K / 32 && g.splits * g.kb_per_split >= s.K / 32);
+    }
+    // Whole stages of two k-blocks for every K share of a block, in the last split too: what is over would be left out.
+    if (g.wstream) {
+        REQUIRE(g.k_shares == 1 || (g.k_shares == 2 && s.kind == P));
+        REQUIRE(s.K / 32 % (2 * g.k_shares) == 0 && g.kb_per_split % (2 * g.k_shares) == 0);
+    } else {
+        REQUIRE(g.k_shares == 1);
     }
     // what the buffers hold is what the plan writes
     if (s.kind == P) REQUIRE(gemm_plan_out_bytes(M, s.N, s.K, s.kind, o, cus) == (size_t)g.splits * M * s.N * 4);
