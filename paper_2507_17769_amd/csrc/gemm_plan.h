@@ -218,9 +218,14 @@ inline GemmPlan plan_gemm(int M, int N, int K, int kind, const GemmOptions& o, i
         // the weights: two K shares inside a block add up through LDS, and three quarters as many blocks as compute units
         // take the place of two each.  Measured with the kernel behind it (us, one share in 8 splits / two shares in 3): O of the 8B
         // shape 13.5 / 12.5 at 8 tokens, 18.1 / 16.0 at 64, 21.9 / 19.3 at 97, 24.6 / 21.5 at 144; QKV up to 32 tokens 11.4 /
-        // 12.6, from there on 16.4 / 16.3 with a third of the partial sums; of the tiny shape each product 0.4 to 0.6 less.
-        // Longer runs lose: O of the 70B shape 28.0 / 28.9 at 16 tokens, down of the 8B shape 28.4 / 29.9 at 64.
-        if (kind != GemmOut::SWIGLU_BF16 && KB % 4 == 0 && (KB + s - 1) / s <= 24 && (N <= K || (M > 32 && (M <= 64 || !wide)))) {
+        // 12.6, from there on 16.4 / 16.3 with a third of the partial sums; QKV from 33 tokens on and O of the tiny shape 0.4 to 0.6 less.
+        // Longer runs lose: O of the 70B shape 28.0 / 28.9 at 16 tokens, down of the 8B shape 28.4 / 29.9 at 64.  In between it
+        // depends on what one share makes of the device: where its splits put exactly two blocks on every unit, 4096 columns, runs of
+        // 16 gain 5 to 8 % at 8 to 144 tokens and runs of 17 to 24 lose up to 3.6 % (22: 19.9 / 20.6 at 64 tokens; 28: 22.6 / 24.1);
+        // where they leave wavefronts to be had, 1024 to 3072 columns, runs of 20 to 24 gain 0.4 to 11 % from 64 tokens on, 5 % less to
+        // 8 % more at 8; where they leave a tail, 5120 columns, 24 gain 13 to 16 % from 64 tokens on.
+        const int run = (KB + s - 1) / s, longest = groups * s == 2 * cus ? 16 : 24;
+        if (kind != GemmOut::SWIGLU_BF16 && KB % 4 == 0 && run <= longest && (N <= K || (M > 32 && (M <= 64 || !wide)))) {
             g.k_shares = 2;
             if (split_opt == 0) s = std::max(1, std::min(s, (3 * cus / 4 + groups / 2) / groups));
         }

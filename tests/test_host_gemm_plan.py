@@ -33,6 +33,14 @@ def test_every_plan_is_valid_and_capped_plans_stay_within_the_other_kernels_memo
     assert int(r.stdout.split()[1]) > 100000
 
 
+def test_streaming_takes_two_k_shares_where_they_measured_faster(planner):
+    # told by the K splits: eight of one share, at most six of two.  4096 columns put two blocks of one share on every compute unit
+    # and gain from two up to runs of 16 k-blocks; fewer columns, and more, up to 24
+    splits = lambda N, K: {p[3] for p in _plans(planner, [(T, N, K, PARTIAL, 1, 0) for T in (8, 64, 97, 144)])}
+    assert splits(4096, 4096) == {3} and splits(2048, 6144) == {6} and splits(3072, 5632) == {4} and splits(5120, 5376) == {2}
+    assert all(splits(4096, K) == {8} for K in (4608, 5632, 6144, 14336)) and splits(3072, 7168) == {8}
+
+
 def test_gpu_tests_of_the_weights_in_registers_gemm_reach_it(planner):
     # test_weights_in_registers_gemm_row_blocks: by the automatic choice, gate/up up to 289 tokens, QKV and down from 257 on
     tokens = [97, 113, 129, 161, 209, 257, 289]
