@@ -88,7 +88,9 @@ typedef struct {
 /* Per-step measurements.  Stages, summed over layers:
  * 0 RMSNorm(attn)  1 QKV GEMM  2 split sum + RoPE + KV append  3 attention (+ split merge)
  * 4 O GEMM  5 split sum + residual + RMSNorm(ffn)  6 gate/up GEMM + SwiGLU
- * 7 down GEMM, split sum + residual (+ the next layer's RMSNorm) */
+ * 7 down GEMM, split sum + residual (+ the next layer's RMSNorm)
+ * Where the QKV GEMM rotates and appends by itself (head dim 64, up to 96 tokens, one K split on the weight-streaming kernel, as
+ * in the tiny shape), its time, here and in ps_gemm_times, holds stage 2 as well, whose own interval is empty. */
 typedef struct {
     int32_t n_tokens;        /* sum of n_new */
     int64_t total_kv;        /* sum of kv_len */

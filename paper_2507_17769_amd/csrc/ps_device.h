@@ -12,7 +12,6 @@ typedef short s16x4_t __attribute__((ext_vector_type(4)));  // 4 bf16 bit patter
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-__device__ __forceinline__ float bf16_to_f32(bf16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
@@ -23,7 +22,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
     v.y = (__bf16)hi;
     return __builtin_bit_cast(uint32_t, v);
 }
-__device__ __forceinline__ bf16_t f32_to_bf16(float x) { return (bf16_t)(pack_bf16(x, 0.f) & 0xFFFFu); }
 
 __device__ __forceinline__ bf16x8_t as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8_t, v); }
 

@@ -10,10 +10,10 @@ namespace ps {
 // ---------------------------------------------------------------------------- RMSNorm
 // One block per token row, one thread per 8 consecutive elements (H <= 8192): out = x * rsqrt(mean(x^2) + eps) * gain,
 // fp32 math, the row held in registers between the sum and the scaling.
-// sum over the block of one value per thread; red: one float per wavefront
-// Sum over a block of n_waves <= 16 wavefronts.  All sums are read from LDS at once: a loop over them waits for each.  With the
-// sum inside a wavefront by DPP and all arguments read at once, the two add+norm launches of a layer of the tiny shape take 0.8 us
-// less; one token of the 8B shape through 32 layers 3331 -> 3307 us with the likes in the rotation and the merge.
+
+// Sum over a block of n_waves <= 16 wavefronts; red: LDS for one float of each.  All sums are read from it at once: a loop over
+// them waits for each.  With the sum inside a wavefront by DPP and all arguments read at once, the two add+norm launches of a layer
+// of the tiny shape take 0.8 us less.
 __device__ __forceinline__ float block_sum(float v, float4 (&red)[4], int n_waves) {
     v = wave_sum(v);
     if ((threadIdx.x & 63) == 0) reinterpret_cast<float*>(red)[threadIdx.x >> 6] = v;
