@@ -24,6 +24,25 @@ struct Staging {  // pinned host buffer for one step's metadata
     size_t bytes = 0;
 };
 
+// Memory of a step's four projections: the largest over them (see gemm_sizes).
+struct LayerNeeds {
+    size_t act_bytes, part_bytes, skfrag_bytes;
+    int skcnt_n;
+};
+
+// Where the buffers of a step lie in the static scratch array; `total` may exceed the array.
+struct StaticLayout {
+    size_t xn, q, attn, act, x1, xmid, part, part_o, part_ml, meta, skfrag, skcnt, total;
+    size_t act_bytes, part_bytes, skfrag_bytes;
+    int skcnt_n;
+};
+
+struct StepMemory {
+    GemmOptions gemm;      // of the layers' projections
+    LayerNeeds needs;
+    StaticLayout layout;
+};
+
 }  // namespace ps
 
 using namespace ps;
@@ -121,6 +140,7 @@ struct ps_ctx {
     hipEvent_t ev[PS_N_STAGES * 2 + 2] = {};
     bool have_events = false;
     StepPlan plan;
+    StepMemory memory{};   // goes with it
 };
 
 static constexpr int ATTN_EV_PAIRS = 2048;
@@ -628,10 +648,10 @@ extern "C" ps_status ps_kv_read(ps_ctx* c, int32_t layer, const ps_seq* seq, int
 }
 
 // ------------------------------------------------------------------------------ planning
-static bool static_fits(const ps_ctx* c, const StepPlan& p);
-static bool static_fits_without_partials(const ps_ctx* c, const StepPlan& p);
+static void plan_memory(ps_ctx* c, const PlanConfig& pc);
 
-static ps_status make_plan(ps_ctx* c, const ps_seq* seqs, int32_t n_seqs, bool with_attention) {
+// for_step: with what step_impl needs to know of the step's memory (of the attention plan, it only depends on two blocks per unit)
+static ps_status make_plan(ps_ctx* c, const ps_seq* seqs, int32_t n_seqs, bool with_attention, bool for_step) {
     const PlanConfig pc = plan_config(c);
     std::string err;
     ps_status st = validate_batch(seqs, n_seqs, pc, c->page_seen, err);
@@ -639,20 +659,13 @@ static ps_status make_plan(ps_ctx* c, const ps_seq* seqs, int32_t n_seqs, bool w
     build_indices(seqs, n_seqs, c->plan);
     if (!with_attention) return PS_OK;
     build_attention_plan(pc, c->plan);
-    // A step whose partials the static scratch cannot hold even so (see step_static_layout), but could hold those of one block per
-    // compute unit, gets those, whichever call runs it, so that ps_step_static takes it and gives the bits of ps_step.
-    if (c->plan.two_blocks_per_cu && static_fits_without_partials(c, c->plan) && !static_fits(c, c->plan)) {
-        PlanConfig one = pc;
-        one.one_block_per_cu = true;
-        build_attention_plan(one, c->plan);
-        if (!static_fits(c, c->plan)) build_attention_plan(pc, c->plan);
-    }
+    if (n_seqs > 0 && (for_step || c->plan.two_blocks_per_cu)) plan_memory(c, pc);
     return PS_OK;
 }
 
 extern "C" ps_status ps_step_indices(ps_ctx* c, const ps_seq* seqs, int32_t n_seqs, int32_t* cu_seqlens, int32_t* positions, int32_t* slot_mapping) {
     if (!c) return PS_EINVAL;
-    ps_status st = make_plan(c, seqs, n_seqs, false);
+    ps_status st = make_plan(c, seqs, n_seqs, false, false);
     if (st != PS_OK) return st;
     const StepPlan& p = c->plan;
     if (cu_seqlens) std::copy(p.cu_seqlens.begin(), p.cu_seqlens.end(), cu_seqlens);
@@ -663,7 +676,7 @@ extern "C" ps_status ps_step_indices(ps_ctx* c, const ps_seq* seqs, int32_t n_se
 
 extern "C" ps_status ps_plan_attention(ps_ctx* c, const ps_seq* seqs, int32_t n_seqs, int32_t* items, int32_t cap, int32_t* n_items) {
     if (!c || !n_items || (!items && cap > 0)) return fail(c, PS_EINVAL, "ps_plan_attention: null argument");
-    ps_status st = make_plan(c, seqs, n_seqs, true);
+    ps_status st = make_plan(c, seqs, n_seqs, true, false);
     if (st != PS_OK) return st;
     const StepPlan& p = c->plan;
     *n_items = (int32_t)p.items.size();
@@ -699,30 +712,23 @@ static GemmOptions head_options(const ps_ctx* c) {
     return o;
 }
 
-// What the tiled GEMM needs beside its output for a step of T tokens: the largest over the layer's four projections.
-static void sk_need(const ps_ctx* c, int T, int head_rows, const GemmOptions& o, size_t* frag_bytes, int* n_counters) {
+// Memory of a step's projections.
+static LayerNeeds layer_needs(const ps_ctx* c, int T, const GemmOptions& o) {
     const ps_model_desc& d = c->desc;
-    const int H = d.hidden, F = d.ffn, NQ = d.n_q_heads * d.head_dim, NQKV = qkv_cols(d);
-    const int shapes[4][3] = {{NQKV, H, GemmOut::PARTIAL_F32}, {H, NQ, GemmOut::PARTIAL_F32}, {2 * F, H, GemmOut::SWIGLU_BF16}, {H, F, GemmOut::PARTIAL_F32}};
-    *frag_bytes = 0;
-    *n_counters = 0;
+    const int H = d.hidden, F = d.ffn, NQ = d.n_q_heads * d.head_dim;
+    const int shapes[4][3] = {{qkv_cols(d), H, GemmOut::PARTIAL_F32}, {H, NQ, GemmOut::PARTIAL_F32}, {2 * F, H, GemmOut::SWIGLU_BF16}, {H, F, GemmOut::PARTIAL_F32}};
+    LayerNeeds n{0, 0, 0, 0};
     for (const auto& sh : shapes) {
-        size_t fb = 0;
-        int nc = 0;
-        gemm_workspace(T, sh[0], sh[1], sh[2], o, &fb, &nc);
-        *frag_bytes = std::max(*frag_bytes, fb);
-        *n_counters = std::max(*n_counters, nc);
+        const GemmSizes z = gemm_sizes(T, sh[0], sh[1], sh[2], o);
+        size_t& out = sh[2] == GemmOut::SWIGLU_BF16 ? n.act_bytes : n.part_bytes;
+        out = std::max(out, z.out_bytes);
+        n.skfrag_bytes = std::max(n.skfrag_bytes, z.frag_bytes);
+        n.skcnt_n = std::max(n.skcnt_n, z.n_counters);
     }
-    if (head_rows > 0) {   // the output projection: one row per sequence
-        size_t fb = 0;
-        int nc = 0;
-        gemm_workspace(head_rows, c->vocab, H, GemmOut::PARTIAL_F32, head_options(c), &fb, &nc);
-        *frag_bytes = std::max(*frag_bytes, fb);
-        *n_counters = std::max(*n_counters, nc);
-    }
+    return n;
 }
 
-static ps_status ensure_workspaces(ps_ctx* c, int T, int n_part_slots, int head_rows, const GemmOptions& o) {
+static ps_status ensure_workspaces(ps_ctx* c, int T, int n_part_slots, int head_rows, const LayerNeeds& needs, const GemmOptions& o) {
     const ps_model_desc& d = c->desc;
     if (T > c->cap_tokens) {
         HIP_TRY(c, hipStreamSynchronize(c->stream));
@@ -735,7 +741,7 @@ static ps_status ensure_workspaces(ps_ctx* c, int T, int n_part_slots, int head_
         if ((st = dev_alloc(c, &c->ws_xn, (size_t)cap16 * H * 2, "xn")) != PS_OK) return st;
         if ((st = dev_alloc(c, &c->ws_q, (size_t)cap * NQ * 2, "q")) != PS_OK) return st;
         if ((st = dev_alloc(c, &c->ws_attn, (size_t)cap16 * NQ * 2, "attn")) != PS_OK) return st;
-        c->act_bytes = gemm_out_bytes(cap, 2 * F, H, GemmOut::SWIGLU_BF16, o);  // whole row tiles of the GEMM
+        c->act_bytes = gemm_sizes(cap, 2 * F, H, GemmOut::SWIGLU_BF16, o).out_bytes;  // whole row tiles of the GEMM
         if ((st = dev_alloc(c, &c->ws_act, c->act_bytes, "act")) != PS_OK) return st;
         if ((st = dev_alloc(c, &c->ws_x1, (size_t)cap * H * 4, "x1")) != PS_OK) return st;
         if (d.n_layers > 1 && (st = dev_alloc(c, &c->ws_xmid, (size_t)cap * H * 4, "inter-layer x")) != PS_OK) return st;
@@ -746,10 +752,7 @@ static ps_status ensure_workspaces(ps_ctx* c, int T, int n_part_slots, int head_
         c->cap_tokens = cap;
     }
     {   // GEMM partial buffer: sized for this step's T (the split count depends on T)
-        const int H = d.hidden, F = d.ffn, NQ = d.n_q_heads * d.head_dim, NQKV = qkv_cols(d);
-        size_t need = gemm_out_bytes(T, NQKV, H, GemmOut::PARTIAL_F32, o);
-        need = std::max(need, gemm_out_bytes(T, H, NQ, GemmOut::PARTIAL_F32, o));
-        need = std::max(need, gemm_out_bytes(T, H, F, GemmOut::PARTIAL_F32, o));
+        const size_t need = needs.part_bytes;
         if (need > c->part_bytes) {
             HIP_TRY(c, hipStreamSynchronize(c->stream));
             dev_free(c->ws_part);
@@ -761,9 +764,13 @@ static ps_status ensure_workspaces(ps_ctx* c, int T, int n_part_slots, int head_
         }
     }
     {   // tiled GEMM workspace
-        size_t fb = 0;
-        int nc = 0;
-        sk_need(c, T, head_rows, o, &fb, &nc);
+        size_t fb = needs.skfrag_bytes;
+        int nc = needs.skcnt_n;
+        if (head_rows > 0) {   // the output projection: one row per sequence
+            const GemmSizes z = gemm_sizes(head_rows, c->vocab, d.hidden, GemmOut::PARTIAL_F32, head_options(c));
+            fb = std::max(fb, z.frag_bytes);
+            nc = std::max(nc, z.n_counters);
+        }
         if (fb > c->skfrag_bytes) {
             HIP_TRY(c, hipStreamSynchronize(c->stream));
             dev_free(c->ws_skfrag);
@@ -839,17 +846,11 @@ struct StepBufs {
     char* meta = nullptr;  // static steps only: device copy of the metadata
 };
 
-// Where the buffers of a step of T tokens lie in the static scratch array; `total` may exceed the array.
-struct StaticLayout {
-    size_t xn, q, attn, act, x1, xmid, part, part_o, part_ml, meta, skfrag, skcnt, total;
-    size_t act_bytes, part_bytes, skfrag_bytes;
-    int skcnt_n;
-};
 // partials_shared: the attention partials, which live from the attention launch to its merge, lie over what only the projections
 // use, none of which runs in between (the counters of the tiled GEMM keep a place of their own: they have to stay zero).
-static StaticLayout static_layout(const ps_ctx* c, int T, int n_part_slots, size_t meta_bytes, const GemmOptions& o, bool partials_shared) {
+static StaticLayout static_layout(const ps_ctx* c, int T, int n_part_slots, size_t meta_bytes, const LayerNeeds& needs, bool partials_shared) {
     const ps_model_desc& d = c->desc;
-    const int H = d.hidden, F = d.ffn, NQ = d.n_q_heads * d.head_dim, NQKV = qkv_cols(d);
+    const int H = d.hidden, NQ = d.n_q_heads * d.head_dim;
     const size_t T16 = (size_t)((T + 15) & ~15);
     StaticLayout m;
     size_t at = 0;
@@ -857,61 +858,69 @@ static StaticLayout static_layout(const ps_ctx* c, int T, int n_part_slots, size
     m.xn = take(T16 * H * 2); m.q = take((size_t)T * NQ * 2); m.attn = take(T16 * NQ * 2);
     m.x1 = take((size_t)T * H * 4); m.xmid = take(d.n_layers > 1 ? (size_t)T * H * 4 : 0);
     m.meta = take(meta_bytes);
-    int n_cnt = 0;
-    sk_need(c, T, 0, o, &m.skfrag_bytes, &n_cnt);
-    m.skcnt_n = (n_cnt + 3) & ~3;
+    m.skcnt_n = (needs.skcnt_n + 3) & ~3;
     m.skcnt = take((size_t)m.skcnt_n * sizeof(int));
     const size_t shared = at;
     m.part_o = take((size_t)n_part_slots * 16 * d.head_dim * 4); m.part_ml = take((size_t)n_part_slots * 16 * 2 * 4);
     const size_t partials_end = at;
     if (partials_shared) at = shared;
-    m.act_bytes = gemm_out_bytes(T, 2 * F, H, GemmOut::SWIGLU_BF16, o);
-    m.act = take(m.act_bytes);
-    m.part_bytes = gemm_out_bytes(T, NQKV, H, GemmOut::PARTIAL_F32, o);
-    m.part_bytes = std::max(m.part_bytes, gemm_out_bytes(T, H, NQ, GemmOut::PARTIAL_F32, o));
-    m.part_bytes = std::max(m.part_bytes, gemm_out_bytes(T, H, F, GemmOut::PARTIAL_F32, o));
-    m.part = take(m.part_bytes);
-    m.skfrag = take(m.skfrag_bytes);
+    m.act_bytes = needs.act_bytes; m.act = take(m.act_bytes);
+    m.part_bytes = needs.part_bytes; m.part = take(m.part_bytes);
+    m.skfrag_bytes = needs.skfrag_bytes; m.skfrag = take(m.skfrag_bytes);
     m.total = std::max(at, partials_end);
     return m;
 }
 
-// GEMM options of a step's layers.  A function of the batch and the options of the context alone, not of the call: a batch
-// that the static scratch can hold is planned within it by every call, so that ps_step_static gives the bits of ps_step.
-static GemmOptions layer_gemm_options(const ps_ctx* c, const StepPlan& p) {
-    GemmOptions o = gemm_options(c);
-    o.cap_splits = true;
-    o.cap_splits = static_layout(c, p.n_tokens, p.n_partial_slots, meta_layout(p, false).total, o, false).total <= (size_t)PS_STATIC_SCRATCH_BYTES;
-    return o;
-}
-
-// The layout of a static step.  Where its buffers do not fit side by side, the partials of a plan with two blocks on a compute
-// unit, twice those of one, share their place: the plan stays what is fastest for ps_step, which has to run the same one.
-static StaticLayout step_static_layout(const ps_ctx* c, const StepPlan& p, size_t meta_bytes, const GemmOptions& o) {
-    const StaticLayout m = static_layout(c, p.n_tokens, p.n_partial_slots, meta_bytes, o, false);
-    if (m.total <= (size_t)PS_STATIC_SCRATCH_BYTES || !p.two_blocks_per_cu) return m;
-    return static_layout(c, p.n_tokens, p.n_partial_slots, meta_bytes, o, true);
-}
-
-// Whether a plan with fewer partials could make the step fit.
-static bool static_fits_without_partials(const ps_ctx* c, const StepPlan& p) {
-    GemmOptions o = gemm_options(c);
-    o.cap_splits = true;
-    return static_layout(c, p.n_tokens, 0, 0, o, false).total <= (size_t)PS_STATIC_SCRATCH_BYTES;
-}
-
-// Whether ps_step_static takes a step with this plan.
-static bool static_fits(const ps_ctx* c, const StepPlan& p) {
-    const size_t meta = meta_layout(p, false).total;
-    return meta <= STATIC_META_SLOT && step_static_layout(c, p, meta, layer_gemm_options(c, p)).total <= (size_t)PS_STATIC_SCRATCH_BYTES;
+// GEMM options and memory of the step that c->plan is for, and its attention plan once more where the scratch makes it another.
+// All of it is a function of the batch and the options of the context alone, not of the call: a batch that the static scratch can
+// hold is planned within it by every call, so that ps_step_static gives the bits of ps_step.
+//
+// Where the buffers of a step do not fit side by side, the partials of a plan with two blocks on a compute unit, twice those of
+// one, share their place: the plan stays what is fastest for ps_step, which has to run the same one.  Where not even that fits, but
+// the partials of one block per unit do, the step gets those.
+//
+// The GEMM plans behind a layout take the host some 10 us, and a step that is waited for shows them: they are made once for each
+// kind of options, and not at all for the capped ones where the scratch cannot hold the rows of the step.
+static void plan_memory(ps_ctx* c, const PlanConfig& pc) {
+    const size_t limit = PS_STATIC_SCRATCH_BYTES;
+    const int T = c->plan.n_tokens;
+    GemmOptions capped = gemm_options(c), free_splits = capped;
+    capped.cap_splits = true;
+    LayerNeeds needs_capped{}, needs_free{};
+    const bool small = static_layout(c, T, 0, 0, needs_free, false).total <= limit;
+    if (small) needs_capped = layer_needs(c, T, capped);
+    const bool fits_without_partials = small && static_layout(c, T, 0, 0, needs_capped, false).total <= limit;
+    bool have_free = false;
+    auto place = [&]() {   // true: ps_step_static takes the step with this plan
+        const StepPlan& p = c->plan;
+        const size_t meta = meta_layout(p, false).total;
+        if (fits_without_partials) {
+            c->memory = StepMemory{capped, needs_capped, static_layout(c, T, p.n_partial_slots, meta, needs_capped, false)};
+            if (c->memory.layout.total <= limit) return meta <= STATIC_META_SLOT;
+        }
+        if (!have_free) needs_free = layer_needs(c, T, free_splits);
+        have_free = true;
+        c->memory = StepMemory{free_splits, needs_free, static_layout(c, T, p.n_partial_slots, meta, needs_free, p.two_blocks_per_cu)};
+        return c->memory.layout.total <= limit && meta <= STATIC_META_SLOT;
+    };
+    if (place() || !c->plan.two_blocks_per_cu || !fits_without_partials) return;
+    AttnPlan& plan = c->plan;
+    AttnPlan two = std::move(plan);
+    const StepMemory memory = c->memory;
+    PlanConfig one = pc;
+    one.one_block_per_cu = true;
+    build_attention_plan(one, c->plan);
+    if (place()) return;
+    plan = std::move(two);
+    c->memory = memory;
 }
 
 // The buffers of a static step.  Nothing is allocated: a step whose buffers do not fit PS_STATIC_SCRATCH_BYTES is refused.
-static ps_status carve_static(ps_ctx* c, const StepPlan& p, size_t meta_bytes, StepBufs* w) {
+static ps_status carve_static(ps_ctx* c, size_t meta_bytes, StepBufs* w) {
     if (meta_bytes > STATIC_META_SLOT)
         return fail(c, PS_ERANGE, "ps_step_static: the step's metadata (" + std::to_string(meta_bytes) + " bytes: positions, page lists, attention work list) exceeds " +
                                       std::to_string(STATIC_META_SLOT) + " bytes; use ps_step for batches of this size");
-    const StaticLayout m = step_static_layout(c, p, meta_bytes, w->gemm);
+    const StaticLayout& m = c->memory.layout;
     if (m.total > (size_t)PS_STATIC_SCRATCH_BYTES)
         return fail(c, PS_ERANGE, "ps_step_static: the step needs " + std::to_string(m.total) + " bytes of scratch, the static array holds " +
                                       std::to_string((size_t)PS_STATIC_SCRATCH_BYTES) + "; use ps_step for batches of this size");
@@ -934,7 +943,7 @@ static ps_status step_impl(ps_ctx* c, const ps_seq* seqs, int32_t n_seqs, const 
     if (!c->pool) return fail(c, PS_ESTATE, "ps_step: no KV pool (call ps_kv_alloc)");
     for (int l = 0; l < c->desc.n_layers; l++)
         if (!c->layers[l].ready) return fail(c, PS_ESTATE, "ps_step: layer " + std::to_string(l) + " has no weights (call ps_init_layer)");
-    ps_status st = make_plan(c, seqs, n_seqs, true);
+    ps_status st = make_plan(c, seqs, n_seqs, true, true);
     if (st != PS_OK) return st;
     const StepPlan& p = c->plan;
     if (stats) {
@@ -965,11 +974,11 @@ static ps_status step_impl(ps_ctx* c, const ps_seq* seqs, int32_t n_seqs, const 
     const int T = p.n_tokens, H = d.hidden, F = d.ffn, NQ = d.n_q_heads * d.head_dim, NQKV = qkv_cols(d);
     const MetaLayout ml = meta_layout(p, tio != nullptr);
     StepBufs W;
-    W.gemm = layer_gemm_options(c, p);
+    W.gemm = c->memory.gemm;
     if (use_static) {
-        if ((st = carve_static(c, p, ml.total, &W)) != PS_OK) return st;
+        if ((st = carve_static(c, ml.total, &W)) != PS_OK) return st;
     } else {
-        if ((st = ensure_workspaces(c, T, p.n_partial_slots, tio ? p.n_seqs : 0, W.gemm)) != PS_OK) return st;
+        if ((st = ensure_workspaces(c, T, p.n_partial_slots, tio ? p.n_seqs : 0, c->memory.needs, W.gemm)) != PS_OK) return st;
         W.xn = c->ws_xn; W.q = c->ws_q; W.attn = c->ws_attn; W.act = c->ws_act; W.x1 = c->ws_x1; W.xmid = c->ws_xmid;
         W.part = c->ws_part; W.part_o = c->part_o; W.part_ml = c->part_ml; W.part_bytes = c->part_bytes; W.act_bytes = c->act_bytes;
         W.skfrag = c->ws_skfrag; W.skfrag_bytes = c->skfrag_bytes; W.skcnt = c->ws_skcnt; W.skcnt_n = c->skcnt_n;

@@ -651,11 +651,7 @@ static int device_cus() {
 
 static int plan_cus(const GemmOptions& o) { return o.cus > 0 ? o.cus : device_cus(); }
 
-size_t gemm_out_bytes(int M, int N, int K, int kind, const GemmOptions& o) { return gemm_plan_out_bytes(M, N, K, kind, o, plan_cus(o)); }
-
-void gemm_workspace(int M, int N, int K, int kind, const GemmOptions& o, size_t* frag_bytes, int* n_counters) {
-    gemm_plan_workspace(M, N, K, kind, o, plan_cus(o), frag_bytes, n_counters);
-}
+GemmSizes gemm_sizes(int M, int N, int K, int kind, const GemmOptions& o) { return gemm_plan_sizes(M, N, K, kind, o, plan_cus(o)); }
 
 template <int BM, int BN, int NS, int KIND>
 static hipError_t launch_sk(const GemmParams& p, const GemmArgs& a, const GemmPlan& g, hipStream_t st) {
@@ -696,7 +692,7 @@ hipError_t launch_gemm(const GemmArgs& a, int* n_splits, hipStream_t st) {
         return hipErrorInvalidValue;
     const GemmPlan g = plan_gemm(a.M, a.N, a.K, a.kind, a.opt, device_cus());
     if ((size_t)g.splits * (a.kind == GemmOut::SWIGLU_BF16 ? 0 : (size_t)a.M * a.N * sizeof(float)) > a.out_bytes ||
-        (a.kind == GemmOut::SWIGLU_BF16 && gemm_out_bytes(a.M, a.N, a.K, a.kind, a.opt) > a.out_bytes))
+        (a.kind == GemmOut::SWIGLU_BF16 && gemm_sizes(a.M, a.N, a.K, a.kind, a.opt).out_bytes > a.out_bytes))
         return hipErrorInvalidValue;
     GemmParams p;
     p.A = a.A; p.Wp = a.Wp; p.M = a.M; p.N = a.N; p.K = a.K; p.kind = a.kind; p.out = a.out;

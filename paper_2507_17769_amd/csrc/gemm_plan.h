@@ -283,28 +283,40 @@ inline GemmPlan plan_gemm(int M, int N, int K, int kind, const GemmOptions& o, i
     return g;
 }
 
-// Bytes of the output of launch_gemm for these options.
-inline size_t gemm_plan_out_bytes(int M, int N, int K, int kind, const GemmOptions& o, int cus) {
+// Memory of a product with these options, all of one plan: the output of launch_gemm, and what it needs beside it (0 unless the
+// tiled kernel serves the product and cuts its tail: only the blocks that share a tile count in on it).
+struct GemmSizes {
+    size_t out_bytes, frag_bytes;
+    int n_counters;
+};
+inline GemmSizes gemm_plan_sizes(int M, int N, int K, int kind, const GemmOptions& o, int cus) {
+    GemmSizes z{0, 0, 0};
+    if (M <= 0) return z;
+    const GemmPlan g = plan_gemm(M, N, K, kind, o, cus);
     if (kind == GemmOut::SWIGLU_BF16) {
         // dense [rows][N/2] in operand order.  The tiled kernel stores whole row tiles without a row check
         // (rows past M are never read back), so the buffer holds M rounded up to its largest tile.
         const size_t rows = M <= 64 ? (size_t)((M + 15) / 16 * 16) : (size_t)((M + 255) / 256 * 256);
-        return rows * (N / 2) * sizeof(uint16_t);
+        z.out_bytes = rows * (N / 2) * sizeof(uint16_t);
+    } else {
+        z.out_bytes = (size_t)g.splits * M * N * sizeof(float);
     }
-    return (size_t)plan_gemm(M, N, K, kind, o, cus).splits * M * N * sizeof(float);
+    if (g.cut_tail) {
+        const int b = g.big_tile ? 256 : 128;
+        z.frag_bytes = (size_t)8 * g.slots_per_xcd * b * b * sizeof(float);
+        z.n_counters = ((M + b - 1) / b) * ((N + b - 1) / b);
+    }
+    return z;
 }
 
-// What launch_gemm needs beside its output (both 0 unless the tiled kernel serves the product and cuts its tail: only the
-// blocks that share a tile count in on it).
+inline size_t gemm_plan_out_bytes(int M, int N, int K, int kind, const GemmOptions& o, int cus) {
+    return gemm_plan_sizes(M, N, K, kind, o, cus).out_bytes;
+}
+
 inline void gemm_plan_workspace(int M, int N, int K, int kind, const GemmOptions& o, int cus, size_t* frag_bytes, int* n_counters) {
-    *frag_bytes = 0;
-    *n_counters = 0;
-    if (M <= 0) return;
-    const GemmPlan g = plan_gemm(M, N, K, kind, o, cus);
-    if (!g.cut_tail) return;
-    const int b = g.big_tile ? 256 : 128;
-    *frag_bytes = (size_t)8 * g.slots_per_xcd * b * b * sizeof(float);
-    *n_counters = ((M + b - 1) / b) * ((N + b - 1) / b);
+    const GemmSizes z = gemm_plan_sizes(M, N, K, kind, o, cus);
+    *frag_bytes = z.frag_bytes;
+    *n_counters = z.n_counters;
 }
 
 }  // namespace ps

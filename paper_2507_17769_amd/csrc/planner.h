@@ -8,15 +8,8 @@
 
 namespace ps {
 
-struct StepPlan {
-    int n_seqs = 0;
-    int n_tokens = 0;
-    int64_t total_kv = 0;
-    std::vector<int32_t> cu_seqlens;  // [n_seqs + 1]
-    std::vector<int32_t> positions;   // [T]
-    std::vector<int32_t> slots;       // [T]
-    std::vector<SeqInfo> seqs;        // [n_seqs]
-    std::vector<int32_t> pages;       // flat page lists (only the ceil(kv_len/16) pages in use)
+// The attention work of a step.
+struct AttnPlan {
     std::vector<AttnItem> items;        // grouped by worker, in worker order
     std::vector<int32_t> worker_begin;  // [n_workers + 1]; the first n_team_workers workers are teams (blocks of four
                                         // wavefronts), the others single wavefronts
@@ -25,6 +18,17 @@ struct StepPlan {
     std::vector<MergeGroup> groups;
     int n_partial_slots = 0;
     int n_partial_items = 0;
+};
+
+struct StepPlan : AttnPlan {
+    int n_seqs = 0;
+    int n_tokens = 0;
+    int64_t total_kv = 0;
+    std::vector<int32_t> cu_seqlens;  // [n_seqs + 1]
+    std::vector<int32_t> positions;   // [T]
+    std::vector<int32_t> slots;       // [T]
+    std::vector<SeqInfo> seqs;        // [n_seqs]
+    std::vector<int32_t> pages;       // flat page lists (only the ceil(kv_len/16) pages in use)
 };
 
 struct PlanConfig {

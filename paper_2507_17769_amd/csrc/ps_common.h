@@ -133,10 +133,10 @@ struct GemmArgs {
     int M, N, K;
     int kind;          // GemmOut::Kind
     void* out;         // PARTIAL_F32: fp32 [splits][M][N] row-major; SWIGLU_BF16: bf16 [M][N/2] in operand order
-    size_t out_bytes;  // capacity of out; at least gemm_out_bytes(...)
+    size_t out_bytes;  // capacity of out (see gemm_sizes)
     GemmOptions opt;
     RopeOut rope;      // QKV only: where the GEMM can, it rotates and appends itself instead of writing out
-    // tiled kernel only (see gemm_workspace): parked accumulators of K runs that cover part of a tile, and one counter
+    // tiled kernel only (see gemm_sizes): parked accumulators of K runs that cover part of a tile, and one counter
     // per tile that must be zero on entry (the kernel leaves it zero)
     float* sk_frag;
     size_t sk_frag_bytes;
@@ -145,9 +145,8 @@ struct GemmArgs {
 };
 // *n_splits receives the number of partial buffers written (1 for SWIGLU_BF16; 0 where rope took the product)
 hipError_t launch_gemm(const GemmArgs& a, int* n_splits, hipStream_t st);
-size_t gemm_out_bytes(int M, int N, int K, int kind, const GemmOptions& o);
-// what launch_gemm needs in sk_frag / sk_counters for this shape (both 0 unless the tiled kernel serves it)
-void gemm_workspace(int M, int N, int K, int kind, const GemmOptions& o, size_t* frag_bytes, int* n_counters);
+// what launch_gemm needs in out and in sk_frag / sk_counters for this shape
+GemmSizes gemm_sizes(int M, int N, int K, int kind, const GemmOptions& o);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st);   // bytes: rounded down to a multiple of 16
 hipError_t launch_fill_words(void* p, size_t bytes, uint32_t word, hipStream_t st);
 
