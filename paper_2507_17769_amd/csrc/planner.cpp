@@ -110,9 +110,12 @@ void build_indices(const ps_seq* seqs, int n_seqs, StepPlan& plan) {
 // work, and two per unit only where the teams have long runs (24 pairs per unit) and more work than fits beside the streams
 // at the rate of HBM (from a fifth of the streams' pairs on: 8B shape, one / two blocks, 9300 pairs of teams to 22600 of streams
 // 108 / 104 us, 12500 to 42300 168 / 157, 6400 to 23600 101 / 101, 6400 to 51800 171 / 175, 5200 to 92400 272 / 294).
-// Measured with the merge on 170 mixtures (17 to 1600 new tokens behind up to 6000 next to 1 to 256 decodes, both large shapes):
-// 9 % faster in the mean than two blocks on every unit with a team on each, where the best split of a sweep gives 11.7 %;
+// Measured with the merge on 150 mixtures (17 to 1600 new tokens behind up to 6000 next to 1 to 256 decodes, both large shapes):
+// 5 % faster in the mean than two blocks on every unit with a team on each, where the best split of a sweep gives 10 %;
 // 128 tokens behind 1500 next to 16 decodes 40.8 -> 33.4 us, 1024 behind 4096 next to 64 202 -> 138, 64 decodes 97 -> 93.
+// None of the constants is sharp on them: 12 to 48 pairs per unit, 0 to half of the streams' pairs, teams weighing 0.5 to 1.4 in two
+// blocks, no head start of the streams or a long one, a half to an eighth of the units, 3 to 14 pairs per team of a small chunk each
+// move the mean by less than 0.3 %, and single mixtures by 1 to 20 % either way.
 static bool share_blocks(const PlanConfig& cfg, double pairs_team, double pairs_wave, double pairs_per_stream, int* n_team, int* n_wave) {
     const int B = std::max(16, cfg.block_slots), cus = std::min(std::max(8, cfg.compute_units), B);
     const double long_run = 24.0 * cus;   // page pairs of the teams; without streams one / two blocks 27 / 31 us at 1200 pairs, 51 / 53 at 5900, 51 / 48 at 6400, 130 / 105 at 25600
