@@ -223,8 +223,8 @@ ps_status ps_step(ps_ctx* ctx, const ps_seq* seqs, int32_t n_seqs, const void* x
  * events are made by ps_create); host-side planning arrays live on the process heap.  Results are
  * bit-identical to ps_step's for the same batch and options.
  * Limits: the buffers of the step must fit the array and its metadata 512 KiB, otherwise PS_ERANGE and nothing
- * is launched (decode batches: an 8B-shaped layer fits 160 one-token sequences, a 70B-shaped one 96; steps with
- * a prefill chunk of hundreds of tokens do not fit; the message states the bytes needed).  No per-stage
+ * is launched (layers of the 8B shape fit 300 one-token sequences or a prefill chunk of 240 tokens next to 16 of them, of the
+ * 70B shape 150 and 90; larger chunks do not fit; the message states the bytes needed).  No per-stage
  * statistics.  All contexts of a process on one GPU share that GPU's array, which keeps the previous call's
  * contents (the one piece that has to start at zero, the arrival counters of the tiled GEMM, the call clears
  * itself with a fill kernel): static

@@ -71,8 +71,8 @@ def test_static_step_matches_ps_step_twice_in_a_row_second_call_smaller():
 
 
 def test_static_step_8b_layer_decode_batch_then_a_smaller_one():
-    """The 64-decode batch of the 8B-shaped layer (about 40 MiB of the array: split partials of 2048 attention
-    workers, six fp32 partial sums of the QKV projection), then 8 decodes on the same context."""
+    """The 64-decode batch of the 8B-shaped layer (about 23 MiB of the array: split partials of 832 attention
+    workers, eight fp32 partial sums of the down projection), then 8 decodes on the same context."""
     b = W.config_batch(1, seed=0)
     eng = Engine(b.model, b.n_pool_pages, 1, 1, max_position=max(s.kv_len for s in b.seqs) + 16)
     eng.n_kv_layers = 1
