@@ -120,14 +120,15 @@ def _random_cache(eng, n_pages):
         eng.ctx.sync()
 
 
-@pytest.mark.parametrize("chunks,decodes,blocks", [
-    ([(128, 8192)], [1000] * 4, 2),      # 480 teams
-    ([(128, 8192)], [2000] * 32, 2),     # as many teams as compute units, and as many blocks of streams
-    ([(150, 8192)], [], 2),              # 512 teams
-    ([(5, 4000)] * 20, [500], 1),        # the partials of two blocks fit nowhere
-    ([(5, 4000)] * 20, [], 1),
+@pytest.mark.parametrize("chunks,decodes,blocks,options", [
+    ([(128, 8192)], [1000] * 4, 2, {}),      # 480 teams
+    ([(128, 8192)], [2000] * 32, 2, {}),     # as many teams as compute units, and as many blocks of streams
+    ([(150, 8192)], [], 2, {}),              # 512 teams
+    ([(100, 8192)], [], 2, {"gemm_tile": 128, "gemm_whole_tiles": 2}),   # with parked accumulators and arrival counters
+    ([(5, 4000)] * 20, [500], 1, {}),        # the partials of two blocks fit nowhere
+    ([(5, 4000)] * 20, [], 1, {}),
 ])
-def test_static_step_8b_layers_of_chunks_behind_long_prefixes(chunks, decodes, blocks):
+def test_static_step_8b_layers_of_chunks_behind_long_prefixes(chunks, decodes, blocks, options):
     """Chunks with runs long enough for two blocks on a compute unit, whose partials do not fit beside the other buffers: they lie
     over those that only the projections use or, if that is not enough, the plan has one block per unit.  Two layers, so that the
     shared place is used by either side in turn."""
@@ -137,11 +138,15 @@ def test_static_step_8b_layers_of_chunks_behind_long_prefixes(chunks, decodes, b
     for layer in range(2):
         eng.load_layer(layer, W.layer_weights(b.model, 7, layer))
     try:
+        for name, value in options.items():
+            eng.ctx.set_option(name, value)
         items = eng.ctx.plan_attention(b.seqs)
         n_team = len(set(items[items[:, 0] < len(chunks), 7].tolist()))
         assert (n_team + (int(items[:, 7].max()) + 1 - n_team + 3) // 4 + 255) // 256 == blocks
         _random_cache(eng, b.n_pool_pages)
         eng.ctx.set_option("poison_workspaces", 1)
-        _assert_same(_both_ways(eng, b, b.activations()), f"{chunks} {len(decodes)} decodes")
+        x_bits = b.activations()
+        for _ in range(2 if options else 1):   # counters that a step left behind would show in the next
+            _assert_same(_both_ways(eng, b, x_bits), f"{chunks} {len(decodes)} decodes {options}")
     finally:
         eng.close()
